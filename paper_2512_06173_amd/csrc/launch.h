@@ -21,9 +21,6 @@ hipError_t sweep_shell_f64(const FieldPtrs<double>& in, const FieldPtrs<double>&
 hipError_t sweep_shell_f32(const FieldPtrs<float>& in, const FieldPtrs<float>& out, const Geom& g,
                            const Box& inner, bool h_pass, hipStream_t st);
 // Two-level step of every two-level emitter under E~ (M x 3, emitter-id order).
-// E~ of every emitter (id order) under the travelling pulse at time t.
-hipError_t wave_field(int M, const double* pos, const double* gamma, const WaveDesc& w, double t,
-                      double* Et, hipStream_t st);
 hipError_t tls_step(const TlsPtrs& tls, double dt, const double* Et, double* mudot,
                     const int64_t* pop_off, const Series& ser, const int64_t* step,
                     hipStream_t st);
@@ -31,6 +28,12 @@ hipError_t tls_step(const TlsPtrs& tls, double dt, const double* Et, double* mud
 hipError_t ml_step(const MlDev& ml, const int* range, double dt, const double* Et, double* mudot,
                    const int64_t* pop_off, const Series& ser, const int64_t* step,
                    hipStream_t st);
+// nsteps classical-path steps of every emitter under f; the states after every step go
+// to out (nsteps x two-level emitters x 3, null: not recorded), the last step's E~ and
+// mu_dot to last and mudot (emitter-id order).
+hipError_t prescribed_steps(const TlsPtrs& tls, const MlDev& ml, const int* range, double dt,
+                            PrescribedField f, int64_t nsteps, double* last, double* mudot,
+                            double* out, const Series& ser, const int64_t* step, hipStream_t st);
 hipError_t sources_f64(const FieldPtrs<double>& f, const Geom& g, const SourceSet& src,
                        const int64_t* step, hipStream_t st);
 hipError_t sources_f32(const FieldPtrs<float>& f, const Geom& g, const SourceSet& src,

@@ -229,6 +229,18 @@ struct WaveDesc {
   double amp, omega, tau, t0, z0;
 };
 
+// Field of the classical-path steps of one launch: a pulse, or rows of an array.
+struct PrescribedField {
+  int wave;
+  const double* Et;  // wave = 0: M x 3 per step, emitter-id order
+  size_t stride;     // doubles per step
+  WaveDesc w;        // wave = 1: the pulse, at t_start + (q0 + q) dt in step q
+  double t_start;
+  int64_t q0;
+  const double* pos;    // [3M]
+  const double* gamma;  // [M]
+};
+
 // Discrete field energy W^n, recorded every `every` steps (0: off).
 struct EnergyRec {
   int every;

@@ -1731,32 +1731,22 @@ mlk_status prescribed_steps(mlk_sim* s, int64_t nsteps, const double* Et, bool h
   const size_t per = 3 * (size_t)s->nem, nt = s->tls_gid.size();
   const TlsPtrs tls = tls_ptrs(s);
   const MlDev ml = ml_dev(s);
-  Series ser = series_of(s);
-  ser.pop_every = 0;  // no series: the step counter does not move
+  const Series ser = series_of(s);
   double* dE = host ? stage : nullptr;
   double* dO = host ? stage + (size_t)K * per : nullptr;
   if (!host) K = nsteps;
   for (int64_t c0 = 0; c0 < nsteps; c0 += K) {
     const int64_t kc = std::min(K, nsteps - c0);
-    const double* e = host ? dE : Et + (size_t)c0 * per;
     double* o = tls_out && nt ? (host ? dO : tls_out + (size_t)c0 * 3 * nt) : nullptr;
     if (host)
       HIPCHK(hipMemcpyAsync(dE, Et + (size_t)c0 * per, (size_t)kc * per * sizeof(double),
                             hipMemcpyHostToDevice, s->stream));
-    for (int64_t q = 0; q < kc; ++q) {
-      const double* eq = e + (size_t)q * per;
-      HIPCHK(tls_step(tls, s->g.dt, eq, s->d_mudot, s->d_popoff, ser, s->d_step, s->stream));
-      if (ml.count > 0)
-        HIPCHK(ml_step(ml, s->ml_range, s->g.dt, eq, s->d_mudot, s->d_popoff, ser, s->d_step,
-                       s->stream));
-      if (o)
-        HIPCHK(hipMemcpyAsync(o + (size_t)q * 3 * nt, s->d_tls_rho, 3 * nt * sizeof(double),
-                              hipMemcpyDeviceToDevice, s->stream));
-    }
-    // E~ of the last step, as mlk_get_emitter_io reports it
-    if (c0 + kc == nsteps)
-      HIPCHK(hipMemcpyAsync(s->d_Et, e + (size_t)(kc - 1) * per, per * sizeof(double),
-                            hipMemcpyDeviceToDevice, s->stream));
+    PrescribedField f{};
+    f.Et = host ? dE : Et + (size_t)c0 * per;
+    f.stride = per;
+    // the last step's E~ and mu_dot are left where mlk_get_emitter_io reads them
+    HIPCHK(mlk::prescribed_steps(tls, ml, s->ml_range, s->g.dt, f, kc, s->d_Et, s->d_mudot, o, ser,
+                                 s->d_step, s->stream));
     if (host && o)
       HIPCHK(hipMemcpyAsync(tls_out + (size_t)c0 * 3 * nt, dO, (size_t)kc * 3 * nt * sizeof(double),
                             hipMemcpyDeviceToHost, s->stream));
@@ -1799,15 +1789,18 @@ mlk_status mlk_step_prescribed_wave(mlk_sim* s, int64_t nsteps, const double pol
   const size_t nt = s->tls_gid.size();
   const TlsPtrs tls = tls_ptrs(s);
   const MlDev ml = ml_dev(s);
-  Series ser = series_of(s);
-  ser.pop_every = 0;  // no series: the step counter does not move
-  WaveDesc w{};
-  for (int c = 0; c < 3; ++c) w.pol[c] = pol[c];
-  w.amp = amp;
-  w.omega = omega;
-  w.tau = tau;
-  w.t0 = t0;
-  w.z0 = z0;
+  const Series ser = series_of(s);
+  PrescribedField f{};
+  f.wave = 1;
+  for (int c = 0; c < 3; ++c) f.w.pol[c] = pol[c];
+  f.w.amp = amp;
+  f.w.omega = omega;
+  f.w.tau = tau;
+  f.w.t0 = t0;
+  f.w.z0 = z0;
+  f.t_start = t_start;
+  f.pos = s->d_pos;
+  f.gamma = s->d_gamma;
   // recorded states go through device staging of at most about 64 MB at a time
   const int64_t K = tls_out && nt ? std::max<int64_t>(1, std::min<int64_t>(
                                         nsteps, (int64_t)((64u << 20) / (24 * nt))))
@@ -1816,17 +1809,9 @@ mlk_status mlk_step_prescribed_wave(mlk_sim* s, int64_t nsteps, const double pol
   if (tls_out && nt) HIPCHK(stage.alloc((size_t)K * 3 * nt));
   for (int64_t c0 = 0; c0 < nsteps; c0 += K) {
     const int64_t kc = std::min(K, nsteps - c0);
-    for (int64_t q = 0; q < kc; ++q) {
-      const double t = t_start + (double)(c0 + q) * s->g.dt;
-      HIPCHK(wave_field(s->nem, s->d_pos, s->d_gamma, w, t, s->d_Et, s->stream));
-      HIPCHK(tls_step(tls, s->g.dt, s->d_Et, s->d_mudot, s->d_popoff, ser, s->d_step, s->stream));
-      if (ml.count > 0)
-        HIPCHK(ml_step(ml, s->ml_range, s->g.dt, s->d_Et, s->d_mudot, s->d_popoff, ser,
-                       s->d_step, s->stream));
-      if (stage.p)
-        HIPCHK(hipMemcpyAsync(stage.p + (size_t)q * 3 * nt, s->d_tls_rho, 3 * nt * sizeof(double),
-                              hipMemcpyDeviceToDevice, s->stream));
-    }
+    f.q0 = c0;
+    HIPCHK(mlk::prescribed_steps(tls, ml, s->ml_range, s->g.dt, f, kc, s->d_Et, s->d_mudot,
+                                 stage.p, ser, s->d_step, s->stream));
     if (stage.p) {
       HIPCHK(hipMemcpyAsync(tls_out + (size_t)c0 * 3 * nt, stage.p,
                             (size_t)kc * 3 * nt * sizeof(double), hipMemcpyDeviceToHost,
