@@ -20,10 +20,6 @@ hipError_t sweep_shell_f64(const FieldPtrs<double>& in, const FieldPtrs<double>&
                            const Geom& g, const Box& inner, bool h_pass, hipStream_t st);
 hipError_t sweep_shell_f32(const FieldPtrs<float>& in, const FieldPtrs<float>& out, const Geom& g,
                            const Box& inner, bool h_pass, hipStream_t st);
-// Two-level step of every two-level emitter under E~ (M x 3, emitter-id order).
-hipError_t tls_step(const TlsPtrs& tls, double dt, const double* Et, double* mudot,
-                    const int64_t* pop_off, const Series& ser, const int64_t* step,
-                    hipStream_t st);
 // Multilevel step of every slot; range[n]..range[n+1] are the slots with n levels.
 hipError_t ml_step(const MlDev& ml, const int* range, double dt, const double* Et, double* mudot,
                    const int64_t* pop_off, const Series& ser, const int64_t* step,
@@ -187,26 +183,18 @@ hipError_t pole_post_f64(const PoleDev& p, const FieldPtrs<double>& f, const Geo
                          const double* epsinv, hipStream_t st);
 hipError_t pole_post_f32(const PoleDev& p, const FieldPtrs<float>& f, const Geom& g,
                          const float* epsinv, hipStream_t st);
-// Single-mode cavity: E~ of every emitter from the mode state, then the
-// sum of mu_dot over the emitters, the (p, q, d) update and the step counter.
-int cavity_blocks(int M);
-hipError_t cavity_field(const CavityDev& c, double* Et, int M, hipStream_t st);
-// Partial sums of <mu> + (dt/2) mu_dot over the states, then the (p, q) leapfrog
-// with the old d, the new d and the step counter.
-hipError_t cavity_update(const CavityDev& c, const TlsPtrs& tls, const MlDev& ml, double dt,
-                         int64_t* step, hipStream_t st);
-// The same sums, stored as d without advancing the mode (set-up, new dipoles).
+// Single-mode cavity: nsteps steps from step number n0 (E~ and mu_dot of the last one
+// are kept), leaving the mode and the step counter at their end.
+hipError_t cavity_steps(const CavityDev& c, const TlsPtrs& tls, const MlDev& ml, const int* range,
+                        double dt, int64_t n0, int64_t nsteps, double* Et, double* mudot,
+                        const int64_t* pop_off, const Series& ser, int64_t* step, hipStream_t st);
+// Partial sums that a step (or cavity_set_dipole) leaves: the size of each of the two
+// sets of CavityDev::partial.
+int cavity_partials(int ntls, const int* ml_range);
+// The total dipole of the states stored as d without advancing the mode (set-up, new
+// dipoles).
 hipError_t cavity_set_dipole(const CavityDev& c, const TlsPtrs& tls, const MlDev& ml, double dt,
                              hipStream_t st);
-// The (p, q, d) update from npartial per-block partial sums already in c.partial.
-hipError_t cavity_advance(const CavityDev& c, int npartial, double dt, int64_t* step,
-                          hipStream_t st);
-// Two-level emitters only: E~ from the mode, the two-level step, and the partial sums
-// of <mu> + (dt/2) mu_dot (x, y) of each block of kTlsThreads slots of the new states
-// into c.partial.
-hipError_t cavity_tls_step(const TlsPtrs& tls, double dt, const CavityDev& c, double* Et,
-                           double* mudot, const int64_t* pop_off, const Series& ser,
-                           const int64_t* step, hipStream_t st);
 hipError_t eps_box_f64(const double* eps, const Geom& g, const Box& box, double* epsinv,
                        hipStream_t st);
 hipError_t eps_box_f32(const double* eps, const Geom& g, const Box& box, float* epsinv,

@@ -4,7 +4,7 @@
 // template parameter and every loop is unrolled.
 #pragma once
 
-#include "mlk_internal.h"
+#include "tls_math.h"
 
 namespace mlk {
 
@@ -12,16 +12,6 @@ namespace mlk {
 template <int N>
 __host__ __device__ constexpr int up(int a, int b) {
   return a <= b ? a * N - a * (a - 1) / 2 + (b - a) : b * N - b * (b - 1) / 2 + (a - b);
-}
-
-// 1 / sqrt(x) for a normal positive x: the hardware's estimate and one third-order
-// correction, y (1 + e/2 + 3 e^2/8) with e = 1 - x y^2 (the binomial series of
-// (1 - e)^{-1/2}; the estimate's e is below 2^-20, so the dropped e^3 term is below
-// FP64 rounding).  About a fifth of the instructions of 1.0 / sqrt(x).
-__device__ __forceinline__ double rsqrt_refined(double x) {
-  const double y = __builtin_amdgcn_rsq(x);
-  const double e = __builtin_fma(-x * y, y, 1.0);
-  return __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
 }
 
 // Cyclic Jacobi on the packed symmetric A: A becomes diagonal, Q holds the

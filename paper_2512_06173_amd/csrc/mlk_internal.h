@@ -261,12 +261,11 @@ struct PoleDev {
 // Single-mode cavity that replaces the grid: mode state and coupling.
 struct CavityDev {
   double* st;       // q_x, q_y, p_x, p_y, d_x, d_y (FP64)
-  double* partial;  // per-block partial sums of mu_dot_x, mu_dot_y
+  double* scratch;  // two more mode states (12 doubles) for the steps of one call
+  double* partial;  // two sets of npart per-block partial sums of <mu> + (dt/2) mu_dot, x and y
+  int npart;
   double w, V, eps; // mode frequency, effective volume, eps = w / sqrt(V)
 };
-// Two-level-only cavity step: one block of kTlsThreads slots per partial sum.
-constexpr int kTlsThreads = 256;
-inline int cavity_tls_blocks(int ntls) { return (ntls + kTlsThreads - 1) / kTlsThreads; }
 
 // Cell (index along axis a; iu, iv along the two others in cyclic order) of a plane.
 __device__ __forceinline__ size_t plane_cell(const Geom& g, int a, int index, int iu, int iv) {

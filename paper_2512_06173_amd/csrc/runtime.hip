@@ -1040,31 +1040,15 @@ mlk_status enqueue_steps(mlk_sim* s, int64_t nsteps) {
   return MLK_OK;
 }
 
-// Cavity steps: E~ from the mode, the emitter steps, then the mode update
-// (which also moves the step counter on).  The grid is left alone.
+// Cavity steps: the emitters and the mode (the grid is left alone).
 mlk_status enqueue_cavity_steps(mlk_sim* s, int64_t nsteps) {
-  const Series ser = series_of(s);
-  const TlsPtrs tls = tls_ptrs(s);
-  const MlDev ml = ml_dev(s);
-  const int ntls = (int)s->tls_gid.size();
-  for (int64_t q = 0; q < nsteps; ++q) {
+  // one call for all steps; with phase timing, one per step (the split changes no result)
+  const int64_t per = s->timing & (1 << MLK_PHASE_EMITTERS) ? 1 : nsteps;
+  for (int64_t q = 0; q < nsteps; q += per) {
     const int t0 = mark_begin(s, MLK_PHASE_EMITTERS);
-    if (ml.count == 0 && ntls > 0) {
-      // two-level emitters only: field, step and partial sums in one launch
-      HIPCHK(cavity_tls_step(tls, s->g.dt, s->cav, s->d_Et, s->d_mudot, s->d_popoff, ser,
-                             s->d_step, s->stream));
-      HIPCHK(cavity_advance(s->cav, cavity_tls_blocks(ntls), s->g.dt, s->d_step, s->stream));
-      mark_end(s, MLK_PHASE_EMITTERS, t0);
-      continue;
-    }
-    if (s->nem > 0) {
-      HIPCHK(cavity_field(s->cav, s->d_Et, s->nem, s->stream));
-      HIPCHK(tls_step(tls, s->g.dt, s->d_Et, s->d_mudot, s->d_popoff, ser, s->d_step, s->stream));
-      if (ml.count > 0)
-        HIPCHK(ml_step(ml, s->ml_range, s->g.dt, s->d_Et, s->d_mudot, s->d_popoff, ser,
-                       s->d_step, s->stream));
-    }
-    HIPCHK(cavity_update(s->cav, tls, ml, s->g.dt, s->d_step, s->stream));
+    HIPCHK(cavity_steps(s->cav, tls_ptrs(s), ml_dev(s), s->ml_range, s->g.dt, s->host_step + q,
+                        per, s->d_Et, s->d_mudot, s->d_popoff, series_of(s), s->d_step,
+                        s->stream));
     mark_end(s, MLK_PHASE_EMITTERS, t0);
   }
   return MLK_OK;
@@ -1143,6 +1127,7 @@ void release(mlk_sim* s) {
   dfree(s->er.partial);
   dfree(s->er.series);
   dfree(s->cav.st);
+  dfree(s->cav.scratch);
   dfree(s->cav.partial);
   for (int k = 0; k < s->npole; ++k) {
     dfree(s->pole[k].P);
@@ -1906,14 +1891,12 @@ mlk_status mlk_set_cavity(mlk_sim* s, double omega, double volume, const double 
                 "the cavity replaces the grid: no sources, probes, flux plane or poles");
   HIPCHK(hipSetDevice(s->desc.device));
   STCHK(sync_sim(s));
-  const size_t nt = s->tls_gid.size();
   double st[6] = {q0[0], q0[1], p0[0], p0[1], 0.0, 0.0};
   if (!s->cav.st) HIPCHK(dalloc(&s->cav.st, 6 * sizeof(double)));
-  // partial sums: at most 256 blocks in the general path, one per 256 two-level
-  // emitters in the two-level path
-  const size_t npart = std::max<size_t>(256, (nt + 255) / 256);
+  if (!s->cav.scratch) HIPCHK(dalloc(&s->cav.scratch, 12 * sizeof(double)));
+  s->cav.npart = cavity_partials((int)s->tls_gid.size(), s->ml_range);
   dfree(s->cav.partial);
-  HIPCHK(dalloc(&s->cav.partial, 2 * npart * sizeof(double)));
+  HIPCHK(dalloc(&s->cav.partial, 4 * (size_t)s->cav.npart * sizeof(double)));
   HIPCHK(hipMemcpy(s->cav.st, st, sizeof(st), hipMemcpyHostToDevice));
   s->cav.w = omega;
   s->cav.V = volume;

@@ -89,3 +89,36 @@ def test_steps_across_the_launch_bound(steps):
     assert all(np.array_equal(sims[0].rho(q), sims[1].rho(q)) for q in range(72))
     for x, y in zip(sims[0].emitter_io(), sims[1].emitter_io()):
         assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("n_tls,n_ml", [(0, 0), (1, 0), (256, 0), (257, 3), (0, 65),
+                                        (262144 + 300, 2), (3, 64 * 1024 + 70)])
+def test_cavity_steps_do_not_depend_on_how_they_are_called(n_tls, n_ml):
+    """Seven cavity steps in one call, in calls of one and with every step timed: mode,
+    states, E~, mu_dot and populations bit for bit (block remainders, two-level ensembles
+    walked with a stride, more partials than the blocks add up for themselves)."""
+    rng = np.random.default_rng(5)
+    t = W.tls_ensemble(rng, n_tls, 0.0, 16.0, "superposition") if n_tls else None
+    m = ensemble({2: n_ml - n_ml // 3, 3: n_ml // 3}, 2) if n_ml else None
+    out = []
+    for mode in range(3):
+        s = mlk().Simulation((16, 16, 16), bc=("periodic",) * 6)
+        if t is not None:
+            s.add_tls(t.pos, t.sigma, t.gamma, t.omega0, t.dipole, t.rho0)
+        if m is not None:
+            s.add_multilevel(**m)
+        s.set_cavity(0.25, 1e4, (0.3, -0.1), (0.0, 0.02))
+        s.record_populations(2)
+        if mode == 2:
+            s.set_timing(True)
+        for k in [7] if mode != 1 else [1] * 7:
+            s.step(k)
+        s.sync()
+        assert s.step_count == 7
+        if mode == 2:
+            assert s.phase_time("emitters")[1] == 7
+        out.append([s.cavity(), s.populations(), *s.emitter_io(), s.checkpoint_save()])
+        s.close()
+    for o in out[1:]:
+        assert all(np.array_equal(x, y) for x, y in zip(out[0], o))
+    assert np.any(out[0][0][:2] != (0.3, -0.1))
