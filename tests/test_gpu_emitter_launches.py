@@ -91,8 +91,8 @@ def test_steps_across_the_launch_bound(steps):
         assert np.array_equal(x, y)
 
 
-@pytest.mark.parametrize("n_tls,n_ml", [(0, 0), (1, 0), (256, 0), (257, 3), (0, 65),
-                                        (262144 + 300, 2), (3, 64 * 1024 + 70)])
+@pytest.mark.parametrize("n_tls,n_ml", [(0, 0), (1, 0), (512, 0), (513, 3), (0, 65),
+                                        (524288 + 300, 2), (3, 64 * 1024 + 70)])
 def test_cavity_steps_do_not_depend_on_how_they_are_called(n_tls, n_ml):
     """Seven cavity steps in one call, in calls of one and with every step timed: mode,
     states, E~, mu_dot and populations bit for bit (block remainders, two-level ensembles
