@@ -7,7 +7,7 @@
 // values of E^n are saved before the sweep overwrites them.  The sum is done
 // in FP64 in a fixed order (block partials, then one block), so it is
 // deterministic.
-#include "mlk_internal.h"
+#include "step_side.h"
 
 namespace mlk {
 
@@ -17,41 +17,6 @@ __device__ __forceinline__ void flux_partial_body(const FieldPtrs<T>& f, const G
                                                   const FluxPlane& fp, int b, int nb) {
   __shared__ double red[256];
   flux_partial_sum(f, g, fp, b, nb, red);
-}
-
-// Single block: probe samples, the flux total, then the step counter moves on.
-template <typename T>
-__device__ __forceinline__ void finish_body(const FieldPtrs<T>& f, const Geom& g,
-                                            const FluxPlane& fp, const Series& ser,
-                                            int64_t* step) {
-  __shared__ double red[256];
-  const int64_t n = *step;
-  const int t = threadIdx.x;
-  if (t < ser.nprobe) {
-    const int comp = ser.probe_comp[t];
-    const T* a = comp < 3 ? f.E[comp] : f.H[comp - 3];
-    const double v = (double)a[ser.probe_idx[t]];
-    ser.probe[(size_t)t * ser.cap + n] = v;
-    if (!isfinite(v)) flag_nonfinite(ser, n);
-  }
-  if (fp.on) {
-    double s = 0.0;
-    for (int q = t; q < fp.nblocks; q += blockDim.x) s += fp.partial[q];
-    red[t] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-      if (t < w) red[t] += red[t + w];
-      __syncthreads();
-    }
-    if (t == 0) {
-      const double F = red[0] * g.dx * g.dx;
-      fp.series[n] = F;
-      *fp.total += g.dt * F;
-      if (!isfinite(F)) flag_nonfinite(ser, n);
-    }
-  }
-  __syncthreads();
-  if (t == 0) *step = n + 1;
 }
 
 template <typename T>
@@ -65,7 +30,7 @@ __global__ __launch_bounds__(256) void k_flux_partial(FieldPtrs<T> f, Geom g, Fl
 template <typename T>
 __global__ __launch_bounds__(256) void k_finish(FieldPtrs<T> f, Geom g, FluxPlane fp, Series ser,
                                                 int64_t* step) {
-  finish_body(f, g, fp, ser, step);
+  finish_body(f, g, fp, ser, *step, step, 256);
 }
 
 // Batched forms: kind 0 flux save, 1 flux partials, 2 finish (one block per job).
@@ -78,7 +43,7 @@ __global__ __launch_bounds__(256) void k_detect_batch(const FluxJob<T>* jobs, co
   if (lb >= J.nblocks) return;
   if (KIND == 0) flux_save_body(J.f, J.g, J.fp, lb * blockDim.x + threadIdx.x);
   else if (KIND == 1) flux_partial_body(J.f, J.g, J.fp, lb, J.nblocks);
-  else finish_body(J.f, J.g, J.fp, J.ser, J.step);
+  else finish_body(J.f, J.g, J.fp, J.ser, *J.step, J.step, 256);
 }
 
 // Discrete field energy (Poynting's theorem on the Yee grid; invariant without
@@ -158,12 +123,18 @@ static hipError_t launch_flux_save(const FieldPtrs<T>& f, const Geom& g, const F
 }
 
 template <typename T>
+static hipError_t launch_partial(const FieldPtrs<T>& f, const Geom& g, const FluxPlane& fp,
+                                 hipStream_t st) {
+  hipLaunchKernelGGL(k_flux_partial<T>, dim3(fp.nblocks), dim3(256), 0, st, f, g, fp);
+  return hipGetLastError();
+}
+
+template <typename T>
 static hipError_t launch_finish(const FieldPtrs<T>& f, const Geom& g, const FluxPlane& fp,
                                 const Series& ser, int64_t* step, bool partials_done,
                                 hipStream_t st) {
   if (fp.on && !partials_done) {
-    hipLaunchKernelGGL(k_flux_partial<T>, dim3(fp.nblocks), dim3(256), 0, st, f, g, fp);
-    hipError_t e = hipGetLastError();
+    const hipError_t e = launch_partial<T>(f, g, fp, st);
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(k_finish<T>, dim3(1), dim3(256), 0, st, f, g, fp, ser, step);
@@ -177,6 +148,14 @@ hipError_t flux_save_f64(const FieldPtrs<double>& f, const Geom& g, const FluxPl
 hipError_t flux_save_f32(const FieldPtrs<float>& f, const Geom& g, const FluxPlane& fp,
                          hipStream_t st) {
   return launch_flux_save<float>(f, g, fp, st);
+}
+hipError_t flux_partial_f64(const FieldPtrs<double>& f, const Geom& g, const FluxPlane& fp,
+                            hipStream_t st) {
+  return launch_partial<double>(f, g, fp, st);
+}
+hipError_t flux_partial_f32(const FieldPtrs<float>& f, const Geom& g, const FluxPlane& fp,
+                            hipStream_t st) {
+  return launch_partial<float>(f, g, fp, st);
 }
 hipError_t finish_f64(const FieldPtrs<double>& f, const Geom& g, const FluxPlane& fp,
                       const Series& ser, int64_t* step, bool partials_done, hipStream_t st) {

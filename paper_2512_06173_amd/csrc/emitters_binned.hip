@@ -26,7 +26,7 @@
 // per emitter as a union-window record (WinRec); a component uses the
 // half-integer variant on its own axis.
 #include "mlk_internal.h"
-#include "tls_math.h"
+#include "step_side.h"
 
 namespace mlk {
 
@@ -478,34 +478,10 @@ __global__ __launch_bounds__(GatherCfg<T>::threads, GatherCfg<T>::waves_per_simd
   gather_body(J.f, J.g, J.bins, J.win, J.Et, bid);
 }
 
-// Exact two-level step of every two-level emitter under its E~ (one thread each).
-__device__ __forceinline__ void tls_body(const TlsPtrs& tls, double dt, const double* Et,
-                                         double* mudot, const int64_t* pop_off, const Series& ser,
-                                         const int64_t* step, int m) {
-  if (m >= tls.count) return;
-  const int e = tls.gid[m];
-  const double et[3] = {Et[3 * e], Et[3 * e + 1], Et[3 * e + 2]};
-  const double d[3] = {tls.dip[3 * m], tls.dip[3 * m + 1], tls.dip[3 * m + 2]};
-  double st[3] = {tls.rho[3 * m], tls.rho[3 * m + 1], tls.rho[3 * m + 2]};
-  double md[3];
-  tls_advance(tls.omega0[m], d, et, dt, st, md);
-  if (!isfinite(st[0] + st[1] + st[2] + md[0] + md[1] + md[2])) flag_nonfinite(ser, *step);
-  tls.rho[3 * m] = st[0];
-  tls.rho[3 * m + 1] = st[1];
-  tls.rho[3 * m + 2] = st[2];
-  mudot[3 * e] = md[0];
-  mudot[3 * e + 1] = md[1];
-  mudot[3 * e + 2] = md[2];
-  if (ser.pop_every > 0) {
-    const int64_t n = *step;
-    if (n % ser.pop_every == 0) ser.pop[(n / ser.pop_every) * ser.npop + pop_off[e]] = st[0];
-  }
-}
-
 __global__ __launch_bounds__(256) void k_tls_step(TlsPtrs tls, double dt, const double* Et,
                                                   double* mudot, const int64_t* pop_off,
-                                                  Series ser, const int64_t* step) {
-  tls_body(tls, dt, Et, mudot, pop_off, ser, step, blockIdx.x * blockDim.x + threadIdx.x);
+                                                  Series ser, int64_t n) {
+  tls_body(tls, dt, Et, mudot, pop_off, ser, n, blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 __global__ __launch_bounds__(256) void k_tls_batch(const TlsJob* jobs, const int* start,
@@ -514,7 +490,8 @@ __global__ __launch_bounds__(256) void k_tls_batch(const TlsJob* jobs, const int
   const TlsJob J = load_job(jobs, j);
   const int lb = blockIdx.x - start[j];
   if (lb >= J.nblocks) return;
-  tls_body(J.tls, J.dt, J.Et, J.mudot, J.pop_off, J.ser, J.step, lb * blockDim.x + threadIdx.x);
+  tls_body(J.tls, J.dt, J.Et, J.mudot, J.pop_off, J.ser, *J.step,
+           lb * blockDim.x + threadIdx.x);
 }
 
 // Fixed-point accumulator of the scatter: 32-bit for FP32 fields, 64-bit for FP64.
@@ -795,11 +772,9 @@ __global__ __launch_bounds__(kThreads, 4) void k_scatter_batch(const ScatterJob<
 }
 
 template <typename T>
-static hipError_t launch_gather_step(const FieldPtrs<T>& f, const Geom& g, const BinPtrs& b,
-                                     const WindowPtrs<T>& win, const TlsPtrs& tls,
-                                     double* Et, double* mudot, const int64_t* pop_off,
-                                     const Series& ser, const int64_t* step,
-                                     const FluxPlane* fp, hipStream_t st) {
+static hipError_t launch_gather(const FieldPtrs<T>& f, const Geom& g, const BinPtrs& b,
+                                const WindowPtrs<T>& win, double* Et, const FluxPlane* fp,
+                                hipStream_t st) {
   if (b.ngather <= 0) return fp ? hipErrorInvalidValue : hipSuccess;
   int nflux = 0;
   FluxPlane fpv{};
@@ -818,9 +793,14 @@ static hipError_t launch_gather_step(const FieldPtrs<T>& f, const Geom& g, const
                        0, st, f, g, b.gbin_em + b.glight0, b.nlight, win, Et);
     e = hipGetLastError();
   }
-  if (e != hipSuccess || tls.count == 0) return e;
-  hipLaunchKernelGGL(k_tls_step, dim3((tls.count + 255) / 256), dim3(256), 0, st, tls, g.dt, Et,
-                     mudot, pop_off, ser, step);
+  return e;
+}
+
+hipError_t tls_step(const TlsPtrs& tls, double dt, const double* Et, double* mudot,
+                    const int64_t* pop_off, const Series& ser, int64_t n, hipStream_t st) {
+  if (tls.count == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_tls_step, dim3((tls.count + 255) / 256), dim3(256), 0, st, tls, dt, Et,
+                     mudot, pop_off, ser, n);
   return hipGetLastError();
 }
 
@@ -838,17 +818,15 @@ static hipError_t launch_scatter(const FieldPtrs<T>& f, const Geom& g, const Bin
   return hipGetLastError();
 }
 
-hipError_t bin_gather_step_f64(const FieldPtrs<double>& f, const Geom& g, const BinPtrs& b,
-                               const WindowPtrs<double>& win, const TlsPtrs& tls, double* Et,
-                               double* mudot, const int64_t* pop_off, const Series& ser,
-                               const int64_t* step, const FluxPlane* fp, hipStream_t st) {
-  return launch_gather_step<double>(f, g, b, win, tls, Et, mudot, pop_off, ser, step, fp, st);
+hipError_t bin_gather_f64(const FieldPtrs<double>& f, const Geom& g, const BinPtrs& b,
+                          const WindowPtrs<double>& win, double* Et, const FluxPlane* fp,
+                          hipStream_t st) {
+  return launch_gather<double>(f, g, b, win, Et, fp, st);
 }
-hipError_t bin_gather_step_f32(const FieldPtrs<float>& f, const Geom& g, const BinPtrs& b,
-                               const WindowPtrs<float>& win, const TlsPtrs& tls, double* Et,
-                               double* mudot, const int64_t* pop_off, const Series& ser,
-                               const int64_t* step, const FluxPlane* fp, hipStream_t st) {
-  return launch_gather_step<float>(f, g, b, win, tls, Et, mudot, pop_off, ser, step, fp, st);
+hipError_t bin_gather_f32(const FieldPtrs<float>& f, const Geom& g, const BinPtrs& b,
+                          const WindowPtrs<float>& win, double* Et, const FluxPlane* fp,
+                          hipStream_t st) {
+  return launch_gather<float>(f, g, b, win, Et, fp, st);
 }
 hipError_t bin_scatter_f64(const FieldPtrs<double>& f, const Geom& g, const BinPtrs& b,
                            const WindowPtrs<double>& win, const double* mudot,

@@ -2,6 +2,7 @@
 #pragma once
 
 #include "mlk_internal.h"
+#include "step_side.h"
 
 namespace mlk {
 
@@ -22,8 +23,7 @@ hipError_t sweep_shell_f32(const FieldPtrs<float>& in, const FieldPtrs<float>& o
                            const Box& inner, bool h_pass, hipStream_t st);
 // Multilevel step of every slot; range[n]..range[n+1] are the slots with n levels.
 hipError_t ml_step(const MlDev& ml, const int* range, double dt, const double* Et, double* mudot,
-                   const int64_t* pop_off, const Series& ser, const int64_t* step,
-                   hipStream_t st);
+                   const int64_t* pop_off, const Series& ser, int64_t n, hipStream_t st);
 // nsteps classical-path steps of every emitter under f; the states after every step go
 // to out (nsteps x two-level emitters x 3, null: not recorded), the last step's E~ and
 // mu_dot to last and mudot (emitter-id order).
@@ -41,9 +41,11 @@ hipError_t sweep_frame_f64(const FieldPtrs<double>& a, const FieldPtrs<double>& 
 hipError_t sweep_frame_f32(const FieldPtrs<float>& a, const FieldPtrs<float>& b, const Geom& g,
                            const Box& inner, int kz, hipStream_t st);
 hipError_t sweep_fused_f64(const FieldPtrs<double>& a, const FieldPtrs<double>& b, const Geom& g,
-                           const Box& box, int kz, int tx, int ty, hipStream_t st);
+                           const Box& box, int kz, int tx, int ty, const SideWork& side,
+                           hipStream_t st);
 hipError_t sweep_fused_f32(const FieldPtrs<float>& a, const FieldPtrs<float>& b, const Geom& g,
-                           const Box& box, int kz, int tx, int ty, hipStream_t st);
+                           const Box& box, int kz, int tx, int ty, const SideWork& side,
+                           hipStream_t st);
 
 hipError_t windows_f64(int count, const double* pos, const double* sigma, double R, const Geom& g,
                        int* lo, int* len, double* w, hipStream_t st);
@@ -72,20 +74,25 @@ hipError_t energy_f32(const FieldPtrs<float>& old, const FieldPtrs<float>& cur, 
                       const EnergyRec& er, const int64_t* step, hipStream_t st);
 // partials_done: the flux partials of this step are formed already (by the scatter
 // launch), so only the finishing block runs
+hipError_t flux_partial_f64(const FieldPtrs<double>& f, const Geom& g, const FluxPlane& fp,
+                            hipStream_t st);
+hipError_t flux_partial_f32(const FieldPtrs<float>& f, const Geom& g, const FluxPlane& fp,
+                            hipStream_t st);
 hipError_t finish_f64(const FieldPtrs<double>& f, const Geom& g, const FluxPlane& fp,
                       const Series& ser, int64_t* step, bool partials_done, hipStream_t st);
 hipError_t finish_f32(const FieldPtrs<float>& f, const Geom& g, const FluxPlane& fp,
                       const Series& ser, int64_t* step, bool partials_done, hipStream_t st);
 
 // fp: when given, the same launch saves the flux plane's E^n (needs ngather > 0)
-hipError_t bin_gather_step_f64(const FieldPtrs<double>& f, const Geom& g, const BinPtrs& b,
-                               const WindowPtrs<double>& win, const TlsPtrs& tls, double* Et,
-                               double* mudot, const int64_t* pop_off, const Series& ser,
-                               const int64_t* step, const FluxPlane* fp, hipStream_t st);
-hipError_t bin_gather_step_f32(const FieldPtrs<float>& f, const Geom& g, const BinPtrs& b,
-                               const WindowPtrs<float>& win, const TlsPtrs& tls, double* Et,
-                               double* mudot, const int64_t* pop_off, const Series& ser,
-                               const int64_t* step, const FluxPlane* fp, hipStream_t st);
+hipError_t bin_gather_f64(const FieldPtrs<double>& f, const Geom& g, const BinPtrs& b,
+                          const WindowPtrs<double>& win, double* Et, const FluxPlane* fp,
+                          hipStream_t st);
+hipError_t bin_gather_f32(const FieldPtrs<float>& f, const Geom& g, const BinPtrs& b,
+                          const WindowPtrs<float>& win, double* Et, const FluxPlane* fp,
+                          hipStream_t st);
+// Two-level step n of every two-level emitter under E~ (emitter-id order).
+hipError_t tls_step(const TlsPtrs& tls, double dt, const double* Et, double* mudot,
+                    const int64_t* pop_off, const Series& ser, int64_t n, hipStream_t st);
 // fp: when given, fp->nblocks more workgroups of the same launch form the flux
 // partials of the plane (no window may reach the plane's E cells)
 hipError_t bin_scatter_f64(const FieldPtrs<double>& f, const Geom& g, const BinPtrs& b,

@@ -206,10 +206,17 @@ struct Series {
   unsigned long long* numeric;
 };
 
-// Record step n as the first non-finite one (the earliest record wins the race only
-// within a launch; launches run in step order, so the first launch to set it wins).
+// Record step n as the first non-finite one.  Steps n - 1 and n can be checked by the
+// same launch, so the earliest of the competing records is kept.
 __device__ __forceinline__ void flag_nonfinite(const Series& ser, int64_t n) {
-  if (ser.numeric) atomicCAS(ser.numeric, 0ull, (unsigned long long)n + 1ull);
+  if (!ser.numeric) return;
+  const unsigned long long v = (unsigned long long)n + 1ull;
+  unsigned long long old = 0ull;  // expected: nothing recorded yet
+  for (;;) {
+    const unsigned long long seen = atomicCAS(ser.numeric, old, v);
+    if (seen == old || (seen != 0ull && seen <= v)) return;
+    old = seen;  // a later step got in first: replace it
+  }
 }
 
 struct FluxPlane {

@@ -41,7 +41,7 @@ constexpr int kMlOneLaunchBlocks = 8192;
 template <int N>
 __device__ __forceinline__ void ml_body(const MlDev& ml, int first, int count, double dt,
                                         const double* Et, double* mudot, const int64_t* pop_off,
-                                        const Series& ser, const int64_t* step, int t) {
+                                        const Series& ser, int64_t n, int t) {
   const int m = first + t;
   if (t >= count) return;
   const int e = ml.gid[m];
@@ -51,7 +51,6 @@ __device__ __forceinline__ void ml_body(const MlDev& ml, int first, int count, d
   bool finite = true;
   const double tr = ml_advance<N>(s, et, dt, finite);
   ml_store<N>(ml, m, s);
-  const int64_t n = *step;
   if (ser.pop_every > 0 && n % ser.pop_every == 0) {
     double* pop = ser.pop + (n / ser.pop_every) * ser.npop + pop_off[e];
 #pragma unroll
@@ -65,19 +64,18 @@ __device__ __forceinline__ void ml_body(const MlDev& ml, int first, int count, d
 template <int N>
 __global__ __launch_bounds__(64) void k_ml_step(MlDev ml, int first, int count, double dt,
                                                 const double* Et, double* mudot,
-                                                const int64_t* pop_off, Series ser,
-                                                const int64_t* step) {
-  ml_body<N>(ml, first, count, dt, Et, mudot, pop_off, ser, step,
+                                                const int64_t* pop_off, Series ser, int64_t n) {
+  ml_body<N>(ml, first, count, dt, Et, mudot, pop_off, ser, n,
              blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 __global__ __launch_bounds__(64) void k_ml_levels(MlDev ml, MlLevels lv, double dt,
                                                   const double* Et, double* mudot,
                                                   const int64_t* pop_off, Series ser,
-                                                  const int64_t* step) {
+                                                  int64_t n) {
   const int b = blockIdx.x;
 #define MLK_LEVEL(N)                                                                  \
-  ml_body<N>(ml, lv.first[N], lv.count[N], dt, Et, mudot, pop_off, ser, step,         \
+  ml_body<N>(ml, lv.first[N], lv.count[N], dt, Et, mudot, pop_off, ser, n,            \
              (b - lv.start[N]) * 64 + (int)threadIdx.x)
   if (b < lv.start[5]) MLK_LEVEL(6);
   else if (b < lv.start[4]) MLK_LEVEL(5);
@@ -93,7 +91,7 @@ __global__ __launch_bounds__(64) void k_ml_batch(const MlJob* jobs, const int* s
   const MlJob J = load_job(jobs, j);
   const int lb = blockIdx.x - start[j];
   if (lb >= J.nblocks) return;
-  ml_body<N>(J.ml, J.first, J.count, J.dt, J.Et, J.mudot, J.pop_off, J.ser, J.step,
+  ml_body<N>(J.ml, J.first, J.count, J.dt, J.Et, J.mudot, J.pop_off, J.ser, *J.step,
              lb * blockDim.x + threadIdx.x);
 }
 
@@ -114,8 +112,7 @@ hipError_t ml_batch(const MlJob* jobs, const int* start, int njobs, int nblocks,
 }
 
 hipError_t ml_step(const MlDev& ml, const int* range, double dt, const double* Et, double* mudot,
-                   const int64_t* pop_off, const Series& ser, const int64_t* step,
-                   hipStream_t st) {
+                   const int64_t* pop_off, const Series& ser, int64_t n, hipStream_t st) {
   int total = 0;
   const MlLevels lv = ml_levels(range, &total);
   if (total == 0) return hipSuccess;
@@ -123,7 +120,7 @@ hipError_t ml_step(const MlDev& ml, const int* range, double dt, const double* E
   for (int nl = 2; nl <= kMaxLevels; ++nl) kinds += lv.count[nl] > 0;
   if (kinds > 1 && total <= kMlOneLaunchBlocks) {
     hipLaunchKernelGGL(k_ml_levels, dim3(total), dim3(64), 0, st, ml, lv, dt, Et, mudot, pop_off,
-                       ser, step);
+                       ser, n);
     return hipGetLastError();
   }
   for (int nl = 2; nl <= kMaxLevels; ++nl) {
@@ -131,11 +128,11 @@ hipError_t ml_step(const MlDev& ml, const int* range, double dt, const double* E
     if (count <= 0) continue;
     const dim3 grid((count + 63) / 64), block(64);
     switch (nl) {
-      case 2: hipLaunchKernelGGL(k_ml_step<2>, grid, block, 0, st, ml, first, count, dt, Et, mudot, pop_off, ser, step); break;
-      case 3: hipLaunchKernelGGL(k_ml_step<3>, grid, block, 0, st, ml, first, count, dt, Et, mudot, pop_off, ser, step); break;
-      case 4: hipLaunchKernelGGL(k_ml_step<4>, grid, block, 0, st, ml, first, count, dt, Et, mudot, pop_off, ser, step); break;
-      case 5: hipLaunchKernelGGL(k_ml_step<5>, grid, block, 0, st, ml, first, count, dt, Et, mudot, pop_off, ser, step); break;
-      case 6: hipLaunchKernelGGL(k_ml_step<6>, grid, block, 0, st, ml, first, count, dt, Et, mudot, pop_off, ser, step); break;
+      case 2: hipLaunchKernelGGL(k_ml_step<2>, grid, block, 0, st, ml, first, count, dt, Et, mudot, pop_off, ser, n); break;
+      case 3: hipLaunchKernelGGL(k_ml_step<3>, grid, block, 0, st, ml, first, count, dt, Et, mudot, pop_off, ser, n); break;
+      case 4: hipLaunchKernelGGL(k_ml_step<4>, grid, block, 0, st, ml, first, count, dt, Et, mudot, pop_off, ser, n); break;
+      case 5: hipLaunchKernelGGL(k_ml_step<5>, grid, block, 0, st, ml, first, count, dt, Et, mudot, pop_off, ser, n); break;
+      case 6: hipLaunchKernelGGL(k_ml_step<6>, grid, block, 0, st, ml, first, count, dt, Et, mudot, pop_off, ser, n); break;
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -882,13 +882,13 @@ hipError_t sweep_passes(const mlk_sim* s, const FieldPtrs<T>& a, const FieldPtrs
                         const FieldPtrs<T>& b, const Box& inner, int kz, int tx, int ty) {
   hipError_t e = hipSuccess;
   if constexpr (sizeof(T) == 4) {
-    e = sweep_fused_f32(ar, b, s->g, inner, kz, tx, ty, s->stream);
+    e = sweep_fused_f32(ar, b, s->g, inner, kz, tx, ty, SideWork{}, s->stream);
     if (e == hipSuccess && s->layer_mode == 2 && split_ok(s))
       return sweep_frame_f32(ar, b, s->g, inner, kFrameKz, s->stream);
     if (e == hipSuccess) e = sweep_shell_f32(a, b, s->g, inner, true, s->stream);
     if (e == hipSuccess) e = sweep_shell_f32(a, b, s->g, inner, false, s->stream);
   } else {
-    e = sweep_fused_f64(ar, b, s->g, inner, kz, tx, ty, s->stream);
+    e = sweep_fused_f64(ar, b, s->g, inner, kz, tx, ty, SideWork{}, s->stream);
     if (e == hipSuccess) e = sweep_shell_f64(a, b, s->g, inner, true, s->stream);
     if (e == hipSuccess) e = sweep_shell_f64(a, b, s->g, inner, false, s->stream);
   }
@@ -903,8 +903,9 @@ FieldPtrs<T> sweep_reads(const mlk_sim* s) {
   return f;
 }
 
+// side: work for extra workgroups of the fused launch
 template <typename T>
-mlk_status sweep(mlk_sim* s) {
+mlk_status sweep(mlk_sim* s, const SideWork& side) {
   constexpr bool f32 = sizeof(T) == 4;
   const FieldPtrs<T> f = field_ptrs<T>(s);
   if (s->desc.sweep == MLK_SWEEP_FUSED) {
@@ -913,15 +914,15 @@ mlk_status sweep(mlk_sim* s) {
     if (f32 && s->layer_mode == 2 && split_ok(s)) {
       // the lean interior, then the layer frame in one launch of the full kernel
       int t0 = mark_begin(s, MLK_PHASE_SWEEP);
-      if constexpr (f32) HIPCHK(sweep_fused_f32(fr, nf, s->g, inner, s->kz, s->tx, s->ty, s->stream));
+      if constexpr (f32) HIPCHK(sweep_fused_f32(fr, nf, s->g, inner, s->kz, s->tx, s->ty, side, s->stream));
       mark_end(s, MLK_PHASE_SWEEP, t0);
       t0 = mark_begin(s, MLK_PHASE_SHELL);
       if constexpr (f32) HIPCHK(sweep_frame_f32(fr, nf, s->g, inner, kFrameKz, s->stream));
       mark_end(s, MLK_PHASE_SHELL, t0);
     } else {
       int t0 = mark_begin(s, MLK_PHASE_SWEEP);
-      if constexpr (f32) HIPCHK(sweep_fused_f32(fr, nf, s->g, inner, s->kz, s->tx, s->ty, s->stream));
-      else HIPCHK(sweep_fused_f64(fr, nf, s->g, inner, s->kz, s->tx, s->ty, s->stream));
+      if constexpr (f32) HIPCHK(sweep_fused_f32(fr, nf, s->g, inner, s->kz, s->tx, s->ty, side, s->stream));
+      else HIPCHK(sweep_fused_f64(fr, nf, s->g, inner, s->kz, s->tx, s->ty, side, s->stream));
       mark_end(s, MLK_PHASE_SWEEP, t0);
       t0 = mark_begin(s, MLK_PHASE_SHELL);
       if constexpr (f32) {
@@ -973,7 +974,27 @@ mlk_status enqueue_steps(mlk_sim* s, int64_t nsteps) {
                          (int)s->wplane[s->fp.axis].size() == s->g.n[s->fp.axis] &&
                          !s->wplane[s->fp.axis][s->fp.index];
   const FluxPlane* fpart = fold_flux ? &s->fp : nullptr;
+  // The fused sweep's launch also takes the two-level steps (the scatter after it needs
+  // them, the sweep does not) and closes the step before; the last step of the call is
+  // closed by a launch of its own.  Kernels take the step number by value, as the
+  // device's counter is one step behind until the sweep.  With the emitter or detector
+  // phase timed, both get launches of their own, which the phase's events enclose.
+  const bool fold = s->desc.sweep == MLK_SWEEP_FUSED &&
+                    !(s->timing & (1 << MLK_PHASE_EMITTERS | 1 << MLK_PHASE_DETECTORS));
+  SideWork side{};
+  if (fold) {
+    side.tls = tls;
+    side.Et = s->d_Et;
+    side.mudot = s->d_mudot;
+    side.pop_off = s->d_popoff;
+    side.ser = ser;
+    side.fp = s->fp;
+    side.step = s->d_step;
+  }
   for (int64_t q = 0; q < nsteps; ++q) {
+    const int64_t n = s->host_step + q;
+    side.n = n;
+    side.finish = fold && q > 0;
     FieldPtrs<T> f = field_ptrs<T>(s);
     if (s->fp.on && !fold_save) {
       const int t0 = mark_begin(s, MLK_PHASE_DETECTORS);
@@ -983,16 +1004,15 @@ mlk_status enqueue_steps(mlk_sim* s, int64_t nsteps) {
     }
     int t0 = mark_begin(s, MLK_PHASE_EMITTERS);
     if (s->nem > 0) {
-      // gather of every emitter, then the two-level and the multilevel steps
-      if constexpr (f32)
-        HIPCHK(bin_gather_step_f32(f, s->g, bins, win, tls, s->d_Et, s->d_mudot, s->d_popoff,
-                                   ser, s->d_step, fsave, s->stream));
-      else
-        HIPCHK(bin_gather_step_f64(f, s->g, bins, win, tls, s->d_Et, s->d_mudot, s->d_popoff,
-                                   ser, s->d_step, fsave, s->stream));
+      // gather of every emitter, then the two-level (unless the sweep's launch takes
+      // them) and the multilevel steps
+      if constexpr (f32) HIPCHK(bin_gather_f32(f, s->g, bins, win, s->d_Et, fsave, s->stream));
+      else HIPCHK(bin_gather_f64(f, s->g, bins, win, s->d_Et, fsave, s->stream));
+      if (!fold)
+        HIPCHK(tls_step(tls, s->g.dt, s->d_Et, s->d_mudot, s->d_popoff, ser, n, s->stream));
       if (ml.count > 0)
-        HIPCHK(ml_step(ml, s->ml_range, s->g.dt, s->d_Et, s->d_mudot, s->d_popoff, ser,
-                       s->d_step, s->stream));
+        HIPCHK(ml_step(ml, s->ml_range, s->g.dt, s->d_Et, s->d_mudot, s->d_popoff, ser, n,
+                       s->stream));
     }
     mark_end(s, MLK_PHASE_EMITTERS, t0);
     t0 = s->npole ? mark_begin(s, MLK_PHASE_POLES) : -1;
@@ -1001,7 +1021,7 @@ mlk_status enqueue_steps(mlk_sim* s, int64_t nsteps) {
       else HIPCHK(pole_pre_f64(s->pole[k], f, s->g, s->stream));
     }
     mark_end(s, MLK_PHASE_POLES, t0);
-    STCHK(sweep<T>(s));
+    STCHK(sweep<T>(s, side));
     f = field_ptrs<T>(s);
     if (s->er.every > 0) {
       // W^n: E^n and H^{n-1/2} are in the spare buffers now, H^{n+1/2} in the current
@@ -1032,6 +1052,13 @@ mlk_status enqueue_steps(mlk_sim* s, int64_t nsteps) {
       else HIPCHK(pole_post_f64(s->pole[k], f, s->g, (const double*)s->epsinv, s->stream));
     }
     mark_end(s, MLK_PHASE_POLES, t0);
+    if (fold && q + 1 < nsteps) {
+      if (s->fp.on && !fold_flux) {
+        if constexpr (f32) HIPCHK(flux_partial_f32(f, s->g, s->fp, s->stream));
+        else HIPCHK(flux_partial_f64(f, s->g, s->fp, s->stream));
+      }
+      continue;
+    }
     t0 = mark_begin(s, MLK_PHASE_DETECTORS);
     if constexpr (f32) HIPCHK(finish_f32(f, s->g, s->fp, ser, s->d_step, fold_flux, s->stream));
     else HIPCHK(finish_f64(f, s->g, s->fp, ser, s->d_step, fold_flux, s->stream));

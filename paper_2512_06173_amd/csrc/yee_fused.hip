@@ -35,6 +35,7 @@
 // already advanced.  Block indices are remapped so that the tiles one XCD
 // runs are spatial neighbours and share its L2.
 #include "mlk_internal.h"
+#include "step_side.h"
 #include "yee_common.h"
 
 namespace mlk {
@@ -568,7 +569,11 @@ __device__ __forceinline__ void fused_body(const FieldPtrs<T>& a, const FieldPtr
 template <typename T, int TX, int TY>
 __global__ __launch_bounds__(TX * TY, 4) void k_fused(FieldPtrs<T> a, FieldPtrs<T> b, Geom g,
                                                    Box box, int kz, int ntx, int nty,
-                                                   int nblocks) {
+                                                   int nblocks, SideWork side) {
+  if ((int)blockIdx.x >= nblocks) {  // uniform across the workgroup
+    side_body<T, TX * TY>(side, a, g, (int)blockIdx.x - nblocks);
+    return;
+  }
   fused_body<T, TX, TY>(a, b, g, box, kz, ntx, nty, nblocks, blockIdx.x);
 }
 
@@ -577,7 +582,11 @@ __global__ __launch_bounds__(TX * TY, 4) void k_fused(FieldPtrs<T> a, FieldPtrs<
 template <typename T, int TX, int TY, int CPM, int W>
 __global__ __launch_bounds__(TX * TY, W) void k_fused_lean(FieldPtrs<T> a, FieldPtrs<T> b, Geom g,
                                                         Box box, int kz, int ntx, int nty,
-                                                        int nblocks) {
+                                                        int nblocks, SideWork side) {
+  if ((int)blockIdx.x >= nblocks) {  // uniform across the workgroup
+    side_body<T, TX * TY>(side, a, g, (int)blockIdx.x - nblocks);
+    return;
+  }
   fused_body<T, TX, TY, CPM>(a, b, g, box, kz, ntx, nty, nblocks, blockIdx.x);
 }
 
@@ -615,22 +624,27 @@ struct LeanWaves {
 // and z layers), 2 the full kernel
 template <typename T, int TX, int TY>
 static hipError_t launch_fused(const FieldPtrs<T>& a, const FieldPtrs<T>& b, const Geom& g,
-                               const Box& box, int kz, int cpm, hipStream_t st) {
+                               const Box& box, int kz, int cpm, SideWork side, hipStream_t st) {
   const int ex = box.hi[0] - box.lo[0], ey = box.hi[1] - box.lo[1], ez = box.hi[2] - box.lo[2];
-  if (ex <= 0 || ey <= 0 || ez <= 0) return hipSuccess;
-  const int ntx = (box.hi[0] - (box.lo[0] & ~31) + TX - 1) / TX, nty = (ey + TY - 1) / TY;
-  const int nch = (ez + kz - 1) / kz;
-  const int nblocks = ntx * nty * nch;
+  int ntx = 0, nty = 0, nblocks = 0;
+  if (ex > 0 && ey > 0 && ez > 0) {
+    ntx = (box.hi[0] - (box.lo[0] & ~31) + TX - 1) / TX;
+    nty = (ey + TY - 1) / TY;
+    nblocks = ntx * nty * ((ez + kz - 1) / kz);
+  }
+  side_blocks(side, TX * TY);
+  const dim3 grid(side.blocks + nblocks), block(TX * TY);
+  if (grid.x == 0) return hipSuccess;
   constexpr int W0 = LeanWaves<T, TX, TY, 0>::value, W1 = LeanWaves<T, TX, TY, 1>::value;
   if (cpm == 0)
-    hipLaunchKernelGGL((k_fused_lean<T, TX, TY, 0, W0>), dim3(nblocks), dim3(TX * TY), 0, st, a,
-                       b, g, box, kz, ntx, nty, nblocks);
+    hipLaunchKernelGGL((k_fused_lean<T, TX, TY, 0, W0>), grid, block, 0, st, a, b, g, box, kz, ntx,
+                       nty, nblocks, side);
   else if (cpm == 1)
-    hipLaunchKernelGGL((k_fused_lean<T, TX, TY, 1, W1>), dim3(nblocks), dim3(TX * TY), 0, st, a,
-                       b, g, box, kz, ntx, nty, nblocks);
+    hipLaunchKernelGGL((k_fused_lean<T, TX, TY, 1, W1>), grid, block, 0, st, a, b, g, box, kz, ntx,
+                       nty, nblocks, side);
   else
-    hipLaunchKernelGGL((k_fused<T, TX, TY>), dim3(nblocks), dim3(TX * TY), 0, st, a, b, g, box,
-                       kz, ntx, nty, nblocks);
+    hipLaunchKernelGGL((k_fused<T, TX, TY>), grid, block, 0, st, a, b, g, box, kz, ntx, nty,
+                       nblocks, side);
   return hipGetLastError();
 }
 
@@ -666,18 +680,20 @@ int fused_cpm(const Geom& g, const Box& box) {
 
 template <typename T, int TX>
 static hipError_t launch_fused_tx(const FieldPtrs<T>& a, const FieldPtrs<T>& b, const Geom& g,
-                                  const Box& box, int kz, int ty, int cpm, hipStream_t st) {
-  if (ty == 16) return launch_fused<T, TX, 16>(a, b, g, box, kz, cpm, st);
-  if (ty == 8) return launch_fused<T, TX, 8>(a, b, g, box, kz, cpm, st);
-  return launch_fused<T, TX, 4>(a, b, g, box, kz, cpm, st);
+                                  const Box& box, int kz, int ty, int cpm, const SideWork& side,
+                                  hipStream_t st) {
+  if (ty == 16) return launch_fused<T, TX, 16>(a, b, g, box, kz, cpm, side, st);
+  if (ty == 8) return launch_fused<T, TX, 8>(a, b, g, box, kz, cpm, side, st);
+  return launch_fused<T, TX, 4>(a, b, g, box, kz, cpm, side, st);
 }
 
 template <typename T>
 static hipError_t launch_fused_any(const FieldPtrs<T>& a, const FieldPtrs<T>& b, const Geom& g,
-                                   const Box& box, int kz, int tx, int ty, hipStream_t st) {
+                                   const Box& box, int kz, int tx, int ty, const SideWork& side,
+                                   hipStream_t st) {
   const int cpm = fused_cpm(g, box);
-  if (tx == 32) return launch_fused_tx<T, 32>(a, b, g, box, kz, ty, cpm, st);
-  return launch_fused_tx<T, 64>(a, b, g, box, kz, ty, cpm, st);
+  if (tx == 32) return launch_fused_tx<T, 32>(a, b, g, box, kz, ty, cpm, side, st);
+  return launch_fused_tx<T, 64>(a, b, g, box, kz, ty, cpm, side, st);
 }
 
 // The y/z layer frame around an interior box: up to four boxes (the z slabs over
@@ -753,12 +769,14 @@ static hipError_t launch_fused_batch(const FusedJob<T>* jobs, const int* start, 
 }
 
 hipError_t sweep_fused_f64(const FieldPtrs<double>& a, const FieldPtrs<double>& b, const Geom& g,
-                           const Box& box, int kz, int tx, int ty, hipStream_t st) {
-  return launch_fused_any<double>(a, b, g, box, kz, tx, ty, st);
+                           const Box& box, int kz, int tx, int ty, const SideWork& side,
+                           hipStream_t st) {
+  return launch_fused_any<double>(a, b, g, box, kz, tx, ty, side, st);
 }
 hipError_t sweep_fused_f32(const FieldPtrs<float>& a, const FieldPtrs<float>& b, const Geom& g,
-                           const Box& box, int kz, int tx, int ty, hipStream_t st) {
-  return launch_fused_any<float>(a, b, g, box, kz, tx, ty, st);
+                           const Box& box, int kz, int tx, int ty, const SideWork& side,
+                           hipStream_t st) {
+  return launch_fused_any<float>(a, b, g, box, kz, tx, ty, side, st);
 }
 hipError_t sweep_frame_f64(const FieldPtrs<double>& a, const FieldPtrs<double>& b, const Geom& g,
                            const Box& inner, int kz, hipStream_t st) {
