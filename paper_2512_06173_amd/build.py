@@ -10,7 +10,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmlk.so")
 SOURCES = ["runtime.hip", "setup.hip", "yee_plain.hip", "yee_fused.hip", "emitters.hip",
-           "emitters_binned.hip", "multilevel.hip", "prescribed.hip", "detectors.hip",
+           "gather.hip", "emitters_binned.hip", "multilevel.hip", "prescribed.hip", "detectors.hip",
            "adjoint.hip", "adjoint_fused.hip", "cavity.hip",
            "dispersive.hip", "calib.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

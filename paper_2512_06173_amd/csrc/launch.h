@@ -103,8 +103,14 @@ hipError_t bin_scatter_f32(const FieldPtrs<float>& f, const Geom& g, const BinPt
                            const FluxPlane* fp, hipStream_t st);
 // bin edge lengths (cells) of the gather (G) and scatter (S) bins for a field precision
 void bin_shape(bool fp32, int G[3], int S[3]);
-// Gather bins of at most this many emitters are light (stage only their windows).
+void gather_bin_shape(bool fp32, int G[3]);
+// Gather bins of at most this many emitters are light (no tile); the workgroups that
+// nlight of their emitters take.
 int gather_light_max();
+int gather_light_blocks(bool fp32, int reach, int nlight);
+// Whether a batch's gather can take 16-byte units on these arrays.
+bool gather_wide_f64(const FieldPtrs<double>& f, const Geom& g);
+bool gather_wide_f32(const FieldPtrs<float>& f, const Geom& g);
 
 // ---- batched launches (one launch per phase over the jobs of many domains)
 template <typename T>
@@ -126,20 +132,14 @@ hipError_t sources_batch_f64(const SourceJob<double>* jobs, const int* start, in
                              int nblocks, hipStream_t st);
 hipError_t sources_batch_f32(const SourceJob<float>* jobs, const int* start, int njobs,
                              int nblocks, hipStream_t st);
-hipError_t gather_batch_f64(const GatherJob<double>* jobs, const int* start, int njobs,
-                            const int2* order, int nblocks, hipStream_t st);
-hipError_t gather_batch_f32(const GatherJob<float>* jobs, const int* start, int njobs,
-                            const int2* order, int nblocks, hipStream_t st);
+hipError_t gather_batch_f64(const GatherJob<double>* jobs, const int2* order, int nblocks,
+                            int reach, bool wide, hipStream_t st);
+hipError_t gather_batch_f32(const GatherJob<float>* jobs, const int2* order, int nblocks,
+                            int reach, bool wide, hipStream_t st);
 hipError_t tls_batch(const TlsJob* jobs, const int* start, int njobs, int nblocks,
                      hipStream_t st);
 hipError_t ml_batch(const MlJob* jobs, const int* start, int njobs, int nblocks, int nl,
                     hipStream_t st);
-// The light bins' emitters of a batch (no tile); light_per_block: emitters per block.
-hipError_t light_batch_f64(const LightJob<double>* jobs, const int* start, int njobs,
-                           int nblocks, hipStream_t st);
-hipError_t light_batch_f32(const LightJob<float>* jobs, const int* start, int njobs, int nblocks,
-                           hipStream_t st);
-int light_per_block(bool fp32);
 hipError_t scatter_batch_f64(const ScatterJob<double>* jobs, const int* start, int njobs,
                              const int2* order, int nblocks, hipStream_t st);
 hipError_t scatter_batch_f32(const ScatterJob<float>* jobs, const int* start, int njobs,

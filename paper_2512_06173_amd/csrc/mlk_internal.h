@@ -333,14 +333,15 @@ __device__ __forceinline__ void flux_partial_sum(const FieldPtrs<T>& f, const Ge
 
 // Binned emitter phase.
 // Gather bins: every emitter belongs to the bin of its centre cell; the
-// workgroup of a bin stages the bin plus a halo of kHalo cells.
+// workgroup of a bin stages the bin plus the windows' reach.
 // Scatter bins: every (bin, emitter) pair whose window touches the bin.
 // Gather bins of at most a few emitters ("light" bins) come after the others and
-// stage only the part of their tile that their windows cover.
+// stage nothing.
 struct BinPtrs {
   int nbx, nby, nbz;        // scatter bins per axis
   int ngather;              // gather bins holding at least one centre
-  int gdense;               // bins [0, gdense) stage the whole tile, the rest are light
+  int gdense;               // bins [0, gdense) stage their tile, the rest are light
+  int reach;                // cells that a window reaches beyond its centre cell, at most
   int glight0, nlight;      // gbin_em[glight0 .. glight0 + nlight): the light bins' emitters
   const int* gbin_org;      // [3*ngather] bin origin in unwrapped cells (centre-cell frame)
   const int* gbin_start;    // [ngather+1] CSR into gbin_em
@@ -457,18 +458,6 @@ struct SourceJob {
   int nblocks;  // bx * src.count
 };
 
-// The light bins' emitters of one domain, gathered without a tile.
-template <typename T>
-struct LightJob {
-  FieldPtrs<T> f;
-  Geom g;
-  const int* em;
-  int count;
-  WindowPtrs<T> win;
-  double* Et;
-  int nblocks;
-};
-
 template <typename T>
 struct GatherJob {
   FieldPtrs<T> f;
@@ -476,7 +465,7 @@ struct GatherJob {
   BinPtrs bins;
   WindowPtrs<T> win;
   double* Et;
-  int nblocks;  // bins.gdense (the light bins go to LightJob)
+  int nblocks;  // tiled bins, then the light bins' emitters a wavefront each
 };
 
 struct TlsJob {

@@ -154,7 +154,7 @@ struct mlk_sim {
   double* d_tls_rho = nullptr;
   // binned emitter phase
   int nbx = 0, nby = 0, nbz = 0;
-  int ngather = 0, nscatter = 0, gdense = 0, glight0 = 0, nlight = 0;
+  int ngather = 0, nscatter = 0, gdense = 0, glight0 = 0, nlight = 0, reach = 0;
   // estimated work of each gather / scatter launch block (host; orders a batch's blocks)
   std::vector<float> gwork, swork;
   // per axis, the planes that some emitter's union window reaches (the cells the
@@ -351,6 +351,7 @@ BinPtrs bin_ptrs(const mlk_sim* s) {
   b.nbz = s->nbz;
   b.ngather = s->ngather;
   b.gdense = s->gdense;
+  b.reach = s->reach;
   b.glight0 = s->glight0;
   b.nlight = s->nlight;
   b.gbin_org = s->d_gbin_org;
@@ -480,24 +481,34 @@ mlk_status build_bins(mlk_sim* s) {
         if (q >= 0 && q < n) s->wplane[a][q] = 1;
       }
   }
+  // how far a window reaches beyond its emitter's centre cell
+  s->reach = 0;
+  for (int e = 0; e < M; ++e)
+    for (int a = 0; a < 3; ++a) {
+      const int c = (int)std::floor(s->pos[3 * e + a]), o = worg[3 * e + a];
+      s->reach = std::max(s->reach, std::max(c - o, o + wn[3 * e + a] - 1 - c));
+    }
+  if (s->reach > kHalo) return fail(MLK_EUNSUPPORTED, "a kernel window reaches %d cells", s->reach);
+  // a batch's launch order: the light bins' workgroups come last
+  s->gwork.resize(s->gdense + gather_light_blocks(s->fp32, s->reach, s->nlight), 0.f);
   // FP32 gather: the eight emitters of a wavefront read their window rows from the
   // staged tile at the same row and plane offsets, so lane i of emitter m reads word
   // s_m + i + (a common offset), and emitters whose windows start in the same LDS
-  // banks conflict.  The bank of s_m is (x offset + tile width x y offset) mod 64 (the
-  // tile's plane stride is a multiple of 64 words).  Within a staged bin, the
+  // banks conflict.  The bank of s_m is its tile index mod 64.  Within a staged bin, the
   // emitters are sorted by that bank and dealt to the wavefronts with a stride, so
   // those of one wavefront (and of each half) start in banks spread around the 64.
   // Only the assignment of emitters to lanes changes, not any result.
   if (s->fp32) {
-    const int TXg = G[0] + 2 * kHalo;
+    const int TXg = G[0] + 2 * kHalo, R = s->reach <= 3 ? 3 : 4, PSg = TXg * (G[1] + 2 * R);
     std::vector<std::pair<int, int>> v;
     for (int b = 0; b < s->gdense; ++b) {
       const int q0 = gstart[b], q1 = gstart[b + 1], n = q1 - q0;
-      const int x0 = gorg[3 * b] - kHalo, y0 = gorg[3 * b + 1] - kHalo;
+      const int x0 = gorg[3 * b] - kHalo, y0 = gorg[3 * b + 1] - R, z0 = gorg[3 * b + 2] - R;
       v.clear();
       for (int q = q0; q < q1; ++q) {
         const int e = gem[q];
-        v.push_back({((worg[3 * e] - x0) + TXg * (worg[3 * e + 1] - y0)) & 63, e});
+        v.push_back({((worg[3 * e] - x0) + TXg * (worg[3 * e + 1] - y0) +
+                      PSg * (worg[3 * e + 2] - z0)) & 63, e});
       }
       std::stable_sort(v.begin(), v.end(), [](const std::pair<int, int>& x,
                                               const std::pair<int, int>& y) {
@@ -2590,7 +2601,8 @@ template <typename T>
 struct BatchTables {
   DevTable<FluxJob<T>> fsave, fpart, finish;
   DevTable<GatherJob<T>> gather;
-  DevTable<LightJob<T>> light;  // the light bins' emitters
+  int gather_reach = 0;     // over the members
+  bool gather_wide = true;  // every member's arrays take 16-byte units
   DevTable<FusedJob<T>> fused[kTileSlots];  // by tile shape, see tile_slot
   bool fused_lean[kTileSlots] = {};  // no job's box reaches a y or z layer
   DevTable<ShellJob<T>> shell;
@@ -2601,7 +2613,6 @@ struct BatchTables {
     free_table(fpart);
     free_table(finish);
     free_table(gather);
-    free_table(light);
     for (auto& f : fused) free_table(f);
     free_table(shell);
     free_table(sources);
@@ -2657,7 +2668,10 @@ mlk_status build_tables(mlk_batch* b, BatchTables<T> (&tab)[2]) {
     std::vector<SourceJob<T>> so;
     std::vector<ScatterJob<T>> sc;
     std::vector<const std::vector<float>*> gw, sw;  // block work of the non-empty jobs
-    std::vector<LightJob<T>> li;
+    int reach = 0;
+    bool wide = true;
+    for (mlk_sim* s : b->sims)
+      if (s->nem > 0) reach = std::max(reach, s->reach);
     for (mlk_sim* s : b->sims) {
       if (q == 1 && b->fused) swap_buffers(s);
       const FieldPtrs<T> cur = field_ptrs<T>(s);
@@ -2671,14 +2685,14 @@ mlk_status build_tables(mlk_batch* b, BatchTables<T> (&tab)[2]) {
       }
       fin.push_back({nxt, s->g, s->fp, ser, s->d_step, 1});
       if (s->nem > 0) {
-        ga.push_back({cur, s->g, bin_ptrs(s), window_ptrs<T>(s), s->d_Et, s->gdense});
+        // (the launch's shape follows the largest reach of the members)
+        const int nlb = gather_light_blocks(s->fp32, reach, s->nlight);
+        s->gwork.resize(s->gdense + nlb, 0.f);
+        ga.push_back({cur, s->g, bin_ptrs(s), window_ptrs<T>(s), s->d_Et, s->gdense + nlb});
         sc.push_back({nxt, s->g, bin_ptrs(s), window_ptrs<T>(s), s->d_mudot, s->nscatter});
-        if (s->gdense > 0) gw.push_back(&s->gwork);
-        if (s->nlight > 0) {
-          const int per = light_per_block(s->fp32);
-          li.push_back({cur, s->g, s->d_gbin_em + s->glight0, s->nlight, window_ptrs<T>(s),
-                        s->d_Et, (s->nlight + per - 1) / per});
-        }
+        if (s->gdense + nlb > 0) gw.push_back(&s->gwork);
+        if constexpr (sizeof(T) == 4) wide = wide && gather_wide_f32(cur, s->g);
+        else wide = wide && gather_wide_f64(cur, s->g);
         if (s->nscatter > 0) sw.push_back(&s->swork);
       }
       Box inner{};
@@ -2722,7 +2736,8 @@ mlk_status build_tables(mlk_batch* b, BatchTables<T> (&tab)[2]) {
     STCHK(make_table(t.finish, fin));
     STCHK(make_table(t.gather, ga));
     STCHK(make_order(t.gather, gw));
-    STCHK(make_table(t.light, li));
+    t.gather_reach = reach;
+    t.gather_wide = wide;
     for (int k = 0; k < kTileSlots; ++k) {
       // the smallest members first (by workgroups; measured a little faster than the
       // members' own order, and than the largest first)
@@ -2780,13 +2795,10 @@ mlk_status enqueue_batch_step(mlk_batch* b, const BatchTables<T>& t) {
     else return detect_batch_f64(d.jobs, d.start, d.njobs, d.nblocks, kind, st);
   };
   HIPCHK(detect(t.fsave, 0));
-  if constexpr (f32) HIPCHK(gather_batch_f32(t.gather.jobs, t.gather.start, t.gather.njobs,
-                                             t.gather.order, t.gather.norder, st));
-  else HIPCHK(gather_batch_f64(t.gather.jobs, t.gather.start, t.gather.njobs, t.gather.order,
-                               t.gather.norder, st));
-  if constexpr (f32) HIPCHK(light_batch_f32(t.light.jobs, t.light.start, t.light.njobs,
-                                            t.light.nblocks, st));
-  else HIPCHK(light_batch_f64(t.light.jobs, t.light.start, t.light.njobs, t.light.nblocks, st));
+  if constexpr (f32) HIPCHK(gather_batch_f32(t.gather.jobs, t.gather.order, t.gather.norder,
+                                             t.gather_reach, t.gather_wide, st));
+  else HIPCHK(gather_batch_f64(t.gather.jobs, t.gather.order, t.gather.norder, t.gather_reach,
+                               t.gather_wide, st));
   HIPCHK(tls_batch(b->tls.jobs, b->tls.start, b->tls.njobs, b->tls.nblocks, st));
   for (int n = 2; n <= kMaxLevels; ++n)
     HIPCHK(ml_batch(b->ml[n].jobs, b->ml[n].start, b->ml[n].njobs, b->ml[n].nblocks, n, st));
