@@ -445,8 +445,11 @@ void gather_bin_shape(bool fp32, int G[3]) {
 }
 
 // A bin of at most this many emitters is light: a wavefront reads 8^3 cells per
-// emitter, a workgroup 14 x 14 rows for all of them.
-int gather_light_max() { return 4; }
+// emitter, a workgroup 14 x 14 rows for all of them.  Step times with 2, 4, 8 and 16:
+// 160^3 with 10,000 emitters 149.7, 148.1, 143.8, 142.2 us; 187 x 149 x 163 FP64 with
+// 20,000 311, 299, 293, 295; 384^3 with 100,000 949, 950, 949, 963; 64-domain batch 585,
+// 576, 575, 577.
+int gather_light_max() { return 8; }
 
 int gather_light_blocks(bool fp32, int reach, int nlight) {
   const int w = (fp32 ? gather_threads<float>(reach) : gather_threads<double>(reach)) / 64;
