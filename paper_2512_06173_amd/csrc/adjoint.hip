@@ -115,7 +115,7 @@ constexpr int kOt[3][2] = {{2, 1}, {0, 2}, {1, 0}};
 // part.  In place, Eb leaves holding that of E^n (identity part, zero on the
 // walls, stored only where a wall zeroes it); out of place the H pass applies
 // the mask.
-template <typename T, bool OOP>
+template <typename T, bool OOP, bool NT>
 __device__ __forceinline__ void adj_e_cell(const AdjPtrs<T>& p, const AdjPtrs<T>& o,
                                            const Geom& g, int i, int j, int k) {
   const size_t id = (size_t)i + (size_t)g.n[0] * ((size_t)j + (size_t)g.n[1] * (size_t)k);
@@ -171,13 +171,13 @@ __device__ __forceinline__ void adj_e_cell(const AdjPtrs<T>& p, const AdjPtrs<T>
   }
   const AdjPtrs<T>& d = OOP ? o : p;
 #pragma unroll
-  for (int c = 0; c < 3; ++c) __builtin_nontemporal_store(hv[c] + hb[c], &d.H[c][id]);
+  for (int c = 0; c < 3; ++c) store_field<NT>(&d.H[c][id], hv[c] + hb[c]);
 }
 
 // Transposed H update.  Hb holds the adjoint of H^{n+1/2} (unchanged: identity
 // part); Eb gains the curl part.  Out of place, Hb is read from o (the E pass
 // wrote it there) and Eb from p, masked on the walls.
-template <typename T, bool OOP>
+template <typename T, bool OOP, bool NT>
 __device__ __forceinline__ void adj_h_cell(const AdjPtrs<T>& p, const AdjPtrs<T>& o,
                                            const Geom& g, int i, int j, int k) {
   const size_t id = (size_t)i + (size_t)g.n[0] * ((size_t)j + (size_t)g.n[1] * (size_t)k);
@@ -219,7 +219,7 @@ __device__ __forceinline__ void adj_h_cell(const AdjPtrs<T>& p, const AdjPtrs<T>
     }
   const AdjPtrs<T>& d = OOP ? o : p;
 #pragma unroll
-  for (int c = 0; c < 3; ++c) __builtin_nontemporal_store(ev[c] + eb[c], &d.E[c][id]);
+  for (int c = 0; c < 3; ++c) store_field<NT>(&d.E[c][id], ev[c] + eb[c]);
 }
 
 // Whole-grid transposed sweep in place: one thread per cell, 64 x 4 cells per
@@ -228,27 +228,27 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_adj_E(AdjPtrs<T> p, Geom g) {
   const int i = blockIdx.x * 64 + threadIdx.x, j = blockIdx.y * 4 + threadIdx.y, k = blockIdx.z;
   if (i >= g.n[0] || j >= g.n[1]) return;
-  adj_e_cell<T, false>(p, p, g, i, j, k);
+  adj_e_cell<T, false, true>(p, p, g, i, j, k);
 }
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_adj_H(AdjPtrs<T> p, Geom g) {
   const int i = blockIdx.x * 64 + threadIdx.x, j = blockIdx.y * 4 + threadIdx.y, k = blockIdx.z;
   if (i >= g.n[0] || j >= g.n[1]) return;
-  adj_h_cell<T, false>(p, p, g, i, j, k);
+  adj_h_cell<T, false, true>(p, p, g, i, j, k);
 }
 
 // The cells outside the fused transposed sweep's box (compact enumeration),
 // out of place: the E pass (E_PASS) writes o.H, then the H pass writes o.E.
-template <typename T, bool E_PASS>
+template <typename T, bool E_PASS, bool NT>
 __global__ __launch_bounds__(256) void k_adj_shell(AdjPtrs<T> p, AdjPtrs<T> o, Geom g,
                                                    ShellMap m) {
   const unsigned t = blockIdx.x * blockDim.x + threadIdx.x;
   if ((long long)t >= m.total) return;
   int i, j, k;
   shell_cell(g, m, t, i, j, k);
-  if (E_PASS) adj_e_cell<T, true>(p, o, g, i, j, k);
-  else adj_h_cell<T, true>(p, o, g, i, j, k);
+  if (E_PASS) adj_e_cell<T, true, NT>(p, o, g, i, j, k);
+  else adj_h_cell<T, true, NT>(p, o, g, i, j, k);
 }
 
 // Flux detector: part 0 adds dt dF/dE^{n+1} and dt dF/dH^{n+1/2}, part 1 adds
@@ -460,10 +460,13 @@ static hipError_t launch_adj_sweep(const AdjSweep<T>& a, const Geom& g, hipStrea
       o.H[c] = a.Ho[c];
     }
     const unsigned blocks = (unsigned)((m.total + 255) / 256);
-    hipLaunchKernelGGL((k_adj_shell<T, true>), dim3(blocks), dim3(256), 0, st, p, o, g, m);
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, st, p, o, g, m);
+    };
+    g.stream ? go(k_adj_shell<T, true, true>) : go(k_adj_shell<T, true, false>);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_adj_shell<T, false>), dim3(blocks), dim3(256), 0, st, p, o, g, m);
+    g.stream ? go(k_adj_shell<T, false, true>) : go(k_adj_shell<T, false, false>);
     return hipGetLastError();
   }
   if (g.n[2] > 65535) return hipErrorInvalidValue;  // one grid row per z plane

@@ -68,7 +68,7 @@ __device__ __forceinline__ bool wall_masked(const Geom& g, int c, int x, int y, 
 
 }  // namespace
 
-template <typename T, int TY, bool ZL>
+template <typename T, int TY, bool ZL, bool NT>
 __global__ __launch_bounds__(64 * TY) void k_adj_fused(AdjFused<T> p, Geom g, Box box, int kz,
                                                        int ntx, int nty, int nblocks) {
   constexpr int EW = 66, EH = TY + 2;   // W plane in LDS: x in [-1, 64], y in [-1, TY]
@@ -400,9 +400,9 @@ __global__ __launch_bounds__(64 * TY) void k_adj_fused(AdjFused<T> p, Geom g, Bo
       }
       hz += idx * ((dL[0][oslot] - D_at(p0, 0, tx + 1, ty)) - dWx_dy);
       // streaming stores, as in the forward sweep
-      __builtin_nontemporal_store(hx, &p.Ho[0][id]);
-      __builtin_nontemporal_store(hy, &p.Ho[1][id]);
-      __builtin_nontemporal_store(hz, &p.Ho[2][id]);
+      store_field<NT>(&p.Ho[0][id], hx);
+      store_field<NT>(&p.Ho[1][id], hy);
+      store_field<NT>(&p.Ho[2][id], hz);
     }
     // G of the own cell: x-terms of the transposed H update (psi adjoint updated)
     {
@@ -487,9 +487,9 @@ __global__ __launch_bounds__(64 * TY) void k_adj_fused(AdjFused<T> p, Geom g, Bo
         e1 = uk[1] + (cf * dHx_dz + idx * (gL[1][sw] - gL[1][sw + 1]));
       }
       const T e2 = uk[2] + (idx * (gL[0][sw] - gL[0][sw + 1]) - cf * dHx_dy);
-      __builtin_nontemporal_store(e0, &p.Eo[0][id]);
-      __builtin_nontemporal_store(e1, &p.Eo[1][id]);
-      __builtin_nontemporal_store(e2, &p.Eo[2][id]);
+      store_field<NT>(&p.Eo[0][id], e0);
+      store_field<NT>(&p.Eo[1][id], e1);
+      store_field<NT>(&p.Eo[2][id], e2);
     }
     hpx = hx;
     hpy = hy;
@@ -544,8 +544,11 @@ static hipError_t launch_adj_box(const AdjFused<T>& p, const Geom& g, const Box&
   if (ex <= 0 || ey <= 0 || ez <= 0) return hipSuccess;
   const int ntx = (box.hi[0] - (box.lo[0] & ~31) + 63) / 64, nty = (ey + TY - 1) / TY;
   const int nblocks = ntx * nty * ((ez + kz - 1) / kz);
-  hipLaunchKernelGGL((k_adj_fused<T, TY, ZL>), dim3(nblocks), dim3(64 * TY), 0, st, p, g, box, kz,
-                     ntx, nty, nblocks);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(64 * TY), 0, st, p, g, box, kz, ntx, nty,
+                       nblocks);
+  };
+  g.stream ? go(k_adj_fused<T, TY, ZL, true>) : go(k_adj_fused<T, TY, ZL, false>);
   return hipGetLastError();
 }
 

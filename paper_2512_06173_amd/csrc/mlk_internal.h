@@ -20,10 +20,35 @@ struct Geom {
   int nhi[3];        // CPML thickness on the high face
   int periodic[3];   // 1 if the axis wraps
   int wall[3];       // 1 if the low face is metallic (PEC or CPML-backed)
+  int stream;        // 1: new field values are stored past the caches (see stream_stores)
   double dt;
   double inv_dx;
   double dx;
 };
+
+// How the sweeps store new field values.  A grid larger than the 256 MB memory-side
+// cache stores them nontemporally: they are read again only in the next step, after the
+// whole grid has passed (256^3 FP32: 231 -> 224 us a step without emitters, 384^3 756 ->
+// 737; 160^3 FP64 160 -> 152).  A grid whose two field sets stay in that cache must not:
+// 128^3 FP32 50.6 -> 41.2 us with ordinary stores, 160^3 (197 MB) 79 -> 63, 128^3 FP64
+// (201 MB) 86.6 -> 83.9; from 226 MB on nontemporal ones win (168^3 FP32 95 against 97,
+// 176^3 102 against 113, 128 x 128 x 144 FP64 97 against 106).  Nor must FP32 grids whose rows
+// are no whole number of 32-byte sectors: the sectors at the tile edges would reach
+// memory in parts (250 x 256 x 256 without CPML 264 -> 199 us with ordinary stores, 333 x
+// 200 x 200 272 -> 241); FP64 rows, twice as long, show no such loss.
+inline int stream_stores(const int n[3], size_t esz) {
+  const double bytes = 12.0 * n[0] * n[1] * n[2] * (double)esz;
+  return bytes > 208e6 && (esz == 8 || (size_t)n[0] * esz % 32 == 0);
+}
+
+// Store of a new field value, past the caches (NT) or not.  The sweep kernels exist in
+// both forms: one kernel that branches on the grid's flag at every store ran 2% slower
+// (256^3 and 384^3).
+template <bool NT, typename T>
+__device__ __forceinline__ void store_field(T* p, T v) {
+  if constexpr (NT) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
 
 // XCD-aware order: hardware hands consecutive workgroups to the 8 XCDs in turn;
 // map them so that each XCD gets a contiguous range of work items (tiles, bins,

@@ -1300,6 +1300,7 @@ mlk_status mlk_create(const mlk_grid_desc* gd, mlk_sim** out) {
   g.inv_dx = 1.0 / gd->dx;
   g.dt = gd->courant * gd->dx;
   s->ncell = (size_t)n[0] * n[1] * n[2];
+  g.stream = stream_stores(n, s->esz);
 
   auto bail = [&](mlk_status st) {
     release(s);
@@ -2601,6 +2602,7 @@ template <typename T>
 struct BatchTables {
   DevTable<FluxJob<T>> fsave, fpart, finish;
   DevTable<GatherJob<T>> gather;
+  bool stream = false;      // new field values past the caches: most cells' members ask for it
   int gather_reach = 0;     // over the members
   bool gather_wide = true;  // every member's arrays take 16-byte units
   DevTable<FusedJob<T>> fused[kTileSlots];  // by tile shape, see tile_slot
@@ -2736,6 +2738,12 @@ mlk_status build_tables(mlk_batch* b, BatchTables<T> (&tab)[2]) {
     STCHK(make_table(t.finish, fin));
     STCHK(make_table(t.gather, ga));
     STCHK(make_order(t.gather, gw));
+    double streamed = 0.0, cells = 0.0;
+    for (const mlk_sim* s : b->sims) {
+      cells += (double)s->ncell;
+      streamed += s->g.stream ? (double)s->ncell : 0.0;
+    }
+    t.stream = streamed > 0.5 * cells;
     t.gather_reach = reach;
     t.gather_wide = wide;
     for (int k = 0; k < kTileSlots; ++k) {
@@ -2806,16 +2814,16 @@ mlk_status enqueue_batch_step(mlk_batch* b, const BatchTables<T>& t) {
     const DevTable<FusedJob<T>>& f = t.fused[k];
     if constexpr (f32)
       HIPCHK(sweep_fused_batch_f32(f.jobs, f.start, f.njobs, f.nblocks, slot_tx(k), slot_ty(k),
-                                   t.fused_lean[k], st));
+                                   t.fused_lean[k], t.stream, st));
     else
       HIPCHK(sweep_fused_batch_f64(f.jobs, f.start, f.njobs, f.nblocks, slot_tx(k), slot_ty(k),
-                                   t.fused_lean[k], st));
+                                   t.fused_lean[k], t.stream, st));
   }
   for (int h = 1; h >= 0; --h) {
     if constexpr (f32) HIPCHK(shell_batch_f32(t.shell.jobs, t.shell.start, t.shell.njobs,
-                                              t.shell.nblocks, h == 1, st));
+                                              t.shell.nblocks, h == 1, t.stream, st));
     else HIPCHK(shell_batch_f64(t.shell.jobs, t.shell.start, t.shell.njobs, t.shell.nblocks,
-                                h == 1, st));
+                                h == 1, t.stream, st));
   }
   if constexpr (f32) HIPCHK(sources_batch_f32(t.sources.jobs, t.sources.start, t.sources.njobs,
                                               t.sources.nblocks, st));
@@ -3276,16 +3284,18 @@ mlk_status time_batch_sweep(mlk_batch* b, const BatchTables<T>& t, double* us) {
       const DevTable<FusedJob<T>>& f = t.fused[k];
       if constexpr (f32)
         err = sweep_fused_batch_f32(f.jobs, f.start, f.njobs, f.nblocks, slot_tx(k), slot_ty(k),
-                                    t.fused_lean[k], st);
+                                    t.fused_lean[k], t.stream, st);
       else
         err = sweep_fused_batch_f64(f.jobs, f.start, f.njobs, f.nblocks, slot_tx(k), slot_ty(k),
-                                    t.fused_lean[k], st);
+                                    t.fused_lean[k], t.stream, st);
     }
     for (int h = 1; h >= 0 && err == hipSuccess; --h) {
       if constexpr (f32)
-        err = shell_batch_f32(t.shell.jobs, t.shell.start, t.shell.njobs, t.shell.nblocks, h == 1, st);
+        err = shell_batch_f32(t.shell.jobs, t.shell.start, t.shell.njobs, t.shell.nblocks, h == 1,
+                              t.stream, st);
       else
-        err = shell_batch_f64(t.shell.jobs, t.shell.start, t.shell.njobs, t.shell.nblocks, h == 1, st);
+        err = shell_batch_f64(t.shell.jobs, t.shell.start, t.shell.njobs, t.shell.nblocks, h == 1,
+                              t.stream, st);
     }
   };
   constexpr int kReps = 3;

@@ -52,10 +52,10 @@ template <typename T>
 __device__ __forceinline__ void st32(T* base, unsigned i, T v) {
   *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + i * (unsigned)sizeof(T)) = v;
 }
-template <typename T>
-__device__ __forceinline__ void st32nt(T* base, unsigned i, T v) {
-  __builtin_nontemporal_store(v, reinterpret_cast<T*>(reinterpret_cast<char*>(base) +
-                                                      i * (unsigned)sizeof(T)));
+// new field value, past the caches (NT) or not
+template <bool NT, typename T>
+__device__ __forceinline__ void st32new(T* base, unsigned i, T v) {
+  store_field<NT>(reinterpret_cast<T*>(reinterpret_cast<char*>(base) + i * (unsigned)sizeof(T)), v);
 }
 // column / plane offsets as 32-bit element indices (valid = false: a zero cell)
 struct Col32 {
@@ -116,7 +116,7 @@ __device__ __forceinline__ int chunk_start(const Geom& g, int lo, int hi, int c,
   return lo + min(max((int)(z + 0.5f), c), ez - (nch - c));
 }
 
-template <typename T, int TX, int TY, int CPM = 2>
+template <typename T, int TX, int TY, int CPM, bool NT>
 __device__ __forceinline__ void fused_body(const FieldPtrs<T>& a, const FieldPtrs<T>& b,
                                            const Geom& g, const Box& box, int kz, int ntx,
                                            int nty, int nblocks, int bid_in) {
@@ -468,11 +468,9 @@ __device__ __forceinline__ void fused_body(const FieldPtrs<T>& a, const FieldPtr
       hx -= dt * (dEz_dy - dEy_dz);
       hy -= dt * (dEx_dz - dEz_dx);
       hz -= dt * (dEy_dx - dEx_dy);
-      // streaming stores: the new fields are read again only in the next step,
-      // long after this sweep has passed through the caches
-      st32nt(b.H[0], id, hx);
-      st32nt(b.H[1], id, hy);
-      st32nt(b.H[2], id, hz);
+      st32new<NT>(b.H[0], id, hx);
+      st32new<NT>(b.H[1], id, hy);
+      st32new<NT>(b.H[2], id, hz);
     }
     hL[0][(ty + 1) * HW + tx + 1] = hx;
     hL[1][(ty + 1) * HW + tx + 1] = hy;
@@ -554,9 +552,9 @@ __device__ __forceinline__ void fused_body(const FieldPtrs<T>& a, const FieldPtr
       const T e0 = tangential_wall(g, 0, i, j, k) ? T(0) : ek[0] + ce * cx;
       const T e1 = tangential_wall(g, 1, i, j, k) ? T(0) : ek[1] + ce * cy;
       const T e2 = tangential_wall(g, 2, i, j, k) ? T(0) : ek[2] + ce * cz;
-      st32nt(b.E[0], id, e0);
-      st32nt(b.E[1], id, e1);
-      st32nt(b.E[2], id, e2);
+      st32new<NT>(b.E[0], id, e0);
+      st32new<NT>(b.E[1], id, e1);
+      st32new<NT>(b.E[2], id, e2);
     }
     hpx = hx;
     hpy = hy;
@@ -566,7 +564,7 @@ __device__ __forceinline__ void fused_body(const FieldPtrs<T>& a, const FieldPtr
   }
 }
 
-template <typename T, int TX, int TY>
+template <typename T, int TX, int TY, bool NT>
 __global__ __launch_bounds__(TX * TY, 4) void k_fused(FieldPtrs<T> a, FieldPtrs<T> b, Geom g,
                                                    Box box, int kz, int ntx, int nty,
                                                    int nblocks, SideWork side) {
@@ -574,12 +572,12 @@ __global__ __launch_bounds__(TX * TY, 4) void k_fused(FieldPtrs<T> a, FieldPtrs<
     side_body<T, TX * TY>(side, a, g, (int)blockIdx.x - nblocks);
     return;
   }
-  fused_body<T, TX, TY>(a, b, g, box, kz, ntx, nty, nblocks, blockIdx.x);
+  fused_body<T, TX, TY, 2, NT>(a, b, g, box, kz, ntx, nty, nblocks, blockIdx.x);
 }
 
 // Boxes where no y or z layer needs stretching (x layers at most): the same body
 // without the y/z layer code, built for more waves per SIMD.
-template <typename T, int TX, int TY, int CPM, int W>
+template <typename T, int TX, int TY, int CPM, int W, bool NT>
 __global__ __launch_bounds__(TX * TY, W) void k_fused_lean(FieldPtrs<T> a, FieldPtrs<T> b, Geom g,
                                                         Box box, int kz, int ntx, int nty,
                                                         int nblocks, SideWork side) {
@@ -587,30 +585,30 @@ __global__ __launch_bounds__(TX * TY, W) void k_fused_lean(FieldPtrs<T> a, Field
     side_body<T, TX * TY>(side, a, g, (int)blockIdx.x - nblocks);
     return;
   }
-  fused_body<T, TX, TY, CPM>(a, b, g, box, kz, ntx, nty, nblocks, blockIdx.x);
+  fused_body<T, TX, TY, CPM, NT>(a, b, g, box, kz, ntx, nty, nblocks, blockIdx.x);
 }
 
 // The frame of y and z layers around such a box, up to four boxes in one launch
 // (full kernel, 64 x 4 tiles): block b belongs to the job whose start range holds it.
-template <typename T>
+template <typename T, bool NT>
 __global__ __launch_bounds__(256, 4) void k_fused_frame(FrameJobs<T> fj) {
   int j = 0;
   while (j + 1 < fj.njobs && (int)blockIdx.x >= fj.start[j + 1]) ++j;
   const FusedJob<T>& J = fj.job[j];
-  fused_body<T, 64, 4>(J.a, J.b, J.g, J.box, J.kz, J.ntx, J.nty, J.nblocks,
+  fused_body<T, 64, 4, 2, NT>(J.a, J.b, J.g, J.box, J.kz, J.ntx, J.nty, J.nblocks,
                    (int)blockIdx.x - fj.start[j]);
 }
 
 // One launch over the jobs of a batch of domains (see BatchJobs); CPM and W as for
 // the single-domain kernels (the lean form when no job's box reaches a y or z layer).
-template <typename T, int TX, int TY, int CPM, int W>
+template <typename T, int TX, int TY, int CPM, int W, bool NT>
 __global__ __launch_bounds__(TX * TY, W) void k_fused_batch(const FusedJob<T>* jobs,
                                                          const int* start, int njobs) {
   const int j = find_job(start, njobs, blockIdx.x);
   const FusedJob<T> J = load_job(jobs, j);
   const int bid = blockIdx.x - start[j];
   if (J.tx != TX || J.ty != TY || bid >= J.nblocks) return;
-  fused_body<T, TX, TY, CPM>(J.a, J.b, J.g, J.box, J.kz, J.ntx, J.nty, J.nblocks, bid);
+  fused_body<T, TX, TY, CPM, NT>(J.a, J.b, J.g, J.box, J.kz, J.ntx, J.nty, J.nblocks, bid);
 }
 
 // Waves per SIMD the lean kernels are built for: FP32 without layer code needs about
@@ -636,15 +634,15 @@ static hipError_t launch_fused(const FieldPtrs<T>& a, const FieldPtrs<T>& b, con
   const dim3 grid(side.blocks + nblocks), block(TX * TY);
   if (grid.x == 0) return hipSuccess;
   constexpr int W0 = LeanWaves<T, TX, TY, 0>::value, W1 = LeanWaves<T, TX, TY, 1>::value;
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, st, a, b, g, box, kz, ntx, nty, nblocks, side);
+  };
   if (cpm == 0)
-    hipLaunchKernelGGL((k_fused_lean<T, TX, TY, 0, W0>), grid, block, 0, st, a, b, g, box, kz, ntx,
-                       nty, nblocks, side);
+    g.stream ? go(k_fused_lean<T, TX, TY, 0, W0, true>) : go(k_fused_lean<T, TX, TY, 0, W0, false>);
   else if (cpm == 1)
-    hipLaunchKernelGGL((k_fused_lean<T, TX, TY, 1, W1>), grid, block, 0, st, a, b, g, box, kz, ntx,
-                       nty, nblocks, side);
+    g.stream ? go(k_fused_lean<T, TX, TY, 1, W1, true>) : go(k_fused_lean<T, TX, TY, 1, W1, false>);
   else
-    hipLaunchKernelGGL((k_fused<T, TX, TY>), grid, block, 0, st, a, b, g, box, kz, ntx, nty,
-                       nblocks, side);
+    g.stream ? go(k_fused<T, TX, TY, true>) : go(k_fused<T, TX, TY, false>);
   return hipGetLastError();
 }
 
@@ -736,35 +734,43 @@ static hipError_t launch_frame(const FieldPtrs<T>& a, const FieldPtrs<T>& b, con
   }
   fj.start[fj.njobs] = total;
   if (total == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_fused_frame<T>, dim3(total), dim3(256), 0, st, fj);
+  if (g.stream)
+    hipLaunchKernelGGL((k_fused_frame<T, true>), dim3(total), dim3(256), 0, st, fj);
+  else
+    hipLaunchKernelGGL((k_fused_frame<T, false>), dim3(total), dim3(256), 0, st, fj);
   return hipGetLastError();
 }
 
 template <typename T, int TX, int TY>
 static void launch_fused_batch_t(const FusedJob<T>* jobs, const int* start, int njobs,
-                                 int nblocks, bool lean, hipStream_t st) {
+                                 int nblocks, bool lean, bool stream, hipStream_t st) {
+  constexpr int W = LeanWaves<T, TX, TY, 1>::value;
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(TX * TY), 0, st, jobs, start, njobs);
+  };
   if (lean)
-    hipLaunchKernelGGL((k_fused_batch<T, TX, TY, 1, LeanWaves<T, TX, TY, 1>::value>),
-                       dim3(nblocks), dim3(TX * TY), 0, st, jobs, start, njobs);
+    stream ? go(k_fused_batch<T, TX, TY, 1, W, true>) : go(k_fused_batch<T, TX, TY, 1, W, false>);
   else
-    hipLaunchKernelGGL((k_fused_batch<T, TX, TY, 2, 4>), dim3(nblocks), dim3(TX * TY), 0, st,
-                       jobs, start, njobs);
+    stream ? go(k_fused_batch<T, TX, TY, 2, 4, true>) : go(k_fused_batch<T, TX, TY, 2, 4, false>);
 }
 
 template <typename T, int TX>
 static void launch_fused_batch_tx(const FusedJob<T>* jobs, const int* start, int njobs,
-                                  int nblocks, int ty, bool lean, hipStream_t st) {
-  if (ty == 16) launch_fused_batch_t<T, TX, 16>(jobs, start, njobs, nblocks, lean, st);
-  else if (ty == 8) launch_fused_batch_t<T, TX, 8>(jobs, start, njobs, nblocks, lean, st);
-  else launch_fused_batch_t<T, TX, 4>(jobs, start, njobs, nblocks, lean, st);
+                                  int nblocks, int ty, bool lean, bool stream, hipStream_t st) {
+  if (ty == 16) launch_fused_batch_t<T, TX, 16>(jobs, start, njobs, nblocks, lean, stream, st);
+  else if (ty == 8) launch_fused_batch_t<T, TX, 8>(jobs, start, njobs, nblocks, lean, stream, st);
+  else launch_fused_batch_t<T, TX, 4>(jobs, start, njobs, nblocks, lean, stream, st);
 }
 
 template <typename T>
 static hipError_t launch_fused_batch(const FusedJob<T>* jobs, const int* start, int njobs,
-                                     int nblocks, int tx, int ty, bool lean, hipStream_t st) {
+                                     int nblocks, int tx, int ty, bool lean, bool stream,
+                                     hipStream_t st) {
   if (nblocks <= 0) return hipSuccess;
-  if (tx == 32) launch_fused_batch_tx<T, 32>(jobs, start, njobs, nblocks, ty, lean, st);
-  else launch_fused_batch_tx<T, 64>(jobs, start, njobs, nblocks, ty, lean, st);
+  if (tx == 32)
+    launch_fused_batch_tx<T, 32>(jobs, start, njobs, nblocks, ty, lean, stream, st);
+  else
+    launch_fused_batch_tx<T, 64>(jobs, start, njobs, nblocks, ty, lean, stream, st);
   return hipGetLastError();
 }
 
@@ -787,12 +793,14 @@ hipError_t sweep_frame_f32(const FieldPtrs<float>& a, const FieldPtrs<float>& b,
   return launch_frame<float>(a, b, g, inner, kz, st);
 }
 hipError_t sweep_fused_batch_f64(const FusedJob<double>* jobs, const int* start, int njobs,
-                                 int nblocks, int tx, int ty, bool lean, hipStream_t st) {
-  return launch_fused_batch<double>(jobs, start, njobs, nblocks, tx, ty, lean, st);
+                                 int nblocks, int tx, int ty, bool lean, bool stream,
+                                 hipStream_t st) {
+  return launch_fused_batch<double>(jobs, start, njobs, nblocks, tx, ty, lean, stream, st);
 }
 hipError_t sweep_fused_batch_f32(const FusedJob<float>* jobs, const int* start, int njobs,
-                                 int nblocks, int tx, int ty, bool lean, hipStream_t st) {
-  return launch_fused_batch<float>(jobs, start, njobs, nblocks, tx, ty, lean, st);
+                                 int nblocks, int tx, int ty, bool lean, bool stream,
+                                 hipStream_t st) {
+  return launch_fused_batch<float>(jobs, start, njobs, nblocks, tx, ty, lean, stream, st);
 }
 
 }  // namespace mlk

@@ -17,7 +17,7 @@
 namespace mlk {
 
 // H^{n+1/2} at cell (i,j,k) from E^n of `in`.
-template <typename T>
+template <bool NT, typename T>
 __device__ __forceinline__ void update_h_cell(const FieldPtrs<T>& in, const FieldPtrs<T>& out,
                                               const Geom& g, int i, int j, int k) {
   // products are not contracted into fused multiply-adds, as in the fused sweep,
@@ -43,15 +43,14 @@ __device__ __forceinline__ void update_h_cell(const FieldPtrs<T>& in, const Fiel
   const T h0 = in.H[0][id] - dt * (dEz_dy - dEy_dz);
   const T h1 = in.H[1][id] - dt * (dEx_dz - dEz_dx);
   const T h2 = in.H[2][id] - dt * (dEy_dx - dEx_dy);
-  // streaming stores (as in the fused sweep)
-  __builtin_nontemporal_store(h0, &out.H[0][id]);
-  __builtin_nontemporal_store(h1, &out.H[1][id]);
-  __builtin_nontemporal_store(h2, &out.H[2][id]);
+  store_field<NT>(&out.H[0][id], h0);
+  store_field<NT>(&out.H[1][id], h1);
+  store_field<NT>(&out.H[2][id], h2);
 }
 
 // E^{n+1} at cell (i,j,k); H^{n+1/2} is read from `out` (already advanced
 // everywhere), E^n from `in`.
-template <typename T>
+template <bool NT, typename T>
 __device__ __forceinline__ void update_e_cell(const FieldPtrs<T>& in, const FieldPtrs<T>& out,
                                               const Geom& g, int i, int j, int k) {
   // products are not contracted into fused multiply-adds, as in the fused sweep,
@@ -81,34 +80,34 @@ __device__ __forceinline__ void update_e_cell(const FieldPtrs<T>& in, const Fiel
   const T n0 = tangential_wall(g, 0, i, j, k) ? T(0) : e0 + ce * cx;
   const T n1 = tangential_wall(g, 1, i, j, k) ? T(0) : e1 + ce * cy;
   const T n2 = tangential_wall(g, 2, i, j, k) ? T(0) : e2 + ce * cz;
-  __builtin_nontemporal_store(n0, &out.E[0][id]);
-  __builtin_nontemporal_store(n1, &out.E[1][id]);
-  __builtin_nontemporal_store(n2, &out.E[2][id]);
+  store_field<NT>(&out.E[0][id], n0);
+  store_field<NT>(&out.E[1][id], n1);
+  store_field<NT>(&out.E[2][id], n2);
 }
 
-template <typename T, bool H>
+template <typename T, bool H, bool NT>
 __global__ __launch_bounds__(256) void k_update_box(FieldPtrs<T> in, FieldPtrs<T> out, Geom g,
                                                     Box box) {
   const int i = box.lo[0] + blockIdx.x * blockDim.x + threadIdx.x;
   const int j = box.lo[1] + blockIdx.y * blockDim.y + threadIdx.y;
   const int k = box.lo[2] + blockIdx.z;
   if (i >= box.hi[0] || j >= box.hi[1]) return;
-  if (H) update_h_cell(in, out, g, i, j, k);
-  else update_e_cell(in, out, g, i, j, k);
+  if (H) update_h_cell<NT>(in, out, g, i, j, k);
+  else update_e_cell<NT>(in, out, g, i, j, k);
 }
 
-template <typename T, bool H>
+template <typename T, bool H, bool NT>
 __global__ __launch_bounds__(256) void k_update_shell(FieldPtrs<T> in, FieldPtrs<T> out, Geom g,
                                                       ShellMap m) {
   const unsigned t = blockIdx.x * blockDim.x + threadIdx.x;
   if ((long long)t >= m.total) return;
   int i, j, k;
   shell_cell(g, m, t, i, j, k);
-  if (H) update_h_cell(in, out, g, i, j, k);
-  else update_e_cell(in, out, g, i, j, k);
+  if (H) update_h_cell<NT>(in, out, g, i, j, k);
+  else update_e_cell<NT>(in, out, g, i, j, k);
 }
 
-template <typename T, bool H>
+template <typename T, bool H, bool NT>
 __global__ __launch_bounds__(256) void k_update_shell_batch(const ShellJob<T>* jobs,
                                                             const int* start, int njobs) {
   const int jb = find_job(start, njobs, blockIdx.x);
@@ -117,8 +116,8 @@ __global__ __launch_bounds__(256) void k_update_shell_batch(const ShellJob<T>* j
   if ((long long)t >= J.m.total) return;
   int i, j, k;
   shell_cell(J.g, J.m, t, i, j, k);
-  if (H) update_h_cell(J.in, J.out, J.g, i, j, k);
-  else update_e_cell(J.in, J.out, J.g, i, j, k);
+  if (H) update_h_cell<NT>(J.in, J.out, J.g, i, j, k);
+  else update_e_cell<NT>(J.in, J.out, J.g, i, j, k);
 }
 
 // Soft source currents J at t = (n + 1/2) dt:  E -= (dt/eps_r) J.  One thread per
@@ -195,8 +194,9 @@ static hipError_t launch_plain(const FieldPtrs<T>& in, const FieldPtrs<T>& out, 
       const int ex = b.hi[0] - b.lo[0], ey = b.hi[1] - b.lo[1], ez = b.hi[2] - b.lo[2];
       if (ex <= 0 || ey <= 0 || ez <= 0) continue;
       dim3 grid((ex + 63) / 64, (ey + 3) / 4, ez);
-      if (pass == 0) hipLaunchKernelGGL((k_update_box<T, true>), grid, block, 0, st, in, out, g, b);
-      else hipLaunchKernelGGL((k_update_box<T, false>), grid, block, 0, st, in, out, g, b);
+      auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, st, in, out, g, b); };
+      if (pass == 0) g.stream ? go(k_update_box<T, true, true>) : go(k_update_box<T, true, false>);
+      else g.stream ? go(k_update_box<T, false, true>) : go(k_update_box<T, false, false>);
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
@@ -232,12 +232,11 @@ static hipError_t launch_shell(const FieldPtrs<T>& in, const FieldPtrs<T>& out, 
   if (m.total == 0) return hipSuccess;
   if (m.total >= 0x7fffff00LL) return hipErrorInvalidValue;  // 32-bit cell index
   const long long blocks = (m.total + 255) / 256;
-  if (h_pass)
-    hipLaunchKernelGGL((k_update_shell<T, true>), dim3((unsigned)blocks), dim3(256), 0, st, in,
-                       out, g, m);
-  else
-    hipLaunchKernelGGL((k_update_shell<T, false>), dim3((unsigned)blocks), dim3(256), 0, st, in,
-                       out, g, m);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, st, in, out, g, m);
+  };
+  if (h_pass) g.stream ? go(k_update_shell<T, true, true>) : go(k_update_shell<T, true, false>);
+  else g.stream ? go(k_update_shell<T, false, true>) : go(k_update_shell<T, false, false>);
   return hipGetLastError();
 }
 
@@ -269,14 +268,13 @@ hipError_t sweep_shell_f32(const FieldPtrs<float>& in, const FieldPtrs<float>& o
 }
 template <typename T>
 static hipError_t launch_shell_batch(const ShellJob<T>* jobs, const int* start, int njobs,
-                                     int nblocks, bool h_pass, hipStream_t st) {
+                                     int nblocks, bool h_pass, bool stream, hipStream_t st) {
   if (nblocks <= 0) return hipSuccess;
-  if (h_pass)
-    hipLaunchKernelGGL((k_update_shell_batch<T, true>), dim3(nblocks), dim3(256), 0, st, jobs,
-                       start, njobs);
-  else
-    hipLaunchKernelGGL((k_update_shell_batch<T, false>), dim3(nblocks), dim3(256), 0, st, jobs,
-                       start, njobs);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(256), 0, st, jobs, start, njobs);
+  };
+  if (h_pass) stream ? go(k_update_shell_batch<T, true, true>) : go(k_update_shell_batch<T, true, false>);
+  else stream ? go(k_update_shell_batch<T, false, true>) : go(k_update_shell_batch<T, false, false>);
   return hipGetLastError();
 }
 template <typename T>
@@ -286,13 +284,13 @@ static hipError_t launch_sources_batch(const SourceJob<T>* jobs, const int* star
   hipLaunchKernelGGL(k_sources_batch<T>, dim3(nblocks), dim3(256), 0, st, jobs, start, njobs);
   return hipGetLastError();
 }
-hipError_t shell_batch_f64(const ShellJob<double>* jobs, const int* start, int njobs, int nblocks,
-                           bool h_pass, hipStream_t st) {
-  return launch_shell_batch<double>(jobs, start, njobs, nblocks, h_pass, st);
+hipError_t shell_batch_f64(const ShellJob<double>* jobs, const int* start, int njobs,
+                           int nblocks, bool h_pass, bool stream, hipStream_t st) {
+  return launch_shell_batch<double>(jobs, start, njobs, nblocks, h_pass, stream, st);
 }
-hipError_t shell_batch_f32(const ShellJob<float>* jobs, const int* start, int njobs, int nblocks,
-                           bool h_pass, hipStream_t st) {
-  return launch_shell_batch<float>(jobs, start, njobs, nblocks, h_pass, st);
+hipError_t shell_batch_f32(const ShellJob<float>* jobs, const int* start, int njobs,
+                           int nblocks, bool h_pass, bool stream, hipStream_t st) {
+  return launch_shell_batch<float>(jobs, start, njobs, nblocks, h_pass, stream, st);
 }
 hipError_t sources_batch_f64(const SourceJob<double>* jobs, const int* start, int njobs,
                              int nblocks, hipStream_t st) {
