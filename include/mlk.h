@@ -460,7 +460,7 @@ mlk_status mlk_batch_autotune(mlk_batch* b, const char* cache_path);
  * per workgroup kz (mlk_set_tuning; the sweep cuts the box's depth into depth/kz
  * chunks, rounded up, of equal cost, z-layer planes weighing more than interior
  * ones, so a chunk may hold a few planes more or less than kz), and the tile width,
- * 64 (the default) or 32 x
+ * 64 or 32 x
  * cells per workgroup (mlk_set_tile_width: narrower tiles give small grids more
  * workgroups; EINVAL for other widths, EUNSUPPORTED when the sim is in layer mode 2
  * and the width leaves no fused box over every x column).  All MLK_ESTATE while the
@@ -470,7 +470,9 @@ mlk_status mlk_batch_autotune(mlk_batch* b, const char* cache_path);
  * rounds (the state is left untouched; each candidate keeps its best round) and
  * keeps the fastest; with cache_path (NULL: no cache) results are read from and
  * added to a JSON file keyed by precision, grid, CPML thicknesses and periodic
- * axes.  The result does not depend on the tile shape (each
+ * axes.  A new sim starts from a rule on the grid's size and row length; until a call
+ * or a tuner sets something, it uses and reports 64 x 4 tiles instead while it is a
+ * member of a batch.  The result does not depend on the tile shape (each
  * cell's arithmetic is the same), only the speed does.  Plain-sweep sims have
  * nothing to tune. */
 mlk_status mlk_autotune(mlk_sim* s, const char* cache_path);
@@ -486,8 +488,9 @@ mlk_status mlk_get_tile_width(mlk_sim* s, int32_t* tx);
  * by the lean fused kernel (no y/z layer code, fewer registers, more waves per
  * SIMD), then the layer frame around it (the z slabs and the y slabs) in one launch
  * of the full kernel (needs y or z layers and a box spanning every x column).  The
- * default is 1 when the y and z layers are a small part of the grid ((nlo + nhi) / n
- * summed over y and z at most 1/4), else 0; mlk_autotune times every mode and keeps
+ * default is 1 (in a batch, until a call or a tuner sets something: 1 when the y and z
+ * layers are a small part of the grid, (nlo + nhi) / n summed over y and z at most 1/4,
+ * else 0); mlk_autotune times every mode and keeps
  * the fastest (and caches it).  Like the tile shape, the mode changes speed, not
  * results.  FP64 fields: always 0 (MLK_EUNSUPPORTED for 1 or 2).  MLK_ESTATE while
  * the sim belongs to a batch (a batch runs modes 0 and 1; a member in mode 2 runs as

@@ -79,6 +79,11 @@ struct DevBuf {
 
 }  // namespace
 
+// How the fused sweep is cut: tile width and rows, z planes per chunk, layer mode.
+struct Tiling {
+  int tx, ty, kz, layers;
+};
+
 struct mlk_sim {
   mlk_grid_desc desc{};
   // phase timing: event pool, pending (phase, start event, end event) marks
@@ -110,6 +115,8 @@ struct mlk_sim {
   int ty = 4;       // y rows per workgroup of the fused sweep (4, 8 or 16)
   int tx = 64;      // x cells per workgroup of the fused sweep (64 or 32)
   int layer_mode = 0;  // y/z CPML layers: 0 shell passes, 1 in the fused kernel, 2 frame launch
+  bool tuned = false;  // any of these four was set, by a call or a tuner
+  Tiling member{};     // used until then in a batch (see default_tiling)
   bool vacuum = true;   // eps_r = 1 in every cell: the fused sweep reads no 1/eps_r
   hipStream_t batch_stream = nullptr;  // stream of the batch this sim belongs to
   bool in_batch = false;
@@ -873,8 +880,73 @@ Box interior_box(const Geom& g, bool layers, int tx) {
   return inner;
 }
 
+// The tiling of a sim that steps alone until it is tuned.  The launch lasts as long as
+// its slowest workgroups, so chunks are cut to give one round of the chip: about 4096
+// wavefronts (16 on each of 256 CUs, what the full kernel's registers allow), half as
+// many again without layers.  Then, from step times of 30 grids (us, best of all shapes
+// in brackets, with one emitter):
+//  * FP32, y and z layers always in the kernel: 32^3 with CPML 10 32.9 -> 19.7 [19.7],
+//    64^3 39.5 -> 24.5 [24.3], 128^3 55.3 -> 41.3 [41.3], 60 x 200 x 90 45.5 -> 37.8
+//    [37.0], 128 x 128 x 1 17.1 -> 16.3 [15.7]
+//  * rows of 32, 96, 160, ... cells take 32-wide tiles (64-wide ones leave half of the
+//    last tile idle): 96^3 46.4 -> 32.2 [32.2], 160^3 77.1 -> 66.0 [66.0]
+//  * rows off the 128-byte lines share lines between tiles, which short chunks keep in
+//    L2: 176^3 120.7 -> 114.3 [112.6], 250 x 200 x 200 216.6 -> 200.1 [200.1], 200^3 206.5 ->
+//    197.3 [181.8, with the layers in the shell passes]
+//  * where one round would need very long chunks, 32 planes and tall tiles: 320^3
+//    518.7 -> 470.2 [470.2], 384^3 about 780 -> 737
+//  * FP64 (layers in the shell passes), 64 x 4 tiles and short chunks: 32^3 without CPML
+//    25.1 -> 18.5 [17.9], 48^3 42.9 -> 33.5 [33.3], 187 x 149 x 163 195.6 -> 193 [192.7]
+// The figures before are of member_tiling, which a batch's members keep.
+Tiling default_tiling(const Geom& g, bool fp32) {
+  Tiling t{64, 4, 8, 0};
+  const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
+  if (fp32 && nx % 64 == 32) {
+    const Box a = interior_box(g, false, 64), b = interior_box(g, false, 32);
+    if (b.lo[0] <= a.lo[0] && b.hi[0] >= a.hi[0]) t.tx = 32;
+  }
+  const bool layers = has_cpml(g, 1) || has_cpml(g, 2);
+  t.layers = fp32 ? 1 : 0;
+  const long long cols =
+      std::max<long long>(1, (long long)((nx + t.tx - 1) / t.tx) * t.tx * ny / 64);
+  const int cap = fp32 && !layers ? 6144 : 4096;
+  const int nch = (int)std::max<long long>(1, cap / cols);  // chunks that make one round
+  t.kz = (nz + nch - 1) / nch;
+  if (!fp32) {
+    t.ty = 4;
+    t.kz = std::min(t.kz, 8);
+    return t;
+  }
+  t.ty = cols * nz < cap ? 4 : (t.tx == 32 ? 16 : 8);
+  if (t.kz > 16 && nx % 32 != 0) {
+    t.kz = 8;
+  } else if (t.kz > 32 && nch < 4) {
+    t.kz = 32;
+    t.ty = 16;
+  }
+  return t;
+}
+
+// The tiling of an untuned member of a batch, whose members fill the chip together:
+// 64 x 4 tiles, chunks for 2048 workgroups but at least eight planes, and (FP32) the y
+// and z layers in the kernel where they are at most a quarter of the grid.
+Tiling member_tiling(const Geom& g, bool fp32) {
+  const int* n = g.n;
+  const int ntile = ((n[0] + 63) / 64) * ((n[1] + 3) / 4);
+  const int kz = (int)(((long long)n[2] * ntile + 2047) / 2048);
+  const bool thin = (double)(g.nlo[1] + g.nhi[1]) / n[1] +
+                        (double)(g.nlo[2] + g.nhi[2]) / n[2] <= 0.25;
+  return {64, 4, std::max(8, std::min(kz, n[2])), fp32 && thin ? 1 : 0};
+}
+
+Tiling tiling(const mlk_sim* s) {
+  if (s->in_batch && !s->tuned) return s->member;
+  return {s->tx, s->ty, s->kz, s->layer_mode};
+}
+
 Box sweep_box(const mlk_sim* s) {
-  return interior_box(s->g, s->fp32 && s->layer_mode == 1, s->tx);
+  const Tiling t = tiling(s);
+  return interior_box(s->g, s->fp32 && t.layers == 1, t.tx);
 }
 
 // The frame launch can take the y/z layers when the fused box of the other modes
@@ -922,18 +994,19 @@ mlk_status sweep(mlk_sim* s, const SideWork& side) {
   if (s->desc.sweep == MLK_SWEEP_FUSED) {
     const FieldPtrs<T> nf = spare_ptrs<T>(s), fr = sweep_reads<T>(s);
     const Box inner = sweep_box(s);
-    if (f32 && s->layer_mode == 2 && split_ok(s)) {
+    const Tiling tl = tiling(s);
+    if (f32 && tl.layers == 2 && split_ok(s)) {
       // the lean interior, then the layer frame in one launch of the full kernel
       int t0 = mark_begin(s, MLK_PHASE_SWEEP);
-      if constexpr (f32) HIPCHK(sweep_fused_f32(fr, nf, s->g, inner, s->kz, s->tx, s->ty, side, s->stream));
+      if constexpr (f32) HIPCHK(sweep_fused_f32(fr, nf, s->g, inner, tl.kz, tl.tx, tl.ty, side, s->stream));
       mark_end(s, MLK_PHASE_SWEEP, t0);
       t0 = mark_begin(s, MLK_PHASE_SHELL);
       if constexpr (f32) HIPCHK(sweep_frame_f32(fr, nf, s->g, inner, kFrameKz, s->stream));
       mark_end(s, MLK_PHASE_SHELL, t0);
     } else {
       int t0 = mark_begin(s, MLK_PHASE_SWEEP);
-      if constexpr (f32) HIPCHK(sweep_fused_f32(fr, nf, s->g, inner, s->kz, s->tx, s->ty, side, s->stream));
-      else HIPCHK(sweep_fused_f64(fr, nf, s->g, inner, s->kz, s->tx, s->ty, side, s->stream));
+      if constexpr (f32) HIPCHK(sweep_fused_f32(fr, nf, s->g, inner, tl.kz, tl.tx, tl.ty, side, s->stream));
+      else HIPCHK(sweep_fused_f64(fr, nf, s->g, inner, tl.kz, tl.tx, tl.ty, side, s->stream));
       mark_end(s, MLK_PHASE_SWEEP, t0);
       t0 = mark_begin(s, MLK_PHASE_SHELL);
       if constexpr (f32) {
@@ -1332,18 +1405,12 @@ mlk_status mlk_create(const mlk_grid_desc* gd, mlk_sim** out) {
       return bail(fail(MLK_ENOMEM, "field allocation of %zu bytes failed", s->ncell * s->esz));
   }
   {
-    // z planes per workgroup of the fused sweep: enough workgroups to fill the chip
-    const int ntile = ((n[0] + 63) / 64) * ((n[1] + 3) / 4);
-    int kz = (int)(((long long)n[2] * ntile + 2047) / 2048);
-    s->kz = std::max(8, std::min(kz, n[2]));
-  }
-  // FP32: the fused sweep takes the y and z layers when they are a small part of
-  // the grid (on small, layer-heavy grids the plain shell passes are faster);
-  // mlk_autotune measures both
-  {
-    const bool thin = (double)(s->g.nlo[1] + s->g.nhi[1]) / n[1] +
-                          (double)(s->g.nlo[2] + s->g.nhi[2]) / n[2] <= 0.25;
-    s->layer_mode = s->fp32 && thin ? 1 : 0;
+    const Tiling t = default_tiling(s->g, s->fp32);
+    s->tx = t.tx;
+    s->ty = t.ty;
+    s->kz = t.kz;
+    s->layer_mode = t.layers;
+    s->member = member_tiling(s->g, s->fp32);
   }
   if (dalloc(&s->epsinv, s->ncell * s->esz) != hipSuccess)
     return bail(fail(MLK_ENOMEM, "eps allocation failed"));
@@ -2706,11 +2773,12 @@ mlk_status build_tables(mlk_batch* b, BatchTables<T> (&tab)[2]) {
         J.b = nxt;
         J.g = s->g;
         J.box = inner;
-        J.kz = s->kz;
-        J.tx = s->tx;
-        J.ty = s->ty;
+        const Tiling tl = tiling(s);
+        J.kz = tl.kz;
+        J.tx = tl.tx;
+        J.ty = tl.ty;
         fused_job_shape(J);
-        fu[tile_slot(s->tx, s->ty)].push_back(J);
+        fu[tile_slot(tl.tx, tl.ty)].push_back(J);
       }
       ShellJob<T> S{};
       S.in = cur;
@@ -3145,13 +3213,14 @@ mlk_status mlk_set_tuning(mlk_sim* s, int32_t ty, int32_t kz) {
   if (s->in_batch) return fail(MLK_ESTATE, "tune members before forming the batch");
   s->ty = ty;
   s->kz = kz;
+  s->tuned = true;
   return MLK_OK;
 }
 
 mlk_status mlk_get_tuning(mlk_sim* s, int32_t* ty, int32_t* kz) {
   if (!s || !ty || !kz) return fail(MLK_EINVAL, "null argument");
-  *ty = s->ty;
-  *kz = s->kz;
+  *ty = tiling(s).ty;
+  *kz = tiling(s).kz;
   return MLK_OK;
 }
 
@@ -3161,10 +3230,13 @@ mlk_status mlk_set_tile_width(mlk_sim* s, int32_t tx) {
   if (s->in_batch) return fail(MLK_ESTATE, "tune members before forming the batch");
   STCHK(sync_sim(s));
   const int old = s->tx;
+  const bool was = s->tuned;
   s->tx = tx;
+  s->tuned = true;
   // the frame launch needs a fused box over every x column, which depends on the width
   if (s->layer_mode == 2 && !split_ok(s)) {
     s->tx = old;
+    s->tuned = was;
     return fail(MLK_EUNSUPPORTED, "the frame launch needs a fused box spanning every x "
                                   "column, which %d-wide tiles do not give here", tx);
   }
@@ -3173,7 +3245,7 @@ mlk_status mlk_set_tile_width(mlk_sim* s, int32_t tx) {
 
 mlk_status mlk_get_tile_width(mlk_sim* s, int32_t* tx) {
   if (!s || !tx) return fail(MLK_EINVAL, "null argument");
-  *tx = s->tx;
+  *tx = tiling(s).tx;
   return MLK_OK;
 }
 
@@ -3188,12 +3260,13 @@ mlk_status mlk_set_sweep_layers(mlk_sim* s, int32_t on) {
                                   "spanning every x column");
   STCHK(sync_sim(s));
   s->layer_mode = on;
+  s->tuned = true;
   return MLK_OK;
 }
 
 mlk_status mlk_get_sweep_layers(mlk_sim* s, int32_t* on) {
   if (!s || !on) return fail(MLK_EINVAL, "null argument");
-  *on = s->layer_mode;
+  *on = tiling(s).layers;
   return MLK_OK;
 }
 
@@ -3205,6 +3278,7 @@ mlk_status mlk_autotune(mlk_sim* s, const char* cache_path) {
   std::vector<TuneEntry> cache = read_cache(cache_path);
   for (const TuneEntry& e : cache)
     if (e.key == key && valid_entry(e)) {
+      s->tuned = true;
       s->tx = e.tx;
       s->ty = e.ty;
       s->kz = e.kz;
@@ -3213,6 +3287,7 @@ mlk_status mlk_autotune(mlk_sim* s, const char* cache_path) {
     }
   HIPCHK(hipSetDevice(s->desc.device));
   STCHK(sync_sim(s));
+  s->tuned = true;  // the candidates are timed through the sim's own settings
   // candidates: layer mode (FP32: with or without the y and z layers in the
   // fused kernel, or in the frame launch) x tile width x rows per workgroup x
   // planes per workgroup
@@ -3338,6 +3413,7 @@ void set_members(mlk_batch* b, int layers, int tx, int ty, int kz) {
     s->tx = tx;
     s->ty = ty;
     s->kz = kz;
+    s->tuned = true;
   }
 }
 
