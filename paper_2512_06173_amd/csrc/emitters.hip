@@ -87,28 +87,13 @@ __global__ void k_records(int count, const int* lo, const int* len, const T* w, 
   WinRec<T>& r = rec[m];
   for (int d = 0; d < kMaxWin; ++d) {
     const int k = org + d - l;
-    r.wr[a][v][d] = (k >= 0 && k < n) ? wv[k] : T(0);
+    r.wr[a][d][v] = (k >= 0 && k < n) ? wv[k] : T(0);
   }
   if (v == 0) {
     r.org[a] = org;
     r.n[a] = min(end - org, kMaxWin);
   }
-  if (t % 6 == 0) {
-    // largest product of 1-D factors over the three component windows
-    double best = 0.0;
-    for (int c = 0; c < 3; ++c) {
-      double p = 1.0;
-      for (int b = 0; b < 3; ++b) {
-        const int sl = win_slot(m, b, b == c);
-        double mx = 0.0;
-        for (int d = 0; d < len[sl]; ++d) mx = fmax(mx, (double)w[(size_t)sl * kMaxWin + d]);
-        p *= mx;
-      }
-      best = fmax(best, p);
-    }
-    r.wmax = (float)(best * (1.0 + 1e-6));
-    r.pad = 0;
-  }
+  if (t % 6 == 0) r.pad[0] = r.pad[1] = 0;
 }
 
 template <typename T>

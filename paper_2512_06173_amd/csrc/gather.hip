@@ -132,14 +132,14 @@ __device__ __forceinline__ void load_lane_win(const WinRec<T>& r, int i, int j0,
   w.nx = o.w;
   w.ny = nn.x - j0;
   w.nz = nn.y;
-  w.wx0 = r.wr[0][0][i];
-  w.wx1 = r.wr[0][1][i];
+  w.wx0 = r.wr[0][i][0];
+  w.wx1 = r.wr[0][i][1];
 #pragma unroll
   for (int v = 0; v < 2; ++v) {
 #pragma unroll
-    for (int d = 0; d < ROWS; ++d) w.wy[v][d] = r.wr[1][v][j0 + d];
+    for (int d = 0; d < ROWS; ++d) w.wy[v][d] = r.wr[1][j0 + d][v];
 #pragma unroll
-    for (int d = 0; d < kMaxWin; ++d) w.wz[v][d] = r.wr[2][v][d];
+    for (int d = 0; d < kMaxWin; ++d) w.wz[v][d] = r.wr[2][d][v];
   }
 }
 
@@ -165,7 +165,7 @@ __device__ __forceinline__ void tile_body(const FieldPtrs<T>& f, const Geom& g,
   LaneWin<T, RG> w;
   if (q0 + grp < q1) {
     e = bins.gbin_em[q0 + grp];
-    load_lane_win<T, R, WEPS, RG>(win.rec[e], i, j0, x0, y0, z0, w);
+    load_lane_win<T, R, WEPS, RG>(win.rec[q0 + grp], i, j0, x0, y0, z0, w);
   }
   // every wavefront waits for its own units, the barrier for those of the others
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -224,7 +224,7 @@ __device__ __forceinline__ void tile_body(const FieldPtrs<T>& f, const Geom& g,
     q += NG;
     if (q < q1) {
       e = bins.gbin_em[q];
-      load_lane_win<T, R, WEPS, RG>(win.rec[e], i, j0, x0, y0, z0, w);
+      load_lane_win<T, R, WEPS, RG>(win.rec[q], i, j0, x0, y0, z0, w);
     }
   }
 }
@@ -246,11 +246,12 @@ __device__ __forceinline__ void light_body(const FieldPtrs<T>& f, const Geom& g,
   static_assert(kLanesPerEmitter * kMaxWin == 64, "one lane per (x offset, plane)");
   const int lane = threadIdx.x & 63;
   const int i = lane % kLanesPerEmitter, k = lane / kLanesPerEmitter;
-  const int e = __builtin_amdgcn_readfirstlane(bins.gbin_em[bins.glight0 + q]);
+  const int em = __builtin_amdgcn_readfirstlane(bins.glight0 + q);
+  const int e = __builtin_amdgcn_readfirstlane(bins.gbin_em[em]);
 #if defined(__HIP_DEVICE_COMPILE__)
-  const auto& r = ((__attribute__((address_space(4))) const WinRec<T>*)win.rec)[e];
+  const auto& r = ((__attribute__((address_space(4))) const WinRec<T>*)win.rec)[em];
 #else
-  const auto& r = win.rec[e];
+  const auto& r = win.rec[em];
 #endif
   const int nx = r.n[0], nyw = r.n[1], nz = r.n[2];
   T t[H][3];  // the lane's row sums of its plane, per row group and component
@@ -281,7 +282,7 @@ __device__ __forceinline__ void light_body(const FieldPtrs<T>& f, const Geom& g,
     for (int h = 0; h < H; ++h)
 #pragma unroll
       for (int j = 0; j < RG; ++j) {
-        const T wy0 = r.wr[1][0][h * RG + j], wy1 = r.wr[1][1][h * RG + j];
+        const T wy0 = r.wr[1][h * RG + j][0], wy1 = r.wr[1][h * RG + j][1];
         t[h][0] += wy0 * v[h][j][0];
         t[h][1] += wy1 * v[h][j][1];
         t[h][2] += wy0 * v[h][j][2];
@@ -295,7 +296,7 @@ __device__ __forceinline__ void light_body(const FieldPtrs<T>& f, const Geom& g,
 #pragma unroll
   for (int kk = 0; kk < kMaxWin; ++kk) {
     if (kk < nz) {  // uniform across the wavefront
-      const T wz0 = r.wr[2][0][kk], wz1 = r.wr[2][1][kk];
+      const T wz0 = r.wr[2][kk][0], wz1 = r.wr[2][kk][1];
 #pragma unroll
       for (int h = 0; h < H; ++h) {
         const int src = i + kLanesPerEmitter * kk;
@@ -307,7 +308,7 @@ __device__ __forceinline__ void light_body(const FieldPtrs<T>& f, const Geom& g,
   }
   if (i < nx) {
     // Ex sits at half-integer x (variant 1); Ey, Ez at integer x
-    const double wx0 = (double)win.rec[e].wr[0][0][i], wx1 = (double)win.rec[e].wr[0][1][i];
+    const double wx0 = (double)win.rec[em].wr[0][i][0], wx1 = (double)win.rec[em].wr[0][i][1];
 #pragma unroll
     for (int h = 0; h < H; ++h) {
       a[h][0] *= wx1;

@@ -170,16 +170,15 @@ struct SourceSet {
 // normalised 1-D weights w[q*kMaxWin ...].
 // The same window in the form the binned kernels stage in LDS.  Per axis the
 // union of the two position variants starts at org[a] and spans n[a] <= kMaxWin
-// points (the integer points of [r - R sigma - 1/2, r + R sigma]); wr[a][v][d] is
+// points (the integer points of [r - R sigma - 1/2, r + R sigma]); wr[a][d][v] is
 // the weight of variant v at point org[a] + d, zero outside that variant's
 // window, so loops over the union need no bounds checks.
 template <typename T>
 struct alignas(16) WinRec {
   int org[3];
   int n[3];
-  float wmax;  // largest 3-D weight of any component's window
-  int pad;
-  T wr[3][2][kMaxWin];
+  int pad[2];
+  T wr[3][kMaxWin][2];
 };
 
 template <typename T>
@@ -188,7 +187,7 @@ struct WindowPtrs {
   const int* len;
   const T* w;
   const double* gamma;
-  const WinRec<T>* rec;  // [M]
+  const WinRec<T>* rec;  // [M], in the order of gbin_em (see BinPtrs)
 };
 
 __host__ __device__ inline int win_slot(int m, int a, int v) { return m * 6 + 2 * a + v; }
@@ -370,10 +369,9 @@ struct BinPtrs {
   int glight0, nlight;      // gbin_em[glight0 .. glight0 + nlight): the light bins' emitters
   const int* gbin_org;      // [3*ngather] bin origin in unwrapped cells (centre-cell frame)
   const int* gbin_start;    // [ngather+1] CSR into gbin_em
-  const int* gbin_em;       // emitter ids
-  int nscatter;             // scatter bins touched by at least one window
-  const int* sbin_id;       // [nscatter]
-  const int* sbin_start;    // [nscatter+1] CSR into sbin_pair
+  const int* gbin_em;       // emitter ids; the record of gbin_em[q] is rec[q]
+  int nscatter;             // workgroups of the scatter, kScWaves bins each
+  const int4* sbin;         // [kScWaves*nscatter] bin, first and end pair (equal: no bin)
   const int4* sbin_pair;    // one PairDesc per (emitter, bin) pair
 };
 
@@ -393,20 +391,19 @@ __device__ __forceinline__ J load_job(const J* jobs, int j) {
 #endif
 }
 
-// A scatter pair: emitter e and, per axis a, the run of its union window inside
-// the bin: window offsets d0 .. d0+c-1 on the bin-local cells l0 .. l0+c-1, packed
-// as l0 | d0 << 4 | (c-1) << 7 at bit 10a of runs.  gw = |gamma| times the
-// record's wmax, rounded up to FP32 (the per-bin bound of the fixed-point grid).
+// A scatter pair: emitter e, where its record's weights lie (in 16-byte units from the first
+// record), and per axis the offset of its union window in the bin, o = (window offset) -
+// (bin-local cell), as a signed byte at bit 8 a of off.
 struct PairDesc {
   int e;
-  unsigned runs;
-  float gw;
+  int off;
+  unsigned rec;
   int pad;
 };
 static_assert(sizeof(PairDesc) == 16, "a pair is loaded as one int4");
-inline unsigned pack_run(int l0, int d0, int c) {
-  return (unsigned)l0 | (unsigned)d0 << 4 | (unsigned)(c - 1) << 7;
-}
+
+// scatter bins, one per wavefront
+constexpr int kScX = 16, kScY = 4, kScZ = 4, kScWaves = 4;
 
 // ---------------------------------------------------------------- batches
 // A batched launch covers the jobs of several domains: job j owns blocks

@@ -148,7 +148,7 @@ struct mlk_sim {
   int* d_wlo = nullptr;
   int* d_wlen = nullptr;
   void* d_w = nullptr;
-  void* d_rec = nullptr;  // WinRec<T>[M]
+  void* d_rec = nullptr;  // WinRec<T>[M], in the gather's order of the emitters
   double* d_pos = nullptr;
   double* d_sigma = nullptr;
   double* d_gamma = nullptr;
@@ -170,8 +170,7 @@ struct mlk_sim {
   int* d_gbin_org = nullptr;
   int* d_gbin_start = nullptr;
   int* d_gbin_em = nullptr;
-  int* d_sbin_id = nullptr;
-  int* d_sbin_start = nullptr;
+  int4* d_sbin = nullptr;
   PairDesc* d_sbin_pair = nullptr;
   int* d_tls_slot = nullptr;
 
@@ -365,28 +364,36 @@ BinPtrs bin_ptrs(const mlk_sim* s) {
   b.gbin_start = s->d_gbin_start;
   b.gbin_em = s->d_gbin_em;
   b.nscatter = s->nscatter;
-  b.sbin_id = s->d_sbin_id;
-  b.sbin_start = s->d_sbin_start;
+  b.sbin = s->d_sbin;
   b.sbin_pair = reinterpret_cast<const int4*>(s->d_sbin_pair);
   return b;
 }
 
 // Union windows of the emitters as the binned kernels see them: origin and
-// length per axis and the largest 3-D weight, read back from the records.
+// length per axis, read back from the records.
 template <typename T>
-mlk_status read_unions(const mlk_sim* s, std::vector<int>& org, std::vector<int>& n,
-                       std::vector<double>& wmax) {
+mlk_status read_unions(const mlk_sim* s, std::vector<int>& org, std::vector<int>& n) {
   std::vector<WinRec<T>> rec(s->nem);
   if (s->nem > 0)
     HIPCHK(hipMemcpy(rec.data(), s->d_rec, rec.size() * sizeof(WinRec<T>),
                      hipMemcpyDeviceToHost));
-  for (int e = 0; e < s->nem; ++e) {
+  for (int e = 0; e < s->nem; ++e)
     for (int a = 0; a < 3; ++a) {
       org[3 * e + a] = rec[e].org[a];
       n[3 * e + a] = rec[e].n[a];
     }
-    wmax[e] = rec[e].wmax;
-  }
+  return MLK_OK;
+}
+
+// The records in the order em: those of a gather bin, and nearly those of a scatter bin,
+// lie side by side.
+template <typename T>
+mlk_status order_records(mlk_sim* s, const std::vector<int>& em) {
+  if (em.empty()) return MLK_OK;
+  std::vector<WinRec<T>> rec(em.size()), out(em.size());
+  HIPCHK(hipMemcpy(rec.data(), s->d_rec, rec.size() * sizeof(WinRec<T>), hipMemcpyDeviceToHost));
+  for (size_t q = 0; q < em.size(); ++q) out[q] = rec[em[q]];
+  HIPCHK(hipMemcpy(s->d_rec, out.data(), out.size() * sizeof(WinRec<T>), hipMemcpyHostToDevice));
   return MLK_OK;
 }
 
@@ -473,11 +480,10 @@ mlk_status build_bins(mlk_sim* s) {
   // inside a bin only on a periodic axis no longer than the bin, where it gives
   // two runs.
   std::vector<int> worg((size_t)M * 3), wn((size_t)M * 3);
-  std::vector<double> wmax(M);
   if (s->fp32)
-    STCHK(read_unions<float>(s, worg, wn, wmax));
+    STCHK(read_unions<float>(s, worg, wn));
   else
-    STCHK(read_unions<double>(s, worg, wn, wmax));
+    STCHK(read_unions<double>(s, worg, wn));
   for (int a = 0; a < 3; ++a) {
     const int n = g.n[a];
     s->wplane[a].assign(n, 0);
@@ -554,17 +560,13 @@ mlk_status build_bins(mlk_sim* s) {
     runs_of(e, 0, rx);
     runs_of(e, 1, ry);
     runs_of(e, 2, rz);
-    float gw = (float)(std::fabs(s->gamma[e]) * wmax[e]);
-    if ((double)gw < std::fabs(s->gamma[e]) * wmax[e]) gw = std::nextafter(gw, INFINITY);
     for (const Run& z : rz)
       for (const Run& y : ry)
         for (const Run& x : rx) {
-          PairDesc pd;
+          PairDesc pd{};
           pd.e = e;
-          pd.runs = pack_run(x.l0, x.d0, x.c) | pack_run(y.l0, y.d0, y.c) << 10 |
-                    pack_run(z.l0, z.d0, z.c) << 20;
-          pd.gw = gw;
-          pd.pad = 0;
+          pd.off = ((x.d0 - x.l0) & 255) | ((y.d0 - y.l0) & 255) << 8 |
+                   ((z.d0 - z.l0) & 255) << 16;
           per_em[e].push_back({x.bin + nb[0] * (y.bin + nb[1] * z.bin), pd});
         }
   }
@@ -586,59 +588,62 @@ mlk_status build_bins(mlk_sim* s) {
   std::vector<int> fill(sstart.begin(), sstart.end() - 1);
   std::vector<PairDesc> spair(npairs);
   // emitters in gather order, so neighbouring pairs touch neighbouring windows
+  const unsigned rec16 = (s->fp32 ? sizeof(WinRec<float>) : sizeof(WinRec<double>)) / 16;
+  const unsigned w16 = (s->fp32 ? offsetof(WinRec<float>, wr) : offsetof(WinRec<double>, wr)) / 16;
+  if ((size_t)M * rec16 > UINT32_MAX) return fail(MLK_EUNSUPPORTED, "too many emitters");
   for (int q = 0; q < M; ++q)
-    for (const auto& bp : per_em[gem[q]]) spair[fill[slot_of[bp.first]]++] = bp.second;
-  // within a bin, pairs by decreasing numbers of planes (z), then rows (y): the
-  // workgroup runs eight pairs per wavefront side by side, each looping over its
-  // own planes and rows, so equal counts keep its lanes busy (stable: ties stay
-  // in gather order)
-  for (size_t sl = 0; sl < sid.size(); ++sl) {
-    auto rows = [](const PairDesc& p) {
-      return 16 * (int)((p.runs >> 27) & 7) + (int)((p.runs >> 17) & 7);
-    };
-    std::stable_sort(spair.begin() + sstart[sl], spair.begin() + sstart[sl + 1],
-                     [&](const PairDesc& x, const PairDesc& y) { return rows(x) > rows(y); });
-  }
-  // bins heaviest first: a workgroup per bin, two per CU, and the bins along the
-  // emitter region's faces hold few pairs; started first, the heavy bins run side by
-  // side and the light ones fill in behind them instead of sharing rounds with them.
-  // Work of a bin: its pairs' row loops (eight pairs per wavefront) plus the clear
-  // and the owner write, which cost every bin the same.
+    for (const auto& bp : per_em[gem[q]]) {
+      PairDesc& pd = spair[fill[slot_of[bp.first]]++];
+      pd = bp.second;
+      pd.rec = (unsigned)q * rec16 + w16;
+    }
+  // The launch's order of bins, kScWaves to a workgroup.  Workgroups go to the eight XCDs
+  // in turn, and neighbouring bins share records and lines of E, so each XCD takes an
+  // eighth of the bins, neighbours in space; within it the heaviest first (in steps of 32
+  // pairs, so that neighbours stay together), as the light ones then fill in behind them.
+  // Work of a bin: its pairs and, in the same unit, what every bin costs.  Where the eighths
+  // differ by more than a quarter in work, the heaviest of all go first instead.
+  std::vector<int4> sbin;
+  s->swork.clear();
   {
-    const size_t nsl = sid.size();
-    std::vector<double> work(nsl, 0.0);
-    for (size_t sl = 0; sl < nsl; ++sl) {
-      double w = 256.0;  // clear, bound and owner write, in row-loop units
-      for (int q = sstart[sl]; q < sstart[sl + 1]; ++q) {
-        const unsigned ru = spair[q].runs;
-        w += (double)((((ru >> 17) & 7) + 1) * (((ru >> 27) & 7) + 1)) / 8.0 + 1.0;
+    const int nsl = (int)sid.size(), nblk = (nsl + kScWaves - 1) / kScWaves;
+    auto work = [&](int sl) { return sl < 0 ? 0 : 16 + sstart[sl + 1] - sstart[sl]; };
+    std::vector<int> seg[8];
+    double most = 0.0, total = 0.0;
+    for (int x = 0, q = 0; x < 8; ++x) {
+      double w = 0.0;
+      for (const int end = q + kScWaves * (nblk / 8 + (x < nblk % 8)); q < end; ++q) {
+        seg[x].push_back(q < nsl ? q : -1);
+        w += work(seg[x].back());
       }
-      work[sl] = w;
+      most = std::max(most, w);
+      total += w;
     }
-    std::vector<int> order(nsl);
-    for (size_t q = 0; q < nsl; ++q) order[q] = (int)q;
-    std::stable_sort(order.begin(), order.end(),
-                     [&](int x, int y) { return work[x] > work[y]; });
-    std::vector<int> sid2, sstart2(1, 0);
-    std::vector<PairDesc> spair2;
-    spair2.reserve(spair.size());
-    s->swork.clear();
-    for (int sl : order) {
-      s->swork.push_back((float)work[sl]);
-      sid2.push_back(sid[sl]);
-      spair2.insert(spair2.end(), spair.begin() + sstart[sl], spair.begin() + sstart[sl + 1]);
-      sstart2.push_back((int)spair2.size());
+    auto heavier = [&](int x, int y) { return work(x) / 32 > work(y) / 32; };
+    std::vector<int> all;
+    if (most <= 1.25 * total / 8) {
+      for (auto& v : seg) std::stable_sort(v.begin(), v.end(), heavier);
+    } else {
+      for (auto& v : seg) all.insert(all.end(), v.begin(), v.end());
+      std::stable_sort(all.begin(), all.end(), heavier);
     }
-    sid.swap(sid2);
-    sstart.swap(sstart2);
-    spair.swap(spair2);
+    for (int b = 0; b < nblk; ++b) {
+      const int* sl = all.empty() ? &seg[b % 8][kScWaves * (b / 8)] : &all[kScWaves * b];
+      float w = 0.f;
+      for (int k = 0; k < kScWaves; ++k) {
+        sbin.push_back(sl[k] < 0 ? make_int4(0, 0, 0, 0)
+                                 : make_int4(sid[sl[k]], sstart[sl[k]], sstart[sl[k] + 1], 0));
+        w = std::max(w, (float)(work(sl[k]) / 32));
+      }
+      s->swork.push_back(w);
+    }
+    s->nscatter = nblk;
   }
-  s->nscatter = (int)sid.size();
+  STCHK(s->fp32 ? order_records<float>(s, gem) : order_records<double>(s, gem));
   STCHK(upload(&s->d_gbin_org, gorg));
   STCHK(upload(&s->d_gbin_start, gstart));
   STCHK(upload(&s->d_gbin_em, gem));
-  STCHK(upload(&s->d_sbin_id, sid));
-  STCHK(upload(&s->d_sbin_start, sstart));
+  STCHK(upload(&s->d_sbin, sbin));
   STCHK(upload(&s->d_sbin_pair, spair));
   STCHK(upload(&s->d_tls_slot, s->tls_slot));
   return MLK_OK;
@@ -1222,8 +1227,7 @@ void release(mlk_sim* s) {
   dfree(s->d_gbin_org);
   dfree(s->d_gbin_start);
   dfree(s->d_gbin_em);
-  dfree(s->d_sbin_id);
-  dfree(s->d_sbin_start);
+  dfree(s->d_sbin);
   dfree(s->d_sbin_pair);
   dfree(s->d_tls_slot);
   dfree(s->d_probe);
