@@ -42,7 +42,7 @@ namespace {
 template <typename T>
 struct ScatterCfg {
   static constexpr int pairs = sizeof(T) == 4 ? 16 : 8;   // of a chunk
-  static constexpr int waves = sizeof(T) == 4 ? 5 : 4;  // per SIMD
+  static constexpr int waves = sizeof(T) == 4 ? 5 : 3;  // per SIMD
 };
 constexpr int kThreads = 64 * kScWaves;
 
@@ -91,13 +91,13 @@ struct Mfma<double> {
 // the bin or with the axis, whose cells are the only ones written.
 //
 // The wavefronts of a workgroup share nothing and never wait for each other; registers allow
-// five a SIMD (FP32), which hide the trips to memory of each other (ids, then records, then
+// five a SIMD (FP64: three), which hide the trips to memory of each other (ids, then records, then
 // E).  With 50,000 to 100,000 emitters no unit is busy more than a third of the time (cube:
 // VALU 32%, matrix cores 18%, LDS 27%) and the reads and writes of E run at 1 to 4 TB/s: what
 // is left is latency.  Before, a workgroup of eight wavefronts summed a bin of 16 x 16 x 16
 // (8 with FP64) cells with LDS atomics, two or three per cell and emitter.  Kernel times,
 // us a step, before and now: cube 256^3 with 100,000 emitters 59.6 -> 50, 187 x 149 x 163
-// FP64 with 20,000 76 -> 54, 384^3 with 100,000 113 -> 89, 160^3 with 10,000 28 -> 16.7,
+// FP64 with 20,000 76 -> 53, 384^3 with 100,000 113 -> 89, 160^3 with 10,000 28 -> 16.7,
 // 10,000 in 12 planes of 64 x 64 42 -> 23 (few bins then, so the launch lasts as long as a
 // bin), 1,000 in 128^3 10.4 -> 6.1.  Measured and not taken: bins of four wavefronts with
 // their pairs staged together (cube 51, 64 x 64 planes 36); E read at the start (54).
@@ -210,12 +210,34 @@ __device__ __forceinline__ void scatter_body(const FieldPtrs<T>& f, const Geom& 
     }
     order();
   };
+  // FP64: the sums of a chunk are added to those of the chunks before with the rounding
+  // error of the addition kept (Knuth's two-sum), as exact as a wider accumulator: with
+  // 256 emitters around one cell the error of J is 2.2e-16 (rms), 5.6e-16 without; the
+  // registers cost a wavefront per SIMD, not time (54 -> 53 us)
+  constexpr bool kExact = sizeof(T) == 8;
+  typename M::Acc hi[kExact ? 3 : 1], lo[kExact ? 3 : 1];
+  auto fold = [&] {
+    if constexpr (kExact) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const typename M::Acc t = hi[c] + acc[c], b = t - hi[c];
+        lo[c] += (hi[c] - (t - b)) + (acc[c] - b);
+        hi[c] = t;
+        acc[c] = {0, 0, 0, 0};
+      }
+    }
+  };
+  if constexpr (kExact) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) hi[c] = lo[c] = {0, 0, 0, 0};
+  }
   int c0 = q0;
   for (; c0 + P < q1; c0 += P) {
     stage(P);
     load_records();
     if (c0 + 2 * P < q1) load_pairs(c0 + 2 * P);
     sums(P);
+    fold();
   }
   stage(q1 - c0);
   // Lane l holds x = l % 16 and four of the rows (y, z), neighbours along y (FP32) or z
@@ -238,6 +260,11 @@ __device__ __forceinline__ void scatter_body(const FieldPtrs<T>& f, const Geom& 
     if (EPS && f.epsinv && r < nr) ei[r] = f.epsinv[cell + r * step];  // null: eps_r = 1
   }
   sums(q1 - c0);
+  if constexpr (kExact) {
+    fold();
+#pragma unroll
+    for (int c = 0; c < 3; ++c) acc[c] = hi[c] + lo[c];
+  }
   // owner write: E -= [eps^-1] J
 #pragma unroll
   for (int r = 0; r < 4; ++r)
