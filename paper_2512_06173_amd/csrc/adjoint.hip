@@ -27,200 +27,9 @@
 // psib, so it is double-buffered.
 #include "mlk_internal.h"
 #include "launch.h"
-#include "yee_common.h"
+#include "adjoint_cells.h"
 
 namespace mlk {
-
-namespace {
-
-template <typename T>
-struct AdjPtrs {
-  T* E[3];           // adjoint of E
-  T* H[3];           // adjoint of H
-  const T* epsinv;   // null in vacuum (eps_r = 1) for the transposed sweep
-  const T* tab;      // CPML tables (b, c, 1/kappa) of the forward sweep
-  const T* psi_in;   // adjoint of psi (both fields), read
-  T* psi_out;        // adjoint of psi, written
-};
-
-// Adjoint of the plain derivative from w, the adjoint of the stretched one, at
-// (i,j,k) for `field` (0: E, 1: H), component c, derivative axis a; `lay` says
-// whether the position lies in a CPML layer of axis a (q: its coordinate there).
-template <typename T>
-__device__ __forceinline__ T dbar(const Geom& g, const AdjPtrs<T>& p, bool lay, int field, int c,
-                                  int a, int q, int i, int j, int k, T w) {
-  if (!lay) return w;
-  const size_t po = psi_offset(g, field, c, a) + psi_index(g, a, i, j, k);
-  const int n = g.n[a];
-  const T* t = p.tab + tab_offset(g, a) + (size_t)field * n + q;
-  return (t[4 * n] + t[2 * n]) * w + t[2 * n] * p.psi_in[po];
-}
-
-template <typename T>
-__device__ __forceinline__ void psib_update(const Geom& g, const AdjPtrs<T>& p, bool lay,
-                                            int field, int c, int a, int q, int i, int j, int k,
-                                            T w) {
-  if (!lay) return;
-  const size_t po = psi_offset(g, field, c, a) + psi_index(g, a, i, j, k);
-  const int n = g.n[a];
-  const T* t = p.tab + tab_offset(g, a) + (size_t)field * n + q;
-  p.psi_out[po] = t[0] * (w + p.psi_in[po]);
-}
-
-// A cell's neighbour one step along each axis (dir = +1 or -1): linear index,
-// coordinate along the axis, existence (false beyond a non-periodic face) and
-// CPML-layer membership.
-struct Nbrs {
-  size_t id[3];
-  int q[3];
-  bool ok[3], lay[3];
-};
-
-__device__ __forceinline__ Nbrs neighbours(const Geom& g, int i, int j, int k, size_t id, int dir) {
-  const size_t st[3] = {1, (size_t)g.n[0], (size_t)g.n[0] * g.n[1]};
-  const int q0[3] = {i, j, k};
-  Nbrs nb;
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    int q = q0[a] + dir;
-    size_t nid = dir > 0 ? id + st[a] : id - st[a];
-    bool ok = true;
-    if (q < 0 || q >= g.n[a]) {
-      ok = g.periodic[a] != 0;
-      q = q < 0 ? q + g.n[a] : q - g.n[a];
-      nid = dir > 0 ? id - (size_t)(g.n[a] - 1) * st[a] : id + (size_t)(g.n[a] - 1) * st[a];
-    }
-    nb.id[a] = ok ? nid : id;
-    nb.q[a] = q;
-    nb.ok[a] = ok;
-    nb.lay[a] = ok && has_cpml(g, a) && in_layer(g, a, q);
-  }
-  return nb;
-}
-
-// curl terms of component c: derivative axis and component of the other field,
-// with the sign of the term
-constexpr int kAx[3][2] = {{1, 2}, {2, 0}, {0, 1}};
-constexpr int kOt[3][2] = {{2, 1}, {0, 2}, {1, 0}};
-
-}  // namespace
-
-// Cell updates of the transposed step.  Every field load of a thread is issued
-// up front, unconditionally (a missing neighbour reads the cell itself and its
-// term is zeroed afterwards), so the loads are in flight together; only the
-// CPML terms load inside branches.  In place (OOP = false), p holds Eb and Hb;
-// out of place, Eb and Hb are read from p and written to o.
-
-// Transposed E update.  Eb holds the adjoint of E^{n+1}; Hb gains the curl
-// part.  In place, Eb leaves holding that of E^n (identity part, zero on the
-// walls, stored only where a wall zeroes it); out of place the H pass applies
-// the mask.
-template <typename T, bool OOP, bool NT>
-__device__ __forceinline__ void adj_e_cell(const AdjPtrs<T>& p, const AdjPtrs<T>& o,
-                                           const Geom& g, int i, int j, int k) {
-  const size_t id = (size_t)i + (size_t)g.n[0] * ((size_t)j + (size_t)g.n[1] * (size_t)k);
-  const T dt = (T)g.dt, idx = (T)g.inv_dx;
-  const int qo[3] = {i, j, k};
-  const Nbrs nb = neighbours(g, i, j, k, id, +1);
-  T eo[3], hv[3], en[3][3], epn[3];
-#pragma unroll
-  for (int c = 0; c < 3; ++c) eo[c] = p.E[c][id];
-  const T ei = p.epsinv ? p.epsinv[id] : T(1);  // null: eps_r = 1 everywhere
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    epn[a] = p.epsinv ? p.epsinv[nb.id[a]] : T(1);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) en[a][c] = c != a ? p.E[c][nb.id[a]] : T(0);
-  }
-#pragma unroll
-  for (int c = 0; c < 3; ++c) hv[c] = p.H[c][id];
-  // wall planes through this cell (a wall zeroes the tangential E on it)
-  const bool w0 = g.wall[0] && i == 0, w1 = g.wall[1] && j == 0, w2 = g.wall[2] && k == 0;
-  const bool wl[3] = {w0, w1, w2};
-  T u[3];
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    const bool m = (c != 0 && w0) || (c != 1 && w1) || (c != 2 && w2);
-    u[c] = m ? T(0) : eo[c];
-  }
-  T hb[3] = {T(0), T(0), T(0)};
-#pragma unroll
-  for (int c = 0; c < 3; ++c)
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int a = kAx[c][s], h = kOt[c][s];
-      const T sg = s == 0 ? T(1) : T(-1);
-      const bool lay = has_cpml(g, a) && in_layer(g, a, qo[a]);
-      // own stencil: d = (H_h(cell) - H_h(cell - e_a)) / dx
-      const T w = sg * dt * ei * u[c];
-      psib_update(g, p, lay, 0, c, a, qo[a], i, j, k, w);
-      hb[h] += dbar(g, p, lay, 0, c, a, qo[a], i, j, k, w) * idx;
-      // the stencil of the E cell above along a reads H_h(cell) with a minus sign;
-      // that cell shares this cell's planes across the other two axes, so the
-      // walls through it are those of the other axes (no term beyond a face)
-      bool m = false;
-#pragma unroll
-      for (int b = 0; b < 3; ++b) m = m || (b != a && b != c && wl[b]);
-      const T wn = (m || !nb.ok[a]) ? T(0) : sg * dt * epn[a] * en[a][c];
-      const int ii = a == 0 ? nb.q[0] : i, jj = a == 1 ? nb.q[1] : j, kk = a == 2 ? nb.q[2] : k;
-      hb[h] -= dbar(g, p, nb.lay[a], 0, c, a, nb.q[a], ii, jj, kk, wn) * idx;
-    }
-  if (!OOP && (w0 || w1 || w2)) {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) p.E[c][id] = u[c];
-  }
-  const AdjPtrs<T>& d = OOP ? o : p;
-#pragma unroll
-  for (int c = 0; c < 3; ++c) store_field<NT>(&d.H[c][id], hv[c] + hb[c]);
-}
-
-// Transposed H update.  Hb holds the adjoint of H^{n+1/2} (unchanged: identity
-// part); Eb gains the curl part.  Out of place, Hb is read from o (the E pass
-// wrote it there) and Eb from p, masked on the walls.
-template <typename T, bool OOP, bool NT>
-__device__ __forceinline__ void adj_h_cell(const AdjPtrs<T>& p, const AdjPtrs<T>& o,
-                                           const Geom& g, int i, int j, int k) {
-  const size_t id = (size_t)i + (size_t)g.n[0] * ((size_t)j + (size_t)g.n[1] * (size_t)k);
-  const T dt = (T)g.dt, idx = (T)g.inv_dx;
-  const int qo[3] = {i, j, k};
-  const Nbrs nb = neighbours(g, i, j, k, id, -1);
-  const AdjPtrs<T>& hs = OOP ? o : p;
-  T hv[3], hn[3][3], ev[3];
-#pragma unroll
-  for (int h = 0; h < 3; ++h) hv[h] = hs.H[h][id];
-#pragma unroll
-  for (int a = 0; a < 3; ++a)
-#pragma unroll
-    for (int h = 0; h < 3; ++h) hn[a][h] = h != a ? hs.H[h][nb.id[a]] : T(0);
-#pragma unroll
-  for (int c = 0; c < 3; ++c) ev[c] = p.E[c][id];
-  if (OOP) {
-    const bool w0 = g.wall[0] && i == 0, w1 = g.wall[1] && j == 0, w2 = g.wall[2] && k == 0;
-#pragma unroll
-    for (int c = 0; c < 3; ++c)
-      if ((c != 0 && w0) || (c != 1 && w1) || (c != 2 && w2)) ev[c] = T(0);
-  }
-  T eb[3] = {T(0), T(0), T(0)};
-#pragma unroll
-  for (int h = 0; h < 3; ++h)
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int a = kAx[h][s], e = kOt[h][s];
-      const T sg = s == 0 ? T(1) : T(-1);
-      const bool lay = has_cpml(g, a) && in_layer(g, a, qo[a]);
-      // own stencil: d = (E_e(cell + e_a) - E_e(cell)) / dx, H -= dt sg s(d)
-      const T w = -sg * dt * hv[h];
-      psib_update(g, p, lay, 1, h, a, qo[a], i, j, k, w);
-      eb[e] -= dbar(g, p, lay, 1, h, a, qo[a], i, j, k, w) * idx;
-      // the stencil of the H cell below along a reads E_e(cell) with a plus sign
-      const T wn = nb.ok[a] ? -sg * dt * hn[a][h] : T(0);
-      const int ii = a == 0 ? nb.q[0] : i, jj = a == 1 ? nb.q[1] : j, kk = a == 2 ? nb.q[2] : k;
-      eb[e] += dbar(g, p, nb.lay[a], 1, h, a, nb.q[a], ii, jj, kk, wn) * idx;
-    }
-  const AdjPtrs<T>& d = OOP ? o : p;
-#pragma unroll
-  for (int c = 0; c < 3; ++c) store_field<NT>(&d.E[c][id], ev[c] + eb[c]);
-}
 
 // Whole-grid transposed sweep in place: one thread per cell, 64 x 4 cells per
 // workgroup over (x, y), one z plane per grid row.
@@ -243,12 +52,7 @@ __global__ __launch_bounds__(256) void k_adj_H(AdjPtrs<T> p, Geom g) {
 template <typename T, bool E_PASS, bool NT>
 __global__ __launch_bounds__(256) void k_adj_shell(AdjPtrs<T> p, AdjPtrs<T> o, Geom g,
                                                    ShellMap m) {
-  const unsigned t = blockIdx.x * blockDim.x + threadIdx.x;
-  if ((long long)t >= m.total) return;
-  int i, j, k;
-  shell_cell(g, m, t, i, j, k);
-  if (E_PASS) adj_e_cell<T, true, NT>(p, o, g, i, j, k);
-  else adj_h_cell<T, true, NT>(p, o, g, i, j, k);
+  adj_shell_body<T, E_PASS, NT>(p, o, g, m, blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // Flux detector: part 0 adds dt dF/dE^{n+1} and dt dF/dH^{n+1/2}, part 1 adds
@@ -445,27 +249,33 @@ static hipError_t launch_adj_sweep(const AdjSweep<T>& a, const Geom& g, hipStrea
   p.psi_in = a.psi[0];
   p.psi_out = a.psi[1];
   if (a.Eo[0]) {
-    // fused transposed sweep on its box, then the shell cells, out of place
+    // fused transposed sweep on its box, then the shell cells, out of place.  The shell's E
+    // pass shares nothing with the fused box and rides in its launch, unless the tiles
+    // start left of the box (what they compute there is overwritten by the passes).
     const Box box = adj_interior_box(g, sizeof(T) == 4);
-    hipError_t e;
-    if constexpr (sizeof(T) == 4) e = adj_fused_f32(a, g, box, st);
-    else e = adj_fused_f64(a, g, box, st);
-    if (e != hipSuccess) return e;
-    const ShellMap m = shell_map(g, box);
-    if (m.total == 0) return hipSuccess;
-    if (m.total >= 0x7fffff00LL) return hipErrorInvalidValue;  // 32-bit cell index
-    AdjPtrs<T> o = p;
+    AdjShell<T> sh{p, p, shell_map(g, box), 0};
     for (int c = 0; c < 3; ++c) {
-      o.E[c] = a.Eo[c];
-      o.H[c] = a.Ho[c];
+      sh.o.E[c] = a.Eo[c];
+      sh.o.H[c] = a.Ho[c];
     }
+    const ShellMap& m = sh.m;
+    if (m.total >= 0x7fffff00LL) return hipErrorInvalidValue;  // 32-bit cell index
     const unsigned blocks = (unsigned)((m.total + 255) / 256);
+    const bool ride = m.total > 0 && box.lo[0] % 32 == 0 && box.hi[0] > box.lo[0] &&
+                      box.hi[1] > box.lo[1] && box.hi[2] > box.lo[2];
+    if (ride) sh.blocks = (int)blocks;
+    hipError_t e;
+    if constexpr (sizeof(T) == 4) e = adj_fused_f32(a, g, box, sh, st);
+    else e = adj_fused_f64(a, g, box, sh, st);
+    if (e != hipSuccess || m.total == 0) return e;
     auto go = [&](auto kernel) {
-      hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, st, p, o, g, m);
+      hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, st, p, sh.o, g, m);
     };
-    g.stream ? go(k_adj_shell<T, true, true>) : go(k_adj_shell<T, true, false>);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    if (!ride) {
+      g.stream ? go(k_adj_shell<T, true, true>) : go(k_adj_shell<T, true, false>);
+      e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
     g.stream ? go(k_adj_shell<T, false, true>) : go(k_adj_shell<T, false, false>);
     return hipGetLastError();
   }

@@ -29,8 +29,10 @@
 // plane ahead), and its neighbours read them from LDS.  The host takes that box
 // only when no tile's low-x halo column or high-x ring column lies in an x
 // layer, so those stay plain.
-#include "mlk_internal.h"
-#include "yee_common.h"
+#include "adjoint_cells.h"
+#include "launch.h"
+
+#include <algorithm>
 
 namespace mlk {
 
@@ -66,27 +68,35 @@ __device__ __forceinline__ bool wall_masked(const Geom& g, int c, int x, int y, 
          (c != 2 && g.wall[2] && z == 0);
 }
 
+template <typename T, int TY>
+struct AdjTile {
+  static constexpr int EW = 66, EH = TY + 2;  // W plane in LDS: x in [-1, 64], y in [-1, TY]
+  static constexpr int HW = 65, HH = TY + 1;  // Hb' plane in LDS: x in [-1, 63], y in [-1, TY-1]
+  T wL[2][3][EH * EW];
+  T hL[3][HH * HW];
+  T dL[2][HH * EW];  // D of the y and z x-terms, plane k, rows -1..TY-1
+  T gL[2][HH * HW];  // G of the y and z x-terms, rows -1..TY-1
+  T xc[2][3][64];    // x CPML b, c, 1/kappa + c of the tile's columns
+};
+
 }  // namespace
 
+// Planes [k0, k1) of a tile.
 template <typename T, int TY, bool ZL, bool NT>
-__global__ __launch_bounds__(64 * TY) void k_adj_fused(AdjFused<T> p, Geom g, Box box, int kz,
-                                                       int ntx, int nty, int nblocks) {
-  constexpr int EW = 66, EH = TY + 2;   // W plane in LDS: x in [-1, 64], y in [-1, TY]
-  constexpr int HW = 65, HH = TY + 1;   // Hb' plane in LDS: x in [-1, 63], y in [-1, TY-1]
+__device__ __forceinline__ void adj_tile(const AdjFused<T>& p, const Geom& g, const Box& box,
+                                         int tile_x, int tile_y, int k0, int k1,
+                                         AdjTile<T, TY>& lds) {
+  constexpr int EW = AdjTile<T, TY>::EW, HW = AdjTile<T, TY>::HW;
   constexpr int NHALO = 2 * EW + 2 * TY;
   static_assert(64 * TY >= NHALO, "one thread per ring slot of the staged plane");
-  __shared__ T wL[2][3][EH * EW];
-  __shared__ T hL[3][HH * HW];
-  __shared__ T dL[2][HH * EW];  // D of the y and z x-terms, plane k, rows -1..TY-1
-  __shared__ T gL[2][HH * HW];  // G of the y and z x-terms, rows -1..TY-1
-  __shared__ T xc[2][3][64];    // x CPML b, c, 1/kappa + c of the tile's columns
-
-  const int bid = xcd_block(blockIdx.x, nblocks);
-  const int tile_x = bid % ntx, tile_y = (bid / ntx) % nty, chunk = bid / (ntx * nty);
+  auto& wL = lds.wL;
+  auto& hL = lds.hL;
+  auto& dL = lds.dL;
+  auto& gL = lds.gL;
+  auto& xc = lds.xc;
   // x tiles start on a 128-byte boundary at or below the box; cells below
   // box.lo[0] are computed too and overwritten by the shell passes
   const int x0 = (box.lo[0] & ~31) + tile_x * 64, y0 = box.lo[1] + tile_y * TY;
-  const int k0 = box.lo[2] + chunk * kz, k1 = min(k0 + kz, box.hi[2]);
 
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6, tid = threadIdx.x;
   const int i = x0 + tx, j = y0 + ty;
@@ -509,6 +519,39 @@ __global__ __launch_bounds__(64 * TY) void k_adj_fused(AdjFused<T> p, Geom g, Bo
   }
 }
 
+// The launch's workgroups: with ZL, nslab on chunks of kzs planes of the two slabs at the z
+// faces, [box.lo, zlo) (nlo chunks) and [zhi, box.hi); then nmid on chunks of kz planes
+// between them; then the shell's E pass.
+struct AdjCut {
+  int zlo, zhi, kz, kzs, nlo, nslab, nmid, ntx, nty;
+};
+
+template <typename T, int TY, bool ZL, bool NT>
+__global__ __launch_bounds__(64 * TY) void k_adj_fused(AdjFused<T> p, Geom g, Box box, AdjCut cut,
+                                                       AdjShell<T> sh) {
+  __shared__ AdjTile<T, TY> lds;
+  const int b = blockIdx.x;
+  if (b >= cut.nslab + cut.nmid) {
+    adj_shell_body<T, true, NT>(sh.p, sh.o, g, sh.m,
+                                (unsigned)(b - cut.nslab - cut.nmid) * 256u + threadIdx.x);
+    return;
+  }
+  const int cols = cut.ntx * cut.nty;
+  if constexpr (ZL) {
+    if (b < cut.nslab) {
+      const int bid = xcd_block(b, cut.nslab), chunk = bid / cols;
+      const bool low = chunk < cut.nlo;
+      const int k0 = low ? box.lo[2] + chunk * cut.kzs : cut.zhi + (chunk - cut.nlo) * cut.kzs;
+      adj_tile<T, TY, true, NT>(p, g, box, bid % cut.ntx, bid / cut.ntx % cut.nty, k0,
+                                min(k0 + cut.kzs, low ? cut.zlo : box.hi[2]), lds);
+      return;
+    }
+  }
+  const int bid = xcd_block(b - cut.nslab, cut.nmid), k0 = cut.zlo + bid / cols * cut.kz;
+  adj_tile<T, TY, false, NT>(p, g, box, bid % cut.ntx, bid / cut.ntx % cut.nty, k0,
+                             min(k0 + cut.kz, cut.zhi), lds);
+}
+
 // Box of the fused transposed sweep: per axis, one cell of margin above the low
 // CPML layers and one below the high layers (none on an axis without layers on
 // that side).
@@ -536,30 +579,14 @@ Box adj_interior_box(const Geom& g, bool zl) {
   return b;
 }
 
-template <typename T, bool ZL>
-static hipError_t launch_adj_box(const AdjFused<T>& p, const Geom& g, const Box& box, int kz,
-                                 hipStream_t st) {
-  constexpr int TY = 4;
-  const int ex = box.hi[0] - box.lo[0], ey = box.hi[1] - box.lo[1], ez = box.hi[2] - box.lo[2];
-  if (ex <= 0 || ey <= 0 || ez <= 0) return hipSuccess;
-  const int ntx = (box.hi[0] - (box.lo[0] & ~31) + 63) / 64, nty = (ey + TY - 1) / TY;
-  const int nblocks = ntx * nty * ((ez + kz - 1) / kz);
-  auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(64 * TY), 0, st, p, g, box, kz, ntx, nty,
-                       nblocks);
-  };
-  g.stream ? go(k_adj_fused<T, TY, ZL, true>) : go(k_adj_fused<T, TY, ZL, false>);
-  return hipGetLastError();
-}
-
 // The box of adj_interior_box.  When it spans every z plane of a grid with z
 // layers, the chunks whose planes (and the planes just outside them) keep clear
 // of the layers run without the z-layer terms, and the two slabs at the z faces
-// with them.
+// with them, in one launch.
 template <typename T>
 static hipError_t launch_adj_fused(const AdjSweep<T>& a, const Geom& g, const Box& box,
-                                   hipStream_t st) {
-  const int kz = a.kz > 0 ? a.kz : 16;
+                                   const AdjShell<T>& sh, hipStream_t st) {
+  constexpr int TY = 4;
   AdjFused<T> p{};
   for (int c = 0; c < 3; ++c) {
     p.E[c] = a.E[c];
@@ -571,33 +598,53 @@ static hipError_t launch_adj_fused(const AdjSweep<T>& a, const Geom& g, const Bo
   p.tab = a.tab;
   p.psi_in = a.psi[0];
   p.psi_out = a.psi[1];
-  if (!(sizeof(T) == 4 && has_cpml(g, 2) && box.lo[2] == 0 && box.hi[2] == g.n[2]))
-    return launch_adj_box<T, false>(p, g, box, kz, st);
-  const int zlo = g.nlo[2] > 0 ? g.nlo[2] + 1 : 0;
-  const int zhi = g.nhi[2] > 0 ? g.n[2] - g.nhi[2] - 1 : g.n[2];
-  if (zlo >= zhi) return launch_adj_box<T, true>(p, g, box, kz, st);
-  Box mid = box, lo = box, hi = box;
-  mid.lo[2] = zlo;
-  mid.hi[2] = zhi;
-  lo.hi[2] = zlo;
-  hi.lo[2] = zhi;
-  // a face slab is a few planes deep: short chunks give it enough workgroups
-  // (measured at 256^3, CPML 10: 16-plane chunks 41 us per slab, 4-plane ones
-  // less than half of that)
-  const int kzs = kz < 4 ? kz : 4;
-  hipError_t e = launch_adj_box<T, false>(p, g, mid, kz, st);
-  if (e == hipSuccess) e = launch_adj_box<T, true>(p, g, lo, kzs, st);
-  if (e == hipSuccess) e = launch_adj_box<T, true>(p, g, hi, kzs, st);
-  return e;
+  const int ex = box.hi[0] - box.lo[0], ey = box.hi[1] - box.lo[1], ez = box.hi[2] - box.lo[2];
+  if (ex <= 0 || ey <= 0 || ez <= 0) return hipSuccess;
+  AdjCut c{};
+  c.ntx = (box.hi[0] - (box.lo[0] & ~31) + 63) / 64;
+  c.nty = (ey + TY - 1) / TY;
+  c.zlo = box.lo[2];
+  c.zhi = box.hi[2];
+  const bool zl = sizeof(T) == 4 && has_cpml(g, 2) && box.lo[2] == 0 && box.hi[2] == g.n[2];
+  if (zl) {
+    c.zlo = g.nlo[2] > 0 ? g.nlo[2] + 1 : 0;
+    c.zhi = g.nhi[2] > 0 ? g.n[2] - g.nhi[2] - 1 : g.n[2];
+    if (c.zlo >= c.zhi) c.zlo = c.zhi = g.n[2];  // layers all through
+  }
+  // Chunks that make about one round of the chip (three workgroups per CU, FP64 two), of
+  // 2 to 16 planes: the first plane of a chunk is computed twice, but on a grid that
+  // leaves CUs idle a shorter march counts for more.  A face slab is a few planes deep and
+  // takes chunks of at most four.  112 x 104 x 120, CPML 10, a reverse step: box, two
+  // slabs and the shell's E pass 83 us in launches of their own with chunks of 16 planes,
+  // 30 in one with chunks of 9 (31 to 33 with chunks of 6 to 3).
+  const int cols = c.ntx * c.nty, slots = 256 * (sizeof(T) == 4 ? 3 : 2);
+  const int kmax = a.kz > 0 ? a.kz : 16;
+  c.kzs = std::min(kmax, 4);
+  const int chunks_lo = (c.zlo - box.lo[2] + c.kzs - 1) / c.kzs;
+  const int chunks_hi = (box.hi[2] - c.zhi + c.kzs - 1) / c.kzs;
+  const int nch = std::max(1, slots / cols - chunks_lo - chunks_hi);
+  c.kz = std::min(kmax, std::max(2, (c.zhi - c.zlo + nch - 1) / nch));
+  c.nlo = chunks_lo;
+  c.nslab = cols * (chunks_lo + chunks_hi);
+  c.nmid = cols * ((c.zhi - c.zlo + c.kz - 1) / c.kz);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(c.nslab + c.nmid + sh.blocks), dim3(64 * TY), 0, st, p, g, box,
+                       c, sh);
+  };
+  if (zl)
+    g.stream ? go(k_adj_fused<T, TY, true, true>) : go(k_adj_fused<T, TY, true, false>);
+  else
+    g.stream ? go(k_adj_fused<T, TY, false, true>) : go(k_adj_fused<T, TY, false, false>);
+  return hipGetLastError();
 }
 
 hipError_t adj_fused_f32(const AdjSweep<float>& a, const Geom& g, const Box& box,
-                         hipStream_t st) {
-  return launch_adj_fused<float>(a, g, box, st);
+                         const AdjShell<float>& sh, hipStream_t st) {
+  return launch_adj_fused<float>(a, g, box, sh, st);
 }
 hipError_t adj_fused_f64(const AdjSweep<double>& a, const Geom& g, const Box& box,
-                         hipStream_t st) {
-  return launch_adj_fused<double>(a, g, box, st);
+                         const AdjShell<double>& sh, hipStream_t st) {
+  return launch_adj_fused<double>(a, g, box, sh, st);
 }
 
 }  // namespace mlk

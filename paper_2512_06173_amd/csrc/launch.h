@@ -165,10 +165,12 @@ hipError_t scatter_plain_f32(const FieldPtrs<float>& f, const Geom& g, const Bin
                              const WindowPtrs<float>& win, const double* amp, double amp0,
                              hipStream_t st);
 Box adj_interior_box(const Geom& g, bool zl);
+template <typename T>
+struct AdjShell;
 hipError_t adj_fused_f64(const AdjSweep<double>& a, const Geom& g, const Box& box,
-                         hipStream_t st);
+                         const AdjShell<double>& sh, hipStream_t st);
 hipError_t adj_fused_f32(const AdjSweep<float>& a, const Geom& g, const Box& box,
-                         hipStream_t st);
+                         const AdjShell<float>& sh, hipStream_t st);
 hipError_t adj_sweep_f64(const AdjSweep<double>& a, const Geom& g, hipStream_t st);
 hipError_t adj_sweep_f32(const AdjSweep<float>& a, const Geom& g, hipStream_t st);
 hipError_t adj_flux_f64(const AdjSweep<double>& a, const Geom& g, int axis, int index,
