@@ -8,7 +8,7 @@
 // One step over dt (Strang splitting, second order):
 //   dephase(dt/2): rho_ab *= exp(-gphi dt/2) for a != b   (exact for this dissipator)
 //   unitary:       rho <- U rho U^+, U = exp(-i H_eff dt) = C - i S,
-//                  C = Q cos(L dt) Q^T, S = Q sin(L dt) Q^T from H_eff = Q L Q^T
+//                  C = cos(H_eff dt), S = sin(H_eff dt) (see ml_math.h)
 //   dephase(dt/2)
 // then mu_dot^c = Tr(rho_dot mu^c) (eq. dipole_derivative) at the new state.  For
 // this model the trace has a closed form (with rho = R + i I):
@@ -24,8 +24,9 @@
 // a lone wavefront per SIMD (10,000 emitters are 159 wavefronts for 1024 SIMDs), so
 // the groups of a mixed ensemble run side by side in one launch, the longest first,
 // instead of one launch after another: 10,000 emitters of 2 to 6 levels took
-// 25.6 + 17.5 + 11.6 + 7.2 + 4.9 us in five launches with the textbook rotation angle
-// (ml_math.h), 10,000-emitter Bragg step 187 -> 137 us with both changes.
+// 25.6 + 17.5 + 11.6 + 7.2 + 4.9 us in five launches with eigenvectors from Jacobi
+// rotations, 15.7 in one with the rotations' angles free of divisions, 11.8 with the
+// cosine and sine from matrix products (ml_math.h).
 #include "ml_math.h"
 
 namespace mlk {
@@ -33,9 +34,9 @@ namespace mlk {
 // Mixed ensembles of at most this many wavefronts take one launch.  It runs one
 // wavefront per SIMD (the registers of six levels); separate launches give the small
 // level counts more, which could only tell where a level count fills the chip by
-// itself.  Measured, separate against one launch, a cavity step with 1,000, 10,000,
-// 50,000, 200,000 and 500,000 emitters of 2 to 6 levels: 66.8, 65.3, 79.9, 97.2, 218.9
-// against 44.1, 42.9, 56.5, 76.0, 190.6 us.
+// itself.  Measured, separate against one launch, a step of 64^3 cells with 1,000,
+// 10,000, 50,000 and 200,000 emitters of 2 to 6 levels: 49.2, 52.9, 79.7, 168.5 against
+// 31.0, 34.8, 61.9, 151.0 us.
 constexpr int kMlOneLaunchBlocks = 8192;
 
 template <int N>
