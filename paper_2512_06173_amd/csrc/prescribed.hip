@@ -2,13 +2,15 @@
 // grid and no back-action.  No emitter sees another one, so a launch carries each
 // emitter through many steps with its parameters and state in registers: per step
 // only the field is read (or evaluated) and, when asked for, the state recorded.
-// 50 steps of 20,000 two-level and 3,000 multilevel emitters under a pulse: 0.38 ms
-// (7.5 us a step, the six-level emitters' instruction stream), against 3.5 ms with the
-// field, the two-level step and five multilevel steps launched at every step.
+// 50 steps of 20,000 two-level and 3,000 multilevel emitters under a pulse: 0.34 ms
+// (the six-level emitters' instruction stream), against 3.5 ms with the field, the
+// two-level step and five multilevel steps launched at every step.
 //
 // Two-level emitters: one thread each, bound by the latency of its sine and cosine
 // chain.  Multilevel emitters: one thread each (ml_math.h), every level count in one
-// launch, the longest first.
+// launch, the longest first.  When every wavefront of both kinds gets a SIMD of its own,
+// the two-level emitters ride in that launch (its registers leave one wavefront a SIMD,
+// which is too few for more): 36 us of the 50 steps above.
 #include <algorithm>
 
 #include "launch.h"
@@ -37,11 +39,9 @@ __device__ __forceinline__ void field_of(const PrescribedField& f, double dt, in
   }
 }
 
-__global__ __launch_bounds__(64) void k_prescribed_tls(TlsPtrs tls, double dt, PrescribedField f,
-                                                       int nsteps, double* last, double* mudot,
-                                                       double* out, Series ser,
-                                                       const int64_t* step) {
-  const int m = blockIdx.x * 64 + threadIdx.x;
+__device__ __forceinline__ void tls_run(const TlsPtrs& tls, double dt, const PrescribedField& f,
+                                        int nsteps, double* last, double* mudot, double* out,
+                                        const Series& ser, const int64_t* step, int m) {
   if (m >= tls.count) return;
   const int e = tls.gid[m];
   const double w0 = tls.omega0[m];
@@ -64,6 +64,13 @@ __global__ __launch_bounds__(64) void k_prescribed_tls(TlsPtrs tls, double dt, P
     mudot[3 * e + c] = md[c];
     last[3 * e + c] = et[c];
   }
+}
+
+__global__ __launch_bounds__(64) void k_prescribed_tls(TlsPtrs tls, double dt, PrescribedField f,
+                                                       int nsteps, double* last, double* mudot,
+                                                       double* out, Series ser,
+                                                       const int64_t* step) {
+  tls_run(tls, dt, f, nsteps, last, mudot, out, ser, step, blockIdx.x * 64 + threadIdx.x);
 }
 
 template <int N>
@@ -89,11 +96,16 @@ __device__ __forceinline__ void ml_run(const MlDev& ml, int first, int count, do
   }
 }
 
-__global__ __launch_bounds__(64) void k_prescribed_ml(MlDev ml, MlLevels lv, double dt,
-                                                      PrescribedField f, int nsteps, double* last,
-                                                      double* mudot, Series ser,
-                                                      const int64_t* step) {
+// The blocks from nml on take the two-level emitters.
+__global__ __launch_bounds__(64) void k_prescribed_ml(MlDev ml, MlLevels lv, int nml, TlsPtrs tls,
+                                                      double dt, PrescribedField f, int nsteps,
+                                                      double* last, double* mudot, double* out,
+                                                      Series ser, const int64_t* step) {
   const int b = blockIdx.x;
+  if (b >= nml) {
+    tls_run(tls, dt, f, nsteps, last, mudot, out, ser, step, (b - nml) * 64 + (int)threadIdx.x);
+    return;
+  }
 #define MLK_LEVEL(N)                                                                       \
   ml_run<N>(ml, lv.first[N], lv.count[N], dt, f, nsteps, last, mudot, ser, step,           \
             (b - lv.start[N]) * 64 + (int)threadIdx.x)
@@ -110,20 +122,23 @@ __global__ __launch_bounds__(64) void k_prescribed_ml(MlDev ml, MlLevels lv, dou
 // Steps per launch: enough that the launch itself no longer counts, few enough that a
 // launch ends within some ten milliseconds.
 constexpr int kPrescribedSteps = 256;
+constexpr int kSimds = 1024;
 
 hipError_t prescribed_steps(const TlsPtrs& tls, const MlDev& ml, const int* range, double dt,
                             PrescribedField f, int64_t nsteps, double* last, double* mudot,
                             double* out, const Series& ser, const int64_t* step, hipStream_t st) {
   int total = 0;
   const MlLevels lv = ml_levels(range, &total);
+  const int ntls = (tls.count + 63) / 64;
+  const int ride = total > 0 && total + ntls <= kSimds ? ntls : 0;
   for (int64_t c0 = 0; c0 < nsteps; c0 += kPrescribedSteps) {
     const int k = (int)std::min<int64_t>(kPrescribedSteps, nsteps - c0);
-    if (tls.count > 0)
-      hipLaunchKernelGGL(k_prescribed_tls, dim3((tls.count + 63) / 64), dim3(64), 0, st, tls, dt, f,
-                         k, last, mudot, out, ser, step);
+    if (ntls > ride)
+      hipLaunchKernelGGL(k_prescribed_tls, dim3(ntls), dim3(64), 0, st, tls, dt, f, k, last, mudot,
+                         out, ser, step);
     if (total > 0)
-      hipLaunchKernelGGL(k_prescribed_ml, dim3(total), dim3(64), 0, st, ml, lv, dt, f, k, last,
-                         mudot, ser, step);
+      hipLaunchKernelGGL(k_prescribed_ml, dim3(total + ride), dim3(64), 0, st, ml, lv, total, tls,
+                         dt, f, k, last, mudot, out, ser, step);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     f.q0 += k;
