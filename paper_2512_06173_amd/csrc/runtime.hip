@@ -963,21 +963,33 @@ bool split_ok(const mlk_sim* s) {
   return b.lo[0] == 0 && b.hi[0] == s->g.n[0];
 }
 
+// Whether the shell's H pass rides in the fused launch: there is a shell, and no tile
+// starts left of the box (what it computes there is overwritten by the passes).
+bool shell_rides(const Box& inner, const ShellMap& m) {
+  return m.total > 0 && m.total < 0x7fffff00LL && inner.lo[0] == 0;
+}
+
 // The fused launch over the sim's box and the passes for the cells outside it:
-// the frame launch (layer mode 2) or the two plain shell passes.
+// the frame launch (layer mode 2) or the plain shell passes, the first of them in the
+// fused launch where it can be.
 template <typename T>
 hipError_t sweep_passes(const mlk_sim* s, const FieldPtrs<T>& a, const FieldPtrs<T>& ar,
                         const FieldPtrs<T>& b, const Box& inner, int kz, int tx, int ty) {
   hipError_t e = hipSuccess;
+  const bool frame = sizeof(T) == 4 && s->layer_mode == 2 && split_ok(s);
+  SideWork side{};
+  const ShellMap m = shell_map(s->g, inner);
+  const bool ride = !frame && shell_rides(inner, m);
+  if (ride) side.shell = m;
   if constexpr (sizeof(T) == 4) {
-    e = sweep_fused_f32(ar, b, s->g, inner, kz, tx, ty, SideWork{}, s->stream);
-    if (e == hipSuccess && s->layer_mode == 2 && split_ok(s))
+    e = sweep_fused_f32(ar, b, s->g, inner, kz, tx, ty, side, s->stream);
+    if (e == hipSuccess && frame)
       return sweep_frame_f32(ar, b, s->g, inner, kFrameKz, s->stream);
-    if (e == hipSuccess) e = sweep_shell_f32(a, b, s->g, inner, true, s->stream);
+    if (e == hipSuccess && !ride) e = sweep_shell_f32(a, b, s->g, inner, true, s->stream);
     if (e == hipSuccess) e = sweep_shell_f32(a, b, s->g, inner, false, s->stream);
   } else {
-    e = sweep_fused_f64(ar, b, s->g, inner, kz, tx, ty, SideWork{}, s->stream);
-    if (e == hipSuccess) e = sweep_shell_f64(a, b, s->g, inner, true, s->stream);
+    e = sweep_fused_f64(ar, b, s->g, inner, kz, tx, ty, side, s->stream);
+    if (e == hipSuccess && !ride) e = sweep_shell_f64(a, b, s->g, inner, true, s->stream);
     if (e == hipSuccess) e = sweep_shell_f64(a, b, s->g, inner, false, s->stream);
   }
   return e;
@@ -993,7 +1005,7 @@ FieldPtrs<T> sweep_reads(const mlk_sim* s) {
 
 // side: work for extra workgroups of the fused launch
 template <typename T>
-mlk_status sweep(mlk_sim* s, const SideWork& side) {
+mlk_status sweep(mlk_sim* s, SideWork side) {
   constexpr bool f32 = sizeof(T) == 4;
   const FieldPtrs<T> f = field_ptrs<T>(s);
   if (s->desc.sweep == MLK_SWEEP_FUSED) {
@@ -1009,16 +1021,21 @@ mlk_status sweep(mlk_sim* s, const SideWork& side) {
       if constexpr (f32) HIPCHK(sweep_frame_f32(fr, nf, s->g, inner, kFrameKz, s->stream));
       mark_end(s, MLK_PHASE_SHELL, t0);
     } else {
+      // (timed phases enclose their own launches)
+      const ShellMap m = shell_map(s->g, inner);
+      const bool ride = shell_rides(inner, m) &&
+                        !(s->timing & (1 << MLK_PHASE_SWEEP | 1 << MLK_PHASE_SHELL));
+      if (ride) side.shell = m;
       int t0 = mark_begin(s, MLK_PHASE_SWEEP);
       if constexpr (f32) HIPCHK(sweep_fused_f32(fr, nf, s->g, inner, tl.kz, tl.tx, tl.ty, side, s->stream));
       else HIPCHK(sweep_fused_f64(fr, nf, s->g, inner, tl.kz, tl.tx, tl.ty, side, s->stream));
       mark_end(s, MLK_PHASE_SWEEP, t0);
       t0 = mark_begin(s, MLK_PHASE_SHELL);
       if constexpr (f32) {
-        HIPCHK(sweep_shell_f32(f, nf, s->g, inner, true, s->stream));
+        if (!ride) HIPCHK(sweep_shell_f32(f, nf, s->g, inner, true, s->stream));
         HIPCHK(sweep_shell_f32(f, nf, s->g, inner, false, s->stream));
       } else {
-        HIPCHK(sweep_shell_f64(f, nf, s->g, inner, true, s->stream));
+        if (!ride) HIPCHK(sweep_shell_f64(f, nf, s->g, inner, true, s->stream));
         HIPCHK(sweep_shell_f64(f, nf, s->g, inner, false, s->stream));
       }
       mark_end(s, MLK_PHASE_SHELL, t0);

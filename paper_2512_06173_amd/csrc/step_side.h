@@ -4,6 +4,7 @@
 #pragma once
 
 #include "tls_math.h"
+#include "yee_cells.h"
 
 namespace mlk {
 
@@ -69,8 +70,10 @@ __device__ __forceinline__ void finish_body(const FieldPtrs<T>& f, const Geom& g
 }
 
 // Extra workgroups of the fused sweep's launch at step n, behind the sweep's own: they
-// fill in where its first workgroups end.  They touch nothing that the sweep writes: the two-level step works on E~ and the emitter
-// states, and step n - 1 is closed from the fields that the sweep of step n reads.
+// fill in where its first workgroups end.  They touch nothing that the sweep writes, and it
+// reads nothing of theirs: the two-level step works on E~ and the emitter states, step n - 1
+// is closed from the fields that the sweep of step n reads, and the shell's H pass reads
+// those too and writes cells outside the box.
 struct SideWork {
   int blocks;      // workgroups in all (0: none)
   int tls_blocks;  // of these, the first run the two-level step
@@ -83,21 +86,29 @@ struct SideWork {
   FluxPlane fp;
   int64_t n;
   int64_t* step;
+  ShellMap shell;    // H pass over the cells outside the fused box (total 0: none)
 };
 
-template <typename T, int NT>
-__device__ __forceinline__ void side_body(const SideWork& w, const FieldPtrs<T>& f, const Geom& g,
-                                          int b) {
+template <typename T, int NT, bool STREAM>
+__device__ __forceinline__ void side_body(const SideWork& w, const FieldPtrs<T>& f,
+                                          const FieldPtrs<T>& out, const Geom& g, int b) {
   if (b < w.tls_blocks)
     tls_body(w.tls, g.dt, w.Et, w.mudot, w.pop_off, w.ser, w.n, b * NT + (int)threadIdx.x);
-  else if (w.finish)
+  else if (b < w.tls_blocks + w.finish)
     finish_body(f, g, w.fp, w.ser, w.n - 1, w.step, NT);
+  else {
+    const unsigned t = (unsigned)(b - w.tls_blocks - w.finish) * NT + threadIdx.x;
+    if ((long long)t >= w.shell.total) return;
+    int i, j, k;
+    shell_cell(g, w.shell, t, i, j, k);
+    update_h_cell<STREAM>(f, out, g, i, j, k);
+  }
 }
 
 // Workgroup counts of the side work for nt-thread workgroups.
 inline void side_blocks(SideWork& w, int nt) {
   w.tls_blocks = (w.tls.count + nt - 1) / nt;
-  w.blocks = w.tls_blocks + w.finish;
+  w.blocks = w.tls_blocks + w.finish + (int)((w.shell.total + nt - 1) / nt);
 }
 
 }  // namespace mlk

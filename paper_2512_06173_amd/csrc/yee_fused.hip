@@ -569,7 +569,7 @@ __global__ __launch_bounds__(TX * TY, 4) void k_fused(FieldPtrs<T> a, FieldPtrs<
                                                    Box box, int kz, int ntx, int nty,
                                                    int nblocks, SideWork side) {
   if ((int)blockIdx.x >= nblocks) {  // uniform across the workgroup
-    side_body<T, TX * TY>(side, a, g, (int)blockIdx.x - nblocks);
+    side_body<T, TX * TY, NT>(side, a, b, g, (int)blockIdx.x - nblocks);
     return;
   }
   fused_body<T, TX, TY, 2, NT>(a, b, g, box, kz, ntx, nty, nblocks, blockIdx.x);
@@ -582,7 +582,7 @@ __global__ __launch_bounds__(TX * TY, W) void k_fused_lean(FieldPtrs<T> a, Field
                                                         Box box, int kz, int ntx, int nty,
                                                         int nblocks, SideWork side) {
   if ((int)blockIdx.x >= nblocks) {  // uniform across the workgroup
-    side_body<T, TX * TY>(side, a, g, (int)blockIdx.x - nblocks);
+    side_body<T, TX * TY, NT>(side, a, b, g, (int)blockIdx.x - nblocks);
     return;
   }
   fused_body<T, TX, TY, CPM, NT>(a, b, g, box, kz, ntx, nty, nblocks, blockIdx.x);

@@ -11,79 +11,9 @@
 // in == out they update in place, which is how the plain sweep runs on the whole
 // grid.  The fused sweep uses them, out of place, on the CPML shell: the cells
 // outside its interior box, enumerated compactly by one launch per pass.
-#include "mlk_internal.h"
-#include "yee_common.h"
+#include "yee_cells.h"
 
 namespace mlk {
-
-// H^{n+1/2} at cell (i,j,k) from E^n of `in`.
-template <bool NT, typename T>
-__device__ __forceinline__ void update_h_cell(const FieldPtrs<T>& in, const FieldPtrs<T>& out,
-                                              const Geom& g, int i, int j, int k) {
-  // products are not contracted into fused multiply-adds, as in the fused sweep,
-  // so that every way of splitting the grid between the two rounds alike
-#pragma clang fp contract(off)
-  const size_t sx = 1, sy = (size_t)g.n[0], sz = (size_t)g.n[0] * g.n[1];
-  const size_t id = cell_index(g, i, j, k);
-  const T idx = (T)g.inv_dx;
-  const T ex = in.E[0][id], ey = in.E[1][id], ez = in.E[2][id];
-  T dEz_dy = (fwd(in.E[2], id, j, g.n[1], g.periodic[1], sy) - ez) * idx;
-  T dEy_dz = (fwd(in.E[1], id, k, g.n[2], g.periodic[2], sz) - ey) * idx;
-  T dEx_dz = (fwd(in.E[0], id, k, g.n[2], g.periodic[2], sz) - ex) * idx;
-  T dEz_dx = (fwd(in.E[2], id, i, g.n[0], g.periodic[0], sx) - ez) * idx;
-  T dEy_dx = (fwd(in.E[1], id, i, g.n[0], g.periodic[0], sx) - ey) * idx;
-  T dEx_dy = (fwd(in.E[0], id, j, g.n[1], g.periodic[1], sy) - ex) * idx;
-  dEz_dy = stretch(g, in.tab, in.psi, out.psi, 1, 0, 1, i, j, k, dEz_dy);
-  dEy_dz = stretch(g, in.tab, in.psi, out.psi, 1, 0, 2, i, j, k, dEy_dz);
-  dEx_dz = stretch(g, in.tab, in.psi, out.psi, 1, 1, 2, i, j, k, dEx_dz);
-  dEz_dx = stretch(g, in.tab, in.psi, out.psi, 1, 1, 0, i, j, k, dEz_dx);
-  dEy_dx = stretch(g, in.tab, in.psi, out.psi, 1, 2, 0, i, j, k, dEy_dx);
-  dEx_dy = stretch(g, in.tab, in.psi, out.psi, 1, 2, 1, i, j, k, dEx_dy);
-  const T dt = (T)g.dt;
-  const T h0 = in.H[0][id] - dt * (dEz_dy - dEy_dz);
-  const T h1 = in.H[1][id] - dt * (dEx_dz - dEz_dx);
-  const T h2 = in.H[2][id] - dt * (dEy_dx - dEx_dy);
-  store_field<NT>(&out.H[0][id], h0);
-  store_field<NT>(&out.H[1][id], h1);
-  store_field<NT>(&out.H[2][id], h2);
-}
-
-// E^{n+1} at cell (i,j,k); H^{n+1/2} is read from `out` (already advanced
-// everywhere), E^n from `in`.
-template <bool NT, typename T>
-__device__ __forceinline__ void update_e_cell(const FieldPtrs<T>& in, const FieldPtrs<T>& out,
-                                              const Geom& g, int i, int j, int k) {
-  // products are not contracted into fused multiply-adds, as in the fused sweep,
-  // so that every way of splitting the grid between the two rounds alike
-#pragma clang fp contract(off)
-  const size_t sx = 1, sy = (size_t)g.n[0], sz = (size_t)g.n[0] * g.n[1];
-  const size_t id = cell_index(g, i, j, k);
-  const T idx = (T)g.inv_dx;
-  const T hx = out.H[0][id], hy = out.H[1][id], hz = out.H[2][id];
-  T dHz_dy = (hz - bwd(out.H[2], id, j, g.n[1], g.periodic[1], sy)) * idx;
-  T dHy_dz = (hy - bwd(out.H[1], id, k, g.n[2], g.periodic[2], sz)) * idx;
-  T dHx_dz = (hx - bwd(out.H[0], id, k, g.n[2], g.periodic[2], sz)) * idx;
-  T dHz_dx = (hz - bwd(out.H[2], id, i, g.n[0], g.periodic[0], sx)) * idx;
-  T dHy_dx = (hy - bwd(out.H[1], id, i, g.n[0], g.periodic[0], sx)) * idx;
-  T dHx_dy = (hx - bwd(out.H[0], id, j, g.n[1], g.periodic[1], sy)) * idx;
-  dHz_dy = stretch(g, in.tab, in.psi, out.psi, 0, 0, 1, i, j, k, dHz_dy);
-  dHy_dz = stretch(g, in.tab, in.psi, out.psi, 0, 0, 2, i, j, k, dHy_dz);
-  dHx_dz = stretch(g, in.tab, in.psi, out.psi, 0, 1, 2, i, j, k, dHx_dz);
-  dHz_dx = stretch(g, in.tab, in.psi, out.psi, 0, 1, 0, i, j, k, dHz_dx);
-  dHy_dx = stretch(g, in.tab, in.psi, out.psi, 0, 2, 0, i, j, k, dHy_dx);
-  dHx_dy = stretch(g, in.tab, in.psi, out.psi, 0, 2, 1, i, j, k, dHx_dy);
-  const T ce = (T)g.dt * in.epsinv[id];
-  const T e0 = in.E[0][id], e1 = in.E[1][id], e2 = in.E[2][id];
-  const T cx = dHz_dy - dHy_dz;
-  const T cy = dHx_dz - dHz_dx;
-  const T cz = dHy_dx - dHx_dy;
-  const T n0 = tangential_wall(g, 0, i, j, k) ? T(0) : e0 + ce * cx;
-  const T n1 = tangential_wall(g, 1, i, j, k) ? T(0) : e1 + ce * cy;
-  const T n2 = tangential_wall(g, 2, i, j, k) ? T(0) : e2 + ce * cz;
-  store_field<NT>(&out.E[0][id], n0);
-  store_field<NT>(&out.E[1][id], n1);
-  store_field<NT>(&out.E[2][id], n2);
-}
 
 template <typename T, bool H, bool NT>
 __global__ __launch_bounds__(256) void k_update_box(FieldPtrs<T> in, FieldPtrs<T> out, Geom g,
