@@ -23,16 +23,17 @@ __device__ __forceinline__ void update_h_cell(const FieldPtrs<T>& in, const Fiel
   T dEz_dx = (fwd(in.E[2], id, i, g.n[0], g.periodic[0], sx) - ez) * idx;
   T dEy_dx = (fwd(in.E[1], id, i, g.n[0], g.periodic[0], sx) - ey) * idx;
   T dEx_dy = (fwd(in.E[0], id, j, g.n[1], g.periodic[1], sy) - ex) * idx;
-  dEz_dy = stretch(g, in.tab, in.psi, out.psi, 1, 0, 1, i, j, k, dEz_dy);
-  dEy_dz = stretch(g, in.tab, in.psi, out.psi, 1, 0, 2, i, j, k, dEy_dz);
-  dEx_dz = stretch(g, in.tab, in.psi, out.psi, 1, 1, 2, i, j, k, dEx_dz);
-  dEz_dx = stretch(g, in.tab, in.psi, out.psi, 1, 1, 0, i, j, k, dEz_dx);
-  dEy_dx = stretch(g, in.tab, in.psi, out.psi, 1, 2, 0, i, j, k, dEy_dx);
-  dEx_dy = stretch(g, in.tab, in.psi, out.psi, 1, 2, 1, i, j, k, dEx_dy);
+  const T o0 = in.H[0][id], o1 = in.H[1][id], o2 = in.H[2][id];
+  const auto lx = layer_load(g, in.tab, in.psi, 1, 1, 2, 0, i, j, k);
+  const auto ly = layer_load(g, in.tab, in.psi, 1, 0, 2, 1, i, j, k);
+  const auto lz = layer_load(g, in.tab, in.psi, 1, 0, 1, 2, i, j, k);
+  layer_apply(lx, out.psi, dEz_dx, dEy_dx);
+  layer_apply(ly, out.psi, dEz_dy, dEx_dy);
+  layer_apply(lz, out.psi, dEy_dz, dEx_dz);
   const T dt = (T)g.dt;
-  const T h0 = in.H[0][id] - dt * (dEz_dy - dEy_dz);
-  const T h1 = in.H[1][id] - dt * (dEx_dz - dEz_dx);
-  const T h2 = in.H[2][id] - dt * (dEy_dx - dEx_dy);
+  const T h0 = o0 - dt * (dEz_dy - dEy_dz);
+  const T h1 = o1 - dt * (dEx_dz - dEz_dx);
+  const T h2 = o2 - dt * (dEy_dx - dEx_dy);
   store_field<NT>(&out.H[0][id], h0);
   store_field<NT>(&out.H[1][id], h1);
   store_field<NT>(&out.H[2][id], h2);
@@ -56,14 +57,14 @@ __device__ __forceinline__ void update_e_cell(const FieldPtrs<T>& in, const Fiel
   T dHz_dx = (hz - bwd(out.H[2], id, i, g.n[0], g.periodic[0], sx)) * idx;
   T dHy_dx = (hy - bwd(out.H[1], id, i, g.n[0], g.periodic[0], sx)) * idx;
   T dHx_dy = (hx - bwd(out.H[0], id, j, g.n[1], g.periodic[1], sy)) * idx;
-  dHz_dy = stretch(g, in.tab, in.psi, out.psi, 0, 0, 1, i, j, k, dHz_dy);
-  dHy_dz = stretch(g, in.tab, in.psi, out.psi, 0, 0, 2, i, j, k, dHy_dz);
-  dHx_dz = stretch(g, in.tab, in.psi, out.psi, 0, 1, 2, i, j, k, dHx_dz);
-  dHz_dx = stretch(g, in.tab, in.psi, out.psi, 0, 1, 0, i, j, k, dHz_dx);
-  dHy_dx = stretch(g, in.tab, in.psi, out.psi, 0, 2, 0, i, j, k, dHy_dx);
-  dHx_dy = stretch(g, in.tab, in.psi, out.psi, 0, 2, 1, i, j, k, dHx_dy);
   const T ce = (T)g.dt * in.epsinv[id];
   const T e0 = in.E[0][id], e1 = in.E[1][id], e2 = in.E[2][id];
+  const auto lx = layer_load(g, in.tab, in.psi, 0, 1, 2, 0, i, j, k);
+  const auto ly = layer_load(g, in.tab, in.psi, 0, 0, 2, 1, i, j, k);
+  const auto lz = layer_load(g, in.tab, in.psi, 0, 0, 1, 2, i, j, k);
+  layer_apply(lx, out.psi, dHz_dx, dHy_dx);
+  layer_apply(ly, out.psi, dHz_dy, dHx_dy);
+  layer_apply(lz, out.psi, dHy_dz, dHx_dz);
   const T cx = dHz_dy - dHy_dz;
   const T cy = dHx_dz - dHz_dx;
   const T cz = dHy_dx - dHx_dy;

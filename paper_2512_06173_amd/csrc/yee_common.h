@@ -28,25 +28,46 @@ __device__ __forceinline__ T bwd(const T* a, size_t id, int q, int n, int period
   return (in || periodic) ? v : T(0);
 }
 
-// Convolutional PML stretching of a derivative d taken along axis a, at the
-// positions of `field` (0: E, integer positions along a; 1: H, half-integer)
-// for component c:  psi <- b psi + c d ;  d <- d / kappa + psi  (inside the
-// layers only).  psi is read from `in` and, if `out` is set, the new value is
-// stored there (the fused sweep reads one buffer and writes the other; halo
-// recomputations store nothing).
+// Convolutional PML stretching of a cell's two derivatives along axis a, those of
+// components c0 and c1 at the positions of `field` (0: E, integer positions along a; 1: H,
+// half-integer): inside the layers psi <- b psi + c d ;  d <- d / kappa + psi.  Loading and
+// applying are apart, so that a cell issues every load before it waits for the first.
 template <typename T>
-__device__ __forceinline__ T stretch(const Geom& g, const T* tab, const T* in, T* out, int field,
-                                     int c, int a, int i, int j, int k, T d) {
-#pragma clang fp contract(off)  // see the cell updates
-  if (!has_cpml(g, a)) return d;
+struct LayerTerm {
+  bool on;
+  T b, c, ik, p0, p1;
+  size_t o0, o1;
+};
+template <typename T>
+__device__ __forceinline__ LayerTerm<T> layer_load(const Geom& g, const T* tab, const T* psi,
+                                                   int field, int c0, int c1, int a, int i, int j,
+                                                   int k) {
+  LayerTerm<T> l{};
   const int q = a == 0 ? i : (a == 1 ? j : k);
-  if (!in_layer(g, a, q)) return d;
-  const size_t po = psi_offset(g, field, c, a) + psi_index(g, a, i, j, k);
-  const int n = g.n[a];
-  const T* t = tab + tab_offset(g, a) + (size_t)field * n + q;
-  const T p = t[0] * in[po] + t[2 * n] * d;
-  if (out) out[po] = p;
-  return t[4 * n] * d + p;
+  l.on = has_cpml(g, a) && in_layer(g, a, q);
+  if (l.on) {
+    const size_t x = psi_index(g, a, i, j, k);
+    l.o0 = psi_offset(g, field, c0, a) + x;
+    l.o1 = psi_offset(g, field, c1, a) + x;
+    const int n = g.n[a];
+    const T* t = tab + tab_offset(g, a) + (size_t)field * n + q;
+    l.b = t[0];
+    l.c = t[2 * n];
+    l.ik = t[4 * n];
+    l.p0 = psi[l.o0];
+    l.p1 = psi[l.o1];
+  }
+  return l;
+}
+template <typename T>
+__device__ __forceinline__ void layer_apply(const LayerTerm<T>& l, T* psi_out, T& d0, T& d1) {
+#pragma clang fp contract(off)  // see the cell updates
+  if (!l.on) return;
+  const T p0 = l.b * l.p0 + l.c * d0, p1 = l.b * l.p1 + l.c * d1;
+  psi_out[l.o0] = p0;
+  psi_out[l.o1] = p1;
+  d0 = l.ik * d0 + p0;
+  d1 = l.ik * d1 + p1;
 }
 
 // True when E component c at (i,j,k) lies on a metallic wall plane (index 0
