@@ -16,29 +16,21 @@ struct AdjPtrs {
   T* psi_out;        // adjoint of psi, written
 };
 
-// Adjoint of the plain derivative from w, the adjoint of the stretched one, at
-// (i,j,k) for `field` (0: E, 1: H), component c, derivative axis a; `lay` says
-// whether the position lies in a CPML layer of axis a (q: its coordinate there).
+// Adjoint of the plain derivative of component c along the axis of l from w, the adjoint of
+// the stretched one (l.p0 and l.p1 belong to the axis's lower and higher other component).
 template <typename T>
-__device__ __forceinline__ T dbar(const Geom& g, const AdjPtrs<T>& p, bool lay, int field, int c,
-                                  int a, int q, int i, int j, int k, T w) {
-  if (!lay) return w;
-  const size_t po = psi_offset(g, field, c, a) + psi_index(g, a, i, j, k);
-  const int n = g.n[a];
-  const T* t = p.tab + tab_offset(g, a) + (size_t)field * n + q;
-  return (t[4 * n] + t[2 * n]) * w + t[2 * n] * p.psi_in[po];
+__device__ __forceinline__ T dbar(const LayerTerm<T>& l, bool first, T w) {
+  return l.on ? (l.ik + l.c) * w + l.c * (first ? l.p0 : l.p1) : w;
 }
 
 template <typename T>
-__device__ __forceinline__ void psib_update(const Geom& g, const AdjPtrs<T>& p, bool lay,
-                                            int field, int c, int a, int q, int i, int j, int k,
-                                            T w) {
-  if (!lay) return;
-  const size_t po = psi_offset(g, field, c, a) + psi_index(g, a, i, j, k);
-  const int n = g.n[a];
-  const T* t = p.tab + tab_offset(g, a) + (size_t)field * n + q;
-  p.psi_out[po] = t[0] * (w + p.psi_in[po]);
+__device__ __forceinline__ void psib_update(const LayerTerm<T>& l, bool first, T* psi_out, T w) {
+  if (l.on) psi_out[first ? l.o0 : l.o1] = l.b * (w + (first ? l.p0 : l.p1));
 }
+
+// The two components other than axis a, and whether c is the lower of them.
+__device__ __forceinline__ constexpr int other0(int a) { return a == 0 ? 1 : 0; }
+__device__ __forceinline__ constexpr int other1(int a) { return a == 2 ? 1 : 2; }
 
 // A cell's neighbour one step along each axis (dir = +1 or -1): linear index,
 // coordinate along the axis, existence (false beyond a non-periodic face) and
@@ -76,10 +68,26 @@ __device__ __forceinline__ Nbrs neighbours(const Geom& g, int i, int j, int k, s
 constexpr int kAx[3][2] = {{1, 2}, {2, 0}, {0, 1}};
 constexpr int kOt[3][2] = {{2, 1}, {0, 2}, {1, 0}};
 
+// The psi adjoint and coefficients of a cell's and its neighbours' derivatives of `field`,
+// per axis.
+template <typename T>
+__device__ __forceinline__ void layers_load(const Geom& g, const AdjPtrs<T>& p, int field, int i,
+                                            int j, int k, const Nbrs& nb, LayerTerm<T> (&own)[3],
+                                            LayerTerm<T> (&nbr)[3]) {
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    own[a] = layer_load(g, p.tab, p.psi_in, field, other0(a), other1(a), a, i, j, k);
+    nbr[a] = LayerTerm<T>{};
+    if (nb.lay[a])
+      nbr[a] = layer_load(g, p.tab, p.psi_in, field, other0(a), other1(a), a,
+                          a == 0 ? nb.q[0] : i, a == 1 ? nb.q[1] : j, a == 2 ? nb.q[2] : k);
+  }
+}
+
 // Cell updates of the transposed step.  Every field load of a thread is issued
 // up front, unconditionally (a missing neighbour reads the cell itself and its
-// term is zeroed afterwards), so the loads are in flight together; only the
-// CPML terms load inside branches.  In place (OOP = false), p holds Eb and Hb;
+// term is zeroed afterwards), and those of the CPML terms after them, so the loads are
+// in flight together.  In place (OOP = false), p holds Eb and Hb;
 // out of place, Eb and Hb are read from p and written to o.
 
 // Transposed E update.  Eb holds the adjoint of E^{n+1}; Hb gains the curl
@@ -91,7 +99,6 @@ __device__ __forceinline__ void adj_e_cell(const AdjPtrs<T>& p, const AdjPtrs<T>
                                            const Geom& g, int i, int j, int k) {
   const size_t id = (size_t)i + (size_t)g.n[0] * ((size_t)j + (size_t)g.n[1] * (size_t)k);
   const T dt = (T)g.dt, idx = (T)g.inv_dx;
-  const int qo[3] = {i, j, k};
   const Nbrs nb = neighbours(g, i, j, k, id, +1);
   T eo[3], hv[3], en[3][3], epn[3];
 #pragma unroll
@@ -105,6 +112,8 @@ __device__ __forceinline__ void adj_e_cell(const AdjPtrs<T>& p, const AdjPtrs<T>
   }
 #pragma unroll
   for (int c = 0; c < 3; ++c) hv[c] = p.H[c][id];
+  LayerTerm<T> own[3], nbr[3];
+  layers_load(g, p, 0, i, j, k, nb, own, nbr);
   // wall planes through this cell (a wall zeroes the tangential E on it)
   const bool w0 = g.wall[0] && i == 0, w1 = g.wall[1] && j == 0, w2 = g.wall[2] && k == 0;
   const bool wl[3] = {w0, w1, w2};
@@ -121,11 +130,11 @@ __device__ __forceinline__ void adj_e_cell(const AdjPtrs<T>& p, const AdjPtrs<T>
     for (int s = 0; s < 2; ++s) {
       const int a = kAx[c][s], h = kOt[c][s];
       const T sg = s == 0 ? T(1) : T(-1);
-      const bool lay = has_cpml(g, a) && in_layer(g, a, qo[a]);
+      const bool first = c == other0(a);
       // own stencil: d = (H_h(cell) - H_h(cell - e_a)) / dx
       const T w = sg * dt * ei * u[c];
-      psib_update(g, p, lay, 0, c, a, qo[a], i, j, k, w);
-      hb[h] += dbar(g, p, lay, 0, c, a, qo[a], i, j, k, w) * idx;
+      psib_update(own[a], first, p.psi_out, w);
+      hb[h] += dbar(own[a], first, w) * idx;
       // the stencil of the E cell above along a reads H_h(cell) with a minus sign;
       // that cell shares this cell's planes across the other two axes, so the
       // walls through it are those of the other axes (no term beyond a face)
@@ -133,8 +142,7 @@ __device__ __forceinline__ void adj_e_cell(const AdjPtrs<T>& p, const AdjPtrs<T>
 #pragma unroll
       for (int b = 0; b < 3; ++b) m = m || (b != a && b != c && wl[b]);
       const T wn = (m || !nb.ok[a]) ? T(0) : sg * dt * epn[a] * en[a][c];
-      const int ii = a == 0 ? nb.q[0] : i, jj = a == 1 ? nb.q[1] : j, kk = a == 2 ? nb.q[2] : k;
-      hb[h] -= dbar(g, p, nb.lay[a], 0, c, a, nb.q[a], ii, jj, kk, wn) * idx;
+      hb[h] -= dbar(nbr[a], first, wn) * idx;
     }
   if (!OOP && (w0 || w1 || w2)) {
 #pragma unroll
@@ -153,7 +161,6 @@ __device__ __forceinline__ void adj_h_cell(const AdjPtrs<T>& p, const AdjPtrs<T>
                                            const Geom& g, int i, int j, int k) {
   const size_t id = (size_t)i + (size_t)g.n[0] * ((size_t)j + (size_t)g.n[1] * (size_t)k);
   const T dt = (T)g.dt, idx = (T)g.inv_dx;
-  const int qo[3] = {i, j, k};
   const Nbrs nb = neighbours(g, i, j, k, id, -1);
   const AdjPtrs<T>& hs = OOP ? o : p;
   T hv[3], hn[3][3], ev[3];
@@ -165,6 +172,8 @@ __device__ __forceinline__ void adj_h_cell(const AdjPtrs<T>& p, const AdjPtrs<T>
     for (int h = 0; h < 3; ++h) hn[a][h] = h != a ? hs.H[h][nb.id[a]] : T(0);
 #pragma unroll
   for (int c = 0; c < 3; ++c) ev[c] = p.E[c][id];
+  LayerTerm<T> own[3], nbr[3];
+  layers_load(g, p, 1, i, j, k, nb, own, nbr);
   if (OOP) {
     const bool w0 = g.wall[0] && i == 0, w1 = g.wall[1] && j == 0, w2 = g.wall[2] && k == 0;
 #pragma unroll
@@ -178,15 +187,14 @@ __device__ __forceinline__ void adj_h_cell(const AdjPtrs<T>& p, const AdjPtrs<T>
     for (int s = 0; s < 2; ++s) {
       const int a = kAx[h][s], e = kOt[h][s];
       const T sg = s == 0 ? T(1) : T(-1);
-      const bool lay = has_cpml(g, a) && in_layer(g, a, qo[a]);
+      const bool first = h == other0(a);
       // own stencil: d = (E_e(cell + e_a) - E_e(cell)) / dx, H -= dt sg s(d)
       const T w = -sg * dt * hv[h];
-      psib_update(g, p, lay, 1, h, a, qo[a], i, j, k, w);
-      eb[e] -= dbar(g, p, lay, 1, h, a, qo[a], i, j, k, w) * idx;
+      psib_update(own[a], first, p.psi_out, w);
+      eb[e] -= dbar(own[a], first, w) * idx;
       // the stencil of the H cell below along a reads E_e(cell) with a plus sign
       const T wn = nb.ok[a] ? -sg * dt * hn[a][h] : T(0);
-      const int ii = a == 0 ? nb.q[0] : i, jj = a == 1 ? nb.q[1] : j, kk = a == 2 ? nb.q[2] : k;
-      eb[e] += dbar(g, p, nb.lay[a], 1, h, a, nb.q[a], ii, jj, kk, wn) * idx;
+      eb[e] += dbar(nbr[a], first, wn) * idx;
     }
   const AdjPtrs<T>& d = OOP ? o : p;
 #pragma unroll
