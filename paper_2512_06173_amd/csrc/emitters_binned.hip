@@ -102,13 +102,13 @@ struct Mfma<double> {
 // bin), 1,000 in 128^3 10.4 -> 6.1.  Measured and not taken: bins of four wavefronts with
 // their pairs staged together (cube 51, 64 x 64 planes 36); E read at the start (54).
 //
-// Blocks from bins.nscatter on (when fp is given) form the flux partials of the plane
-// instead, in the LDS of the weights.
+// Blocks from bins.nscatter on (when more is given) form the flux partials of the plane, in
+// the LDS of the weights, and then the soft sources.
 template <typename T, bool EPS = true>
 __device__ __forceinline__ void scatter_body(const FieldPtrs<T>& f, const Geom& g,
                                              const BinPtrs& bins, const WindowPtrs<T>& win,
                                              const double* mudot, double amp0, int bid,
-                                             const FluxPlane* fp = nullptr) {
+                                             const ScatterMore* more = nullptr) {
   typedef T T2 __attribute__((ext_vector_type(2)));
   typedef int piece_t __attribute__((ext_vector_type(4)));
   using M = Mfma<T>;
@@ -122,10 +122,17 @@ __device__ __forceinline__ void scatter_body(const FieldPtrs<T>& f, const Geom& 
   __shared__ alignas(16) T2 sWin[kScWaves][P * kStride];
   __shared__ alignas(16) T sAmp[kScWaves][P][4];
   __shared__ int sOff[kScWaves][P];
-  if (fp && bid >= bins.nscatter) {  // uniform across the block
+  if (more && bid >= bins.nscatter) {  // uniform across the block
     static_assert(sizeof(sWin) >= 256 * sizeof(double) && kThreads == 256, "the flux sums");
-    flux_partial_sum(f, g, *fp, bid - bins.nscatter, fp->nblocks,
-                     reinterpret_cast<double*>(&sWin[0][0]));
+    int b = bid - bins.nscatter;
+    const int nflux = more->flux ? more->fp.nblocks : 0;
+    if (b < nflux) {
+      flux_partial_sum(f, g, more->fp, b, nflux, reinterpret_cast<double*>(&sWin[0][0]));
+    } else {
+      b -= nflux;
+      const int q = b / more->sblocks;
+      source_body(f, g, more->src.s[q], more->step, (b - q * more->sblocks) * 256 + threadIdx.x);
+    }
     return;
   }
   const int lane = threadIdx.x & 63;
@@ -279,11 +286,12 @@ __global__ __launch_bounds__(kThreads, ScatterCfg<T>::waves) void k_scatter_bins
   scatter_body(f, g, bins, win, mudot, g.dt * g.inv_dx * g.inv_dx * g.inv_dx, blockIdx.x);
 }
 
-// The scatter with the flux partials of the plane in fp.nblocks more workgroups.
+// The scatter with the flux partials and the soft sources in more workgroups.
 template <typename T>
-__global__ __launch_bounds__(kThreads, ScatterCfg<T>::waves) void k_scatter_flux(
-    FieldPtrs<T> f, Geom g, BinPtrs bins, WindowPtrs<T> win, const double* mudot, FluxPlane fp) {
-  scatter_body(f, g, bins, win, mudot, g.dt * g.inv_dx * g.inv_dx * g.inv_dx, blockIdx.x, &fp);
+__global__ __launch_bounds__(kThreads, ScatterCfg<T>::waves) void k_scatter_more(
+    FieldPtrs<T> f, Geom g, BinPtrs bins, WindowPtrs<T> win, const double* mudot,
+    ScatterMore more) {
+  scatter_body(f, g, bins, win, mudot, g.dt * g.inv_dx * g.inv_dx * g.inv_dx, blockIdx.x, &more);
 }
 
 template <typename T>
@@ -315,11 +323,14 @@ hipError_t tls_step(const TlsPtrs& tls, double dt, const double* Et, double* mud
 template <typename T>
 static hipError_t launch_scatter(const FieldPtrs<T>& f, const Geom& g, const BinPtrs& b,
                                  const WindowPtrs<T>& win, const double* mudot,
-                                 const FluxPlane* fp, hipStream_t st) {
+                                 ScatterMore more, hipStream_t st) {
   if (b.nscatter <= 0) return hipSuccess;
-  if (fp && fp->on && fp->nblocks > 0)
-    hipLaunchKernelGGL(k_scatter_flux<T>, dim3(b.nscatter + fp->nblocks), dim3(kThreads), 0, st,
-                       f, g, b, win, mudot, *fp);
+  more.flux = more.flux && more.fp.on && more.fp.nblocks > 0;
+  more.sblocks = source_blocks(g, more.src);
+  const int nmore = (more.flux ? more.fp.nblocks : 0) + more.src.count * more.sblocks;
+  if (nmore > 0)
+    hipLaunchKernelGGL(k_scatter_more<T>, dim3(b.nscatter + nmore), dim3(kThreads), 0, st, f, g, b,
+                       win, mudot, more);
   else
     hipLaunchKernelGGL(k_scatter_bins<T>, dim3(b.nscatter), dim3(kThreads), 0, st, f, g, b, win,
                        mudot);
@@ -328,13 +339,13 @@ static hipError_t launch_scatter(const FieldPtrs<T>& f, const Geom& g, const Bin
 
 hipError_t bin_scatter_f64(const FieldPtrs<double>& f, const Geom& g, const BinPtrs& b,
                            const WindowPtrs<double>& win, const double* mudot,
-                           const FluxPlane* fp, hipStream_t st) {
-  return launch_scatter<double>(f, g, b, win, mudot, fp, st);
+                           const ScatterMore& more, hipStream_t st) {
+  return launch_scatter<double>(f, g, b, win, mudot, more, st);
 }
 hipError_t bin_scatter_f32(const FieldPtrs<float>& f, const Geom& g, const BinPtrs& b,
                            const WindowPtrs<float>& win, const double* mudot,
-                           const FluxPlane* fp, hipStream_t st) {
-  return launch_scatter<float>(f, g, b, win, mudot, fp, st);
+                           const ScatterMore& more, hipStream_t st) {
+  return launch_scatter<float>(f, g, b, win, mudot, more, st);
 }
 
 template <typename T>

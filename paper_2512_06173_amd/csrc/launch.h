@@ -97,10 +97,10 @@ hipError_t tls_step(const TlsPtrs& tls, double dt, const double* Et, double* mud
 // partials of the plane (no window may reach the plane's E cells)
 hipError_t bin_scatter_f64(const FieldPtrs<double>& f, const Geom& g, const BinPtrs& b,
                            const WindowPtrs<double>& win, const double* mudot,
-                           const FluxPlane* fp, hipStream_t st);
+                           const ScatterMore& more, hipStream_t st);
 hipError_t bin_scatter_f32(const FieldPtrs<float>& f, const Geom& g, const BinPtrs& b,
                            const WindowPtrs<float>& win, const double* mudot,
-                           const FluxPlane* fp, hipStream_t st);
+                           const ScatterMore& more, hipStream_t st);
 // bin edge lengths (cells) of the gather (G) and scatter (S) bins for a field precision
 void bin_shape(bool fp32, int G[3], int S[3]);
 void gather_bin_shape(bool fp32, int G[3]);

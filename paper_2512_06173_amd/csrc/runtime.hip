@@ -1003,9 +1003,9 @@ FieldPtrs<T> sweep_reads(const mlk_sim* s) {
   return f;
 }
 
-// side: work for extra workgroups of the fused launch
+// side: work for extra workgroups of the fused launch; sources: whether to add the sources
 template <typename T>
-mlk_status sweep(mlk_sim* s, SideWork side) {
+mlk_status sweep(mlk_sim* s, SideWork side, bool sources) {
   constexpr bool f32 = sizeof(T) == 4;
   const FieldPtrs<T> f = field_ptrs<T>(s);
   if (s->desc.sweep == MLK_SWEEP_FUSED) {
@@ -1052,7 +1052,7 @@ mlk_status sweep(mlk_sim* s, SideWork side) {
     else HIPCHK(sweep_plain_f64(f, f, s->g, &all, 1, true, true, s->stream));
     mark_end(s, MLK_PHASE_SWEEP, t0);
   }
-  if (s->src.count > 0) {
+  if (sources && s->src.count > 0) {
     const FieldPtrs<T> cur = field_ptrs<T>(s);
     const int t0 = mark_begin(s, MLK_PHASE_SOURCES);
     if constexpr (f32) HIPCHK(sources_f32(cur, s->g, s->src, s->d_step, s->stream));
@@ -1079,7 +1079,30 @@ mlk_status enqueue_steps(mlk_sim* s, int64_t nsteps) {
   const bool fold_flux = binned && s->fp.on && s->npole == 0 && s->nscatter > 0 &&
                          (int)s->wplane[s->fp.axis].size() == s->g.n[s->fp.axis] &&
                          !s->wplane[s->fp.axis][s->fp.index];
-  const FluxPlane* fpart = fold_flux ? &s->fp : nullptr;
+  // The scatter launch takes the soft sources too when no window reaches their cells and
+  // the flux partials, if they are formed there, read none of them.
+  bool fold_src = binned && s->nscatter > 0 && s->src.count > 0 &&
+                  !(s->timing & (1 << MLK_PHASE_SOURCES | 1 << MLK_PHASE_SCATTER));
+  for (int q = 0; q < s->src.count && fold_src; ++q) {
+    const Source& o = s->src.s[q];
+    auto reached = [&](int a, int p) {
+      return (int)s->wplane[a].size() != s->g.n[a] || s->wplane[a][p] != 0;
+    };
+    auto on_flux = [&](int a, int p) { return a == s->fp.axis && p == s->fp.index; };
+    if (o.kind == 0)
+      fold_src = !reached(o.axis, o.index) &&
+                 !(fold_flux && (o.axis != s->fp.axis || on_flux(o.axis, o.index)));
+    else
+      fold_src = !(reached(0, o.ijk[0]) && reached(1, o.ijk[1]) && reached(2, o.ijk[2])) &&
+                 !(fold_flux && on_flux(s->fp.axis, o.ijk[s->fp.axis]));
+  }
+  ScatterMore more{};
+  if (fold_flux) {
+    more.flux = 1;
+    more.fp = s->fp;
+  }
+  if (fold_src) more.src = s->src;
+  more.step = s->d_step;
   // The fused sweep's launch also takes the two-level steps (the scatter after it needs
   // them, the sweep does not) and closes the step before; the last step of the call is
   // closed by a launch of its own.  Kernels take the step number by value, as the
@@ -1127,7 +1150,7 @@ mlk_status enqueue_steps(mlk_sim* s, int64_t nsteps) {
       else HIPCHK(pole_pre_f64(s->pole[k], f, s->g, s->stream));
     }
     mark_end(s, MLK_PHASE_POLES, t0);
-    STCHK(sweep<T>(s, side));
+    STCHK(sweep<T>(s, side, !fold_src));
     f = field_ptrs<T>(s);
     if (s->er.every > 0) {
       // W^n: E^n and H^{n-1/2} are in the spare buffers now, H^{n+1/2} in the current
@@ -1142,9 +1165,9 @@ mlk_status enqueue_steps(mlk_sim* s, int64_t nsteps) {
       FieldPtrs<T> fs = f;
       if (s->vacuum) fs.epsinv = nullptr;
       if constexpr (f32)
-        HIPCHK(bin_scatter_f32(fs, s->g, bins, win, s->d_mudot, fpart, s->stream));
+        HIPCHK(bin_scatter_f32(fs, s->g, bins, win, s->d_mudot, more, s->stream));
       else
-        HIPCHK(bin_scatter_f64(fs, s->g, bins, win, s->d_mudot, fpart, s->stream));
+        HIPCHK(bin_scatter_f64(fs, s->g, bins, win, s->d_mudot, more, s->stream));
     } else if (s->nem > 0) {
       if constexpr (f32)
         HIPCHK(scatter_atomic_f32(f, s->g, win, s->nem, s->d_mudot, s->stream));

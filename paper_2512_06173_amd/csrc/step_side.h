@@ -111,4 +111,14 @@ inline void side_blocks(SideWork& w, int nt) {
   w.blocks = w.tls_blocks + w.finish + (int)((w.shell.total + nt - 1) / nt);
 }
 
+// What else the scatter's launch takes, in workgroups of 256 threads behind its own: the
+// flux partials (flux set), and the soft sources (sblocks workgroups each).  Neither may share
+// a cell with a window, nor a source with the flux plane.
+struct ScatterMore {
+  int flux, sblocks;
+  FluxPlane fp;
+  SourceSet src;
+  const int64_t* step;
+};
+
 }  // namespace mlk

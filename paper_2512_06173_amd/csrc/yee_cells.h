@@ -1,6 +1,9 @@
 // Plain Yee updates of one cell, shared by the plain passes (yee_plain.hip) and the
-// workgroups of the fused sweep's launch that take the shell's H pass.
+// workgroups of the fused sweep's launch that take the shell's H pass, and the soft sources,
+// which ride in the scatter's launch.
 #pragma once
+#include <algorithm>
+
 #include "mlk_internal.h"
 #include "yee_common.h"
 
@@ -74,6 +77,51 @@ __device__ __forceinline__ void update_e_cell(const FieldPtrs<T>& in, const Fiel
   store_field<NT>(&out.E[0][id], n0);
   store_field<NT>(&out.E[1][id], n1);
   store_field<NT>(&out.E[2][id], n2);
+}
+
+// Soft source currents J at t = (n + 1/2) dt:  E -= (dt/eps_r) J.  One thread per
+// cell of each source's support (a plane, or one cell); metallic-wall cells of
+// the driven component keep E = 0.
+template <typename T>
+__device__ __forceinline__ void source_body(const FieldPtrs<T>& f, const Geom& g, const Source& s,
+                                            const int64_t* step, int t) {
+  int i, j, k;
+  double scale;
+  if (s.kind == 0) {
+    const int u = (s.axis + 1) % 3, v = (s.axis + 2) % 3;
+    if (t >= g.n[u] * g.n[v]) return;
+    int p[3];
+    p[s.axis] = s.index;
+    p[u] = t % g.n[u];
+    p[v] = t / g.n[u];
+    i = p[0];
+    j = p[1];
+    k = p[2];
+    scale = g.inv_dx;
+  } else {
+    if (t > 0) return;
+    i = s.ijk[0];
+    j = s.ijk[1];
+    k = s.ijk[2];
+    scale = g.inv_dx * g.inv_dx * g.inv_dx;
+  }
+  if (tangential_wall(g, s.comp, i, j, k)) return;
+  const double tm = ((double)(*step) + 0.5) * g.dt;
+  const size_t id = cell_index(g, i, j, k);
+  const double J = pulse_value(s, tm) * scale;
+  const double ei = f.epsinv ? (double)f.epsinv[id] : 1.0;  // null: eps_r = 1 everywhere
+  f.E[s.comp][id] -= (T)((double)g.dt * ei * J);
+}
+
+// Blocks of 256 threads per source of a set (the largest support).
+inline int source_blocks(const Geom& g, const SourceSet& src) {
+  int maxp = 1;
+  for (int q = 0; q < src.count; ++q)
+    if (src.s[q].kind == 0) {
+      const int u = (src.s[q].axis + 1) % 3, v = (src.s[q].axis + 2) % 3;
+      maxp = std::max(maxp, g.n[u] * g.n[v]);
+    }
+  return (maxp + 255) / 256;
 }
 
 }  // namespace mlk

@@ -50,39 +50,6 @@ __global__ __launch_bounds__(256) void k_update_shell_batch(const ShellJob<T>* j
   else update_e_cell<NT>(J.in, J.out, J.g, i, j, k);
 }
 
-// Soft source currents J at t = (n + 1/2) dt:  E -= (dt/eps_r) J.  One thread per
-// cell of each source's support (a plane, or one cell); metallic-wall cells of
-// the driven component keep E = 0.
-template <typename T>
-__device__ __forceinline__ void source_body(const FieldPtrs<T>& f, const Geom& g, const Source& s,
-                                            const int64_t* step, int t) {
-  int i, j, k;
-  double scale;
-  if (s.kind == 0) {
-    const int u = (s.axis + 1) % 3, v = (s.axis + 2) % 3;
-    if (t >= g.n[u] * g.n[v]) return;
-    int p[3];
-    p[s.axis] = s.index;
-    p[u] = t % g.n[u];
-    p[v] = t / g.n[u];
-    i = p[0];
-    j = p[1];
-    k = p[2];
-    scale = g.inv_dx;
-  } else {
-    if (t > 0) return;
-    i = s.ijk[0];
-    j = s.ijk[1];
-    k = s.ijk[2];
-    scale = g.inv_dx * g.inv_dx * g.inv_dx;
-  }
-  if (tangential_wall(g, s.comp, i, j, k)) return;
-  const double tm = ((double)(*step) + 0.5) * g.dt;
-  const size_t id = cell_index(g, i, j, k);
-  const double J = pulse_value(s, tm) * scale;
-  f.E[s.comp][id] -= (T)((double)g.dt * (double)f.epsinv[id] * J);
-}
-
 template <typename T>
 __global__ void k_sources(FieldPtrs<T> f, Geom g, SourceSet src, const int64_t* step) {
   const int q = blockIdx.y;
@@ -99,17 +66,6 @@ __global__ __launch_bounds__(256) void k_sources_batch(const SourceJob<T>* jobs,
   if (lb >= J.nblocks) return;
   const int q = lb / J.bx;
   source_body(J.f, J.g, J.src.s[q], J.step, (lb - q * J.bx) * blockDim.x + threadIdx.x);
-}
-
-// Blocks of 256 threads per source of a set (the largest support).
-inline int source_blocks(const Geom& g, const SourceSet& src) {
-  int maxp = 1;
-  for (int q = 0; q < src.count; ++q)
-    if (src.s[q].kind == 0) {
-      const int u = (src.s[q].axis + 1) % 3, v = (src.s[q].axis + 2) % 3;
-      maxp = max(maxp, g.n[u] * g.n[v]);
-    }
-  return (maxp + 255) / 256;
 }
 
 template <typename T>

@@ -52,3 +52,34 @@ def test_scatter_against_the_oracle(case, n, precision):
     err = max(np.max(np.abs(a - b)) for a, b in zip(got, want)) / scale
     print(f"[scatter] {shape} {precision} {n}: {err:.2e} of {scale:.2e}", flush=True)
     assert scale > 0 and err <= (1e-13 if precision == "fp64" else (n + 6) * 2.0 ** -24)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("eps", [False, True])
+@pytest.mark.parametrize("flux", [None, (2, 4), (2, 20), (0, 3), (2, 3)])
+@pytest.mark.parametrize("plane", [(2, 3), (2, 12), (0, 2)])
+@pytest.mark.parametrize("point", [(3, 4, 5), (15, 11, 12), (15, 11, 3)])
+def test_sources_with_the_scatter(precision, eps, flux, plane, point):
+    """A plane and a point source clear of the windows (z = 8 to 16 or so) and within them, with
+    flux planes apart from them and through them: whether they ride in the scatter's launch
+    or have their own (as while their phase is timed), the run is the same bit for bit."""
+    rng = np.random.default_rng(4)
+    pos = np.column_stack([rng.uniform(8, 22, 30), rng.uniform(7, 15, 30),
+                           rng.uniform(11.5, 12.5, 30)])
+    field = rng.uniform(1.0, 4.0, (24, 22, 30))
+    runs = []
+    for timed in (False, True):
+        s = mlk().Simulation((30, 22, 24), precision=precision)
+        if eps:
+            s.set_eps(field)
+        s.add_tls(pos=pos, sigma=np.full(30, 1.0), gamma=np.ones(30), omega0=np.full(30, 0.25),
+                  dipole=np.tile([0.3, 0.2, -0.4], (30, 1)), rho0=np.tile([0.5, 0.1, 0.4], (30, 1)))
+        s.add_plane_source(plane[0], plane[1], (plane[0] + 2) % 3, 0.7, 0.3, 3.0, 2.0)
+        s.add_point_source(0, point, 0.9, 0.3, 3.0, 1.0)
+        if flux:
+            s.add_flux_plane(*flux)
+        if timed:
+            s.set_timing(["sources"])
+        s.step(7)
+        runs.append([np.asarray(f) for f in s.fields()] + ([s.flux_series()] if flux else []))
+    assert all(np.array_equal(x, y) for x, y in zip(*runs))
