@@ -2718,6 +2718,8 @@ struct BatchTables {
   bool gather_wide = true;  // every member's arrays take 16-byte units
   DevTable<FusedJob<T>> fused[kTileSlots];  // by tile shape, see tile_slot
   bool fused_lean[kTileSlots] = {};  // no job's box reaches a y or z layer
+  int side_slot = -1;        // the fused launch that takes the side work (-1: none)
+  bool shell_rides = false;  // the shells' H pass is part of it
   DevTable<ShellJob<T>> shell;
   DevTable<SourceJob<T>> sources;
   DevTable<ScatterJob<T>> scatter;
@@ -2782,7 +2784,7 @@ mlk_status build_tables(mlk_batch* b, BatchTables<T> (&tab)[2]) {
     std::vector<ScatterJob<T>> sc;
     std::vector<const std::vector<float>*> gw, sw;  // block work of the non-empty jobs
     int reach = 0;
-    bool wide = true;
+    bool wide = true, rides = true;
     for (mlk_sim* s : b->sims)
       if (s->nem > 0) reach = std::max(reach, s->reach);
     for (mlk_sim* s : b->sims) {
@@ -2825,6 +2827,8 @@ mlk_status build_tables(mlk_batch* b, BatchTables<T> (&tab)[2]) {
         fu[tile_slot(tl.tx, tl.ty)].push_back(J);
       }
       ShellJob<T> S{};
+      if (b->fused && shell_map(s->g, inner).total > 0)
+        rides = rides && shell_rides(inner, shell_map(s->g, inner));
       S.in = cur;
       S.out = nxt;
       S.g = s->g;
@@ -2869,6 +2873,10 @@ mlk_status build_tables(mlk_batch* b, BatchTables<T> (&tab)[2]) {
       for (const FusedJob<T>& J : fu[k]) lean = lean && fused_cpm(J.g, J.box) <= 1;
       t.fused_lean[k] = lean;
     }
+    t.side_slot = -1;
+    for (int k = kTileSlots - 1; k >= 0; --k)
+      if (t.fused[k].nblocks > 0) t.side_slot = k;
+    t.shell_rides = rides;
     STCHK(make_table(t.shell, sh));
     STCHK(make_table(t.sources, so));
     STCHK(make_table(t.scatter, sc));
@@ -2905,6 +2913,47 @@ mlk_status rebuild_tables(mlk_batch* b) {
   return b->fp32 ? build_tables<float>(b, b->t32) : build_tables<double>(b, b->t64);
 }
 
+// The fused launches of a batched step and the shell passes; tls: the two-level steps ride.
+template <typename T>
+hipError_t batch_sweeps(mlk_batch* b, const BatchTables<T>& t, bool tls) {
+  constexpr bool f32 = sizeof(T) == 4;
+  hipStream_t st = b->stream;
+  hipError_t e = hipSuccess;
+  for (int k = 0; k < kTileSlots && e == hipSuccess; ++k) {
+    const DevTable<FusedJob<T>>& f = t.fused[k];
+    BatchSide<T> side{};
+    if (k == t.side_slot) {
+      if (tls) {
+        side.tls = b->tls.jobs;
+        side.tls_start = b->tls.start;
+        side.tls_jobs = b->tls.njobs;
+        side.ntls = b->tls.nblocks;
+      }
+      if (t.shell_rides) {
+        side.shell = t.shell.jobs;
+        side.shell_start = t.shell.start;
+        side.shell_jobs = t.shell.njobs;
+        side.nshell = t.shell.nblocks;
+      }
+    }
+    if constexpr (f32)
+      e = sweep_fused_batch_f32(f.jobs, f.start, f.njobs, f.nblocks, slot_tx(k), slot_ty(k),
+                                t.fused_lean[k], t.stream, side, st);
+    else
+      e = sweep_fused_batch_f64(f.jobs, f.start, f.njobs, f.nblocks, slot_tx(k), slot_ty(k),
+                                t.fused_lean[k], t.stream, side, st);
+  }
+  for (int h = t.side_slot >= 0 && t.shell_rides ? 0 : 1; h >= 0 && e == hipSuccess; --h) {
+    if constexpr (f32)
+      e = shell_batch_f32(t.shell.jobs, t.shell.start, t.shell.njobs, t.shell.nblocks, h == 1,
+                          t.stream, st);
+    else
+      e = shell_batch_f64(t.shell.jobs, t.shell.start, t.shell.njobs, t.shell.nblocks, h == 1,
+                          t.stream, st);
+  }
+  return e;
+}
+
 // Enqueue one batched step on tables of parity q.
 template <typename T>
 mlk_status enqueue_batch_step(mlk_batch* b, const BatchTables<T>& t) {
@@ -2919,24 +2968,13 @@ mlk_status enqueue_batch_step(mlk_batch* b, const BatchTables<T>& t) {
                                              t.gather_reach, t.gather_wide, st));
   else HIPCHK(gather_batch_f64(t.gather.jobs, t.gather.order, t.gather.norder, t.gather_reach,
                                t.gather_wide, st));
-  HIPCHK(tls_batch(b->tls.jobs, b->tls.start, b->tls.njobs, b->tls.nblocks, st));
+  // the first fused launch takes the two-level steps and, where it can, the shells' H pass
+  const bool tls_rides = t.side_slot >= 0;
+  if (!tls_rides)
+    HIPCHK(tls_batch(b->tls.jobs, b->tls.start, b->tls.njobs, b->tls.nblocks, st));
   for (int n = 2; n <= kMaxLevels; ++n)
     HIPCHK(ml_batch(b->ml[n].jobs, b->ml[n].start, b->ml[n].njobs, b->ml[n].nblocks, n, st));
-  for (int k = 0; k < kTileSlots; ++k) {
-    const DevTable<FusedJob<T>>& f = t.fused[k];
-    if constexpr (f32)
-      HIPCHK(sweep_fused_batch_f32(f.jobs, f.start, f.njobs, f.nblocks, slot_tx(k), slot_ty(k),
-                                   t.fused_lean[k], t.stream, st));
-    else
-      HIPCHK(sweep_fused_batch_f64(f.jobs, f.start, f.njobs, f.nblocks, slot_tx(k), slot_ty(k),
-                                   t.fused_lean[k], t.stream, st));
-  }
-  for (int h = 1; h >= 0; --h) {
-    if constexpr (f32) HIPCHK(shell_batch_f32(t.shell.jobs, t.shell.start, t.shell.njobs,
-                                              t.shell.nblocks, h == 1, t.stream, st));
-    else HIPCHK(shell_batch_f64(t.shell.jobs, t.shell.start, t.shell.njobs, t.shell.nblocks,
-                                h == 1, t.stream, st));
-  }
+  HIPCHK(batch_sweeps(b, t, true));
   if constexpr (f32) HIPCHK(sources_batch_f32(t.sources.jobs, t.sources.start, t.sources.njobs,
                                               t.sources.nblocks, st));
   else HIPCHK(sources_batch_f64(t.sources.jobs, t.sources.start, t.sources.njobs,
@@ -3399,23 +3437,7 @@ mlk_status time_batch_sweep(mlk_batch* b, const BatchTables<T>& t, double* us) {
   HIPCHK(hipEventCreate(&e1));
   hipError_t err = hipSuccess;
   auto once = [&]() {
-    for (int k = 0; k < kTileSlots && err == hipSuccess; ++k) {
-      const DevTable<FusedJob<T>>& f = t.fused[k];
-      if constexpr (f32)
-        err = sweep_fused_batch_f32(f.jobs, f.start, f.njobs, f.nblocks, slot_tx(k), slot_ty(k),
-                                    t.fused_lean[k], t.stream, st);
-      else
-        err = sweep_fused_batch_f64(f.jobs, f.start, f.njobs, f.nblocks, slot_tx(k), slot_ty(k),
-                                    t.fused_lean[k], t.stream, st);
-    }
-    for (int h = 1; h >= 0 && err == hipSuccess; --h) {
-      if constexpr (f32)
-        err = shell_batch_f32(t.shell.jobs, t.shell.start, t.shell.njobs, t.shell.nblocks, h == 1,
-                              t.stream, st);
-      else
-        err = shell_batch_f64(t.shell.jobs, t.shell.start, t.shell.njobs, t.shell.nblocks, h == 1,
-                              t.stream, st);
-    }
+    if (err == hipSuccess) err = batch_sweeps(b, t, false);
   };
   constexpr int kReps = 3;
   once();  // warm-up

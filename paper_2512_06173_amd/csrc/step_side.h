@@ -121,4 +121,16 @@ struct ScatterMore {
   const int64_t* step;
 };
 
+// What rides in a batch's fused launch: its tables of two-level steps and of shells (for
+// their H pass), with the tables' blocks of 256 threads (0: none).
+template <typename T>
+struct BatchSide {
+  const TlsJob* tls;
+  const int* tls_start;
+  int tls_jobs, ntls;
+  const ShellJob<T>* shell;
+  const int* shell_start;
+  int shell_jobs, nshell;
+};
+
 }  // namespace mlk

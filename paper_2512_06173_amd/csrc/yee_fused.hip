@@ -599,11 +599,43 @@ __global__ __launch_bounds__(256, 4) void k_fused_frame(FrameJobs<T> fj) {
                    (int)blockIdx.x - fj.start[j]);
 }
 
+// The side work of a batch, in units of 256 threads (a wavefront belongs to one unit, whatever
+// the workgroup's size): two-level steps, then the shells' H pass.
+template <typename T, int THREADS, bool NT>
+__device__ __forceinline__ void batch_side_body(const BatchSide<T>& w, int b) {
+  const unsigned gt = (unsigned)b * THREADS + threadIdx.x;
+  int u = __builtin_amdgcn_readfirstlane((int)(gt >> 8));
+  const int l = (int)(gt & 255u);
+  if (u < w.ntls) {
+    const int j = find_job(w.tls_start, w.tls_jobs, u);
+    const TlsJob J = load_job(w.tls, j);
+    u -= w.tls_start[j];
+    if (u < J.nblocks)
+      tls_body(J.tls, J.dt, J.Et, J.mudot, J.pop_off, J.ser, *J.step, u * 256 + l);
+    return;
+  }
+  u -= w.ntls;
+  if (u >= w.nshell) return;
+  const int j = find_job(w.shell_start, w.shell_jobs, u);
+  const ShellJob<T> J = load_job(w.shell, j);
+  const unsigned t = (unsigned)(u - w.shell_start[j]) * 256u + l;
+  if ((long long)t >= J.m.total) return;
+  int x, y, z;
+  shell_cell(J.g, J.m, t, x, y, z);
+  update_h_cell<NT>(J.in, J.out, J.g, x, y, z);
+}
+
 // One launch over the jobs of a batch of domains (see BatchJobs); CPM and W as for
 // the single-domain kernels (the lean form when no job's box reaches a y or z layer).
+// Blocks from nblocks on take the side work.
 template <typename T, int TX, int TY, int CPM, int W, bool NT>
 __global__ __launch_bounds__(TX * TY, W) void k_fused_batch(const FusedJob<T>* jobs,
-                                                         const int* start, int njobs) {
+                                                         const int* start, int njobs,
+                                                         int nblocks, BatchSide<T> side) {
+  if ((int)blockIdx.x >= nblocks) {  // uniform across the workgroup
+    batch_side_body<T, TX * TY, NT>(side, (int)blockIdx.x - nblocks);
+    return;
+  }
   const int j = find_job(start, njobs, blockIdx.x);
   const FusedJob<T> J = load_job(jobs, j);
   const int bid = blockIdx.x - start[j];
@@ -743,10 +775,13 @@ static hipError_t launch_frame(const FieldPtrs<T>& a, const FieldPtrs<T>& b, con
 
 template <typename T, int TX, int TY>
 static void launch_fused_batch_t(const FusedJob<T>* jobs, const int* start, int njobs,
-                                 int nblocks, bool lean, bool stream, hipStream_t st) {
+                                 int nblocks, bool lean, bool stream, const BatchSide<T>& side,
+                                 hipStream_t st) {
   constexpr int W = LeanWaves<T, TX, TY, 1>::value;
+  const int nside = (int)(((long long)(side.ntls + side.nshell) * 256 + TX * TY - 1) / (TX * TY));
   auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(TX * TY), 0, st, jobs, start, njobs);
+    hipLaunchKernelGGL(kernel, dim3(nblocks + nside), dim3(TX * TY), 0, st, jobs, start, njobs,
+                       nblocks, side);
   };
   if (lean)
     stream ? go(k_fused_batch<T, TX, TY, 1, W, true>) : go(k_fused_batch<T, TX, TY, 1, W, false>);
@@ -756,21 +791,22 @@ static void launch_fused_batch_t(const FusedJob<T>* jobs, const int* start, int 
 
 template <typename T, int TX>
 static void launch_fused_batch_tx(const FusedJob<T>* jobs, const int* start, int njobs,
-                                  int nblocks, int ty, bool lean, bool stream, hipStream_t st) {
-  if (ty == 16) launch_fused_batch_t<T, TX, 16>(jobs, start, njobs, nblocks, lean, stream, st);
-  else if (ty == 8) launch_fused_batch_t<T, TX, 8>(jobs, start, njobs, nblocks, lean, stream, st);
-  else launch_fused_batch_t<T, TX, 4>(jobs, start, njobs, nblocks, lean, stream, st);
+                                  int nblocks, int ty, bool lean, bool stream,
+                                  const BatchSide<T>& side, hipStream_t st) {
+  if (ty == 16) launch_fused_batch_t<T, TX, 16>(jobs, start, njobs, nblocks, lean, stream, side, st);
+  else if (ty == 8) launch_fused_batch_t<T, TX, 8>(jobs, start, njobs, nblocks, lean, stream, side, st);
+  else launch_fused_batch_t<T, TX, 4>(jobs, start, njobs, nblocks, lean, stream, side, st);
 }
 
 template <typename T>
 static hipError_t launch_fused_batch(const FusedJob<T>* jobs, const int* start, int njobs,
                                      int nblocks, int tx, int ty, bool lean, bool stream,
-                                     hipStream_t st) {
+                                     const BatchSide<T>& side, hipStream_t st) {
   if (nblocks <= 0) return hipSuccess;
   if (tx == 32)
-    launch_fused_batch_tx<T, 32>(jobs, start, njobs, nblocks, ty, lean, stream, st);
+    launch_fused_batch_tx<T, 32>(jobs, start, njobs, nblocks, ty, lean, stream, side, st);
   else
-    launch_fused_batch_tx<T, 64>(jobs, start, njobs, nblocks, ty, lean, stream, st);
+    launch_fused_batch_tx<T, 64>(jobs, start, njobs, nblocks, ty, lean, stream, side, st);
   return hipGetLastError();
 }
 
@@ -794,13 +830,13 @@ hipError_t sweep_frame_f32(const FieldPtrs<float>& a, const FieldPtrs<float>& b,
 }
 hipError_t sweep_fused_batch_f64(const FusedJob<double>* jobs, const int* start, int njobs,
                                  int nblocks, int tx, int ty, bool lean, bool stream,
-                                 hipStream_t st) {
-  return launch_fused_batch<double>(jobs, start, njobs, nblocks, tx, ty, lean, stream, st);
+                                 const BatchSide<double>& side, hipStream_t st) {
+  return launch_fused_batch<double>(jobs, start, njobs, nblocks, tx, ty, lean, stream, side, st);
 }
 hipError_t sweep_fused_batch_f32(const FusedJob<float>* jobs, const int* start, int njobs,
                                  int nblocks, int tx, int ty, bool lean, bool stream,
-                                 hipStream_t st) {
-  return launch_fused_batch<float>(jobs, start, njobs, nblocks, tx, ty, lean, stream, st);
+                                 const BatchSide<float>& side, hipStream_t st) {
+  return launch_fused_batch<float>(jobs, start, njobs, nblocks, tx, ty, lean, stream, side, st);
 }
 
 }  // namespace mlk
