@@ -65,15 +65,63 @@ void dfree(P*& p) {
   p = nullptr;
 }
 
-// Device buffer owned by a scope.
+// Device blocks that a sim keeps from one adjoint call for the next, at most a GiB of them:
+// a call takes two dozen, and allocating and freeing them took 3.0 of its 11.8 ms on
+// 112 x 104 x 120 cells (48 steps).  Above that a call's own work hides it, and the memory
+// is worth more to others.  A block is reused for the same size only; a call of another shape
+// frees what it finds first.  The owner's stream has been synchronised when a block is
+// handed out (mlk_adjoint does that first), and it belongs to one sim, like every call on it.
+struct Scratch {
+  static constexpr size_t kKeep = (size_t)1 << 30;
+  std::vector<std::pair<void*, size_t>> blocks;
+  size_t bytes = 0;
+  void clear() {
+    for (auto& b : blocks) (void)hipFree(b.first);
+    blocks.clear();
+    bytes = 0;
+  }
+  hipError_t get(void** p, size_t n) {
+    for (size_t q = 0; q < blocks.size(); ++q)
+      if (blocks[q].second == n) {
+        *p = blocks[q].first;
+        bytes -= n;
+        blocks.erase(blocks.begin() + q);
+        return hipSuccess;
+      }
+    clear();
+    return dalloc(p, n);
+  }
+  void put(void* p, size_t n) {
+    if (bytes + n > kKeep) {
+      (void)hipFree(p);
+      return;
+    }
+    blocks.push_back({p, n});
+    bytes += n;
+  }
+};
+
+// Device buffer owned by a scope, taken from and given back to a Scratch if there is one.
 template <typename T>
 struct DevBuf {
   T* p = nullptr;
-  ~DevBuf() { dfree(p); }
-  hipError_t alloc(size_t n) {
-    dfree(p);
+  size_t n = 0;
+  Scratch* pool = nullptr;
+  DevBuf() = default;
+  explicit DevBuf(Scratch* s) : pool(s) {}
+  DevBuf(const DevBuf&) = delete;
+  DevBuf& operator=(const DevBuf&) = delete;
+  ~DevBuf() { release(); }
+  void release() {
+    if (p && pool) pool->put(p, n * sizeof(T));
+    else dfree(p);
+    p = nullptr;
+  }
+  hipError_t alloc(size_t count) {
+    release();
+    n = count;
     if (n == 0) return hipSuccess;
-    return dalloc(&p, n * sizeof(T));
+    return pool ? pool->get((void**)&p, n * sizeof(T)) : dalloc(&p, n * sizeof(T));
   }
 };
 
@@ -88,6 +136,7 @@ struct mlk_sim {
   mlk_grid_desc desc{};
   // phase timing: event pool, pending (phase, start event, end event) marks
   int timing = 0;  // bit p set: phase p is timed
+  Scratch scratch;
   std::vector<hipEvent_t> events;
   size_t next_event = 0;
   std::vector<std::array<int, 3>> marks;
@@ -1211,6 +1260,7 @@ mlk_status enqueue_cavity_steps(mlk_sim* s, int64_t nsteps) {
 }
 
 void release(mlk_sim* s) {
+  s->scratch.clear();
   for (hipEvent_t e : s->events) (void)hipEventDestroy(e);
   s->events.clear();
   // caller-owned buffers are dropped, not freed
@@ -2337,7 +2387,8 @@ mlk_status adjoint_run(mlk_sim* s, int kind, const double* weights, int64_t T_st
   STCHK(reserve_series(s, T_steps));
   const int64_t step0 = s->host_step;
 
-  DevBuf<char> ckpt;
+  Scratch* const sp = &s->scratch;
+  DevBuf<char> ckpt{sp};
   HIPCHK(ckpt.alloc(ck * (size_t)nseg));
   hipEvent_t ev[3];
   for (auto& e : ev) HIPCHK(hipEventCreate(&e));
@@ -2375,7 +2426,10 @@ mlk_status adjoint_run(mlk_sim* s, int kind, const double* weights, int64_t T_st
   // adjoint state; a fused-sweep sim takes the transposed sweep out of place
   // (fused box plus shell), with two sets of adjoint fields used in turn
   const bool oop = s->desc.sweep == MLK_SWEEP_FUSED;
-  DevBuf<T> Eb[2][3], Hb[2][3], psib[2];
+  using Buf = DevBuf<T>;
+  Buf Eb[2][3] = {{Buf{sp}, Buf{sp}, Buf{sp}}, {Buf{sp}, Buf{sp}, Buf{sp}}};
+  Buf Hb[2][3] = {{Buf{sp}, Buf{sp}, Buf{sp}}, {Buf{sp}, Buf{sp}, Buf{sp}}};
+  Buf psib[2] = {Buf{sp}, Buf{sp}};
   for (int q = 0; q < (oop ? 2 : 1); ++q)
     for (int c = 0; c < 3; ++c) {
       HIPCHK(Eb[q][c].alloc(nc));
@@ -2388,7 +2442,7 @@ mlk_status adjoint_run(mlk_sim* s, int kind, const double* weights, int64_t T_st
     HIPCHK(psib[q].alloc(npsi));
     if (npsi) HIPCHK(hipMemsetAsync(psib[q].p, 0, npsi * sizeof(T), st));
   }
-  DevBuf<double> sb, gd, mub, etb, geps;
+  DevBuf<double> sb{sp}, gd{sp}, mub{sp}, etb{sp}, geps{sp};
   HIPCHK(sb.alloc((size_t)3 * nt));
   HIPCHK(gd.alloc((size_t)3 * nt));
   HIPCHK(mub.alloc((size_t)3 * M));
@@ -2404,8 +2458,8 @@ mlk_status adjoint_run(mlk_sim* s, int kind, const double* weights, int64_t T_st
     HIPCHK(hipMemcpy(sb.p, s0.data(), s0.size() * sizeof(double), hipMemcpyHostToDevice));
   }
   // tape of one segment
-  DevBuf<T> tbox;
-  DevBuf<double> ts, tg, tf;
+  Buf tbox{sp};
+  DevBuf<double> ts{sp}, tg{sp}, tf{sp};
   HIPCHK(tbox.alloc(nb * 3 * (size_t)(K + 1)));
   HIPCHK(ts.alloc((size_t)3 * nt * K));
   HIPCHK(tg.alloc((size_t)3 * M * K));

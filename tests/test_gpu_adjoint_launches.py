@@ -58,3 +58,25 @@ def test_fused_adjoint_matches_plain(case, precision):
     assert abs(fv - pv) <= tol * abs(pv) and rel(fge, pge) <= tol
     if emitters:
         assert rel(fgd, pgd) <= tol
+
+
+def test_adjoint_calls_of_changing_shape():
+    """The device blocks kept between calls: calls with other steps, checkpoints and boxes in
+    between (more and less of everything) leave a call's result as it was, bit for bit."""
+    shape = (40, 30, 28)
+    rng = np.random.default_rng(3)
+    tls = W.TLSSet(pos=np.array(shape) / 2 + rng.uniform(-1, 1, (4, 3)), sigma=np.full(4, 0.8),
+                   gamma=np.ones(4), omega0=rng.uniform(0.45, 0.55, 4),
+                   dipole=0.6 * rng.standard_normal((4, 3)), rho0=np.tile([0.5, 0.5, 0.0], (4, 1)))
+    w = W.Workload(name="adj_shapes", shape=shape, bc=("cpml",) * 6, cpml=(5,) * 6,
+                   eps=rng.uniform(1.0, 2.0, shape[::-1]), tls=tls,
+                   point_sources=[W.PointSource(1, (19, 14, 13), 1.0, 0.5, 2.0, 6.0)],
+                   flux=(2, 16), steps=20, precision="fp32")
+    sim = mlk().from_workload(w, sweep="fused")
+    box = ((16, 11, 10), (22, 17, 16))
+    calls = [(20, box, 8), (20, box, 8), (31, ((10, 10, 10), (28, 20, 20)), 5), (20, box, 8),
+             (3, ((16, 11, 10), (17, 12, 11)), 3), (20, box, 8)]
+    res = [sim.adjoint("flux", n, b, checkpoint_every=k) for n, b, k in calls]
+    for q in (1, 3, 5):
+        assert res[q][0] == res[0][0]
+        assert all(np.array_equal(x, y) for x, y in zip(res[q][1:], res[0][1:]))
