@@ -363,7 +363,11 @@ mlk_status mlk_checkpoint_load(mlk_sim* s, const void* src, int32_t mem_kind);
  *   SHELL         the CPML-shell passes of the fused mode (steps 1, 6)
  *   SOURCES       soft source currents (step 5)
  *   SCATTER       molecular current scatter into E (step 5)
- *   DETECTORS     flux plane save, probes, flux series, step counter (step 7) */
+ *   DETECTORS     flux plane save, probes, flux series, step counter (step 7)
+ * What a timed phase covers has launches of its own, which the events enclose.  Untimed,
+ * the two-level steps, the closing of the step before and the H pass of the shell run as
+ * extra workgroups of the sweep's launch, and soft sources that no emitter window reaches
+ * in the scatter's. */
 enum {
   MLK_PHASE_EMITTERS = 0,
   MLK_PHASE_SWEEP = 1,
