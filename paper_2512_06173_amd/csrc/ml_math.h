@@ -14,105 +14,78 @@ __host__ __device__ constexpr int up(int a, int b) {
   return a <= b ? a * N - a * (a - 1) / 2 + (b - a) : b * N - b * (b - 1) / 2 + (a - b);
 }
 
-// Z = X Y for packed symmetric X and Y that commute (polynomials of one matrix): Z is
-// symmetric too.
+// Cyclic Jacobi (by rows) on the packed symmetric A: A becomes diagonal, Q holds the
+// eigenvectors.  The pairs (p, q) of equal p + q are disjoint and wait for none of each
+// other, so a sweep of N (N - 1) / 2 rotations goes in 2 N - 3 rounds, whose angles are
+// formed side by side:
+//   h = sqrt(d^2 + b^2), cos^2 phi = (1 + |d| / h) / 2, t = sgn(d) b / (2 h cos^2 phi),
+//   c = 1 / sqrt(t^2 + 1), s = t c,
+// d = A_qq - A_pp, b = 2 A_pq (both scaled by a power of two first, so nothing overflows or
+// vanishes; reciprocal square roots instead of divisions as far as t).  c keeps the root and
+// the quotient of the textbook form: their rounding adds up to 1e-11 in a population over
+// 20,000 steps, and what rounds otherwise (c from a reciprocal square root, the same
+// rotations in another order, or no rotations: cos and sin of H dt from matrix products,
+// whose trace stays within 1e-12) ends up 1.2e-12 to 1.6e-12 apart in the fields and up to
+// 2e-11 in the populations, beyond what results are held to.
+// Rotations with A_pq = 0 are the identity.  What bounds the kernel is the instruction
+// stream of one wavefront (an emitter per lane, few wavefronts on the chip).
 template <int N>
-__device__ __forceinline__ void sym_mul(const double (&X)[N * (N + 1) / 2],
-                                        const double (&Y)[N * (N + 1) / 2],
-                                        double (&Z)[N * (N + 1) / 2]) {
+__device__ __forceinline__ void jacobi(double (&A)[N * (N + 1) / 2], double (&Q)[N][N]) {
 #pragma unroll
   for (int a = 0; a < N; ++a)
 #pragma unroll
-    for (int b = a; b < N; ++b) {
-      double z = 0.0;
+    for (int b = 0; b < N; ++b) Q[a][b] = a == b ? 1.0 : 0.0;
+  for (int sweep = 0; sweep < 32; ++sweep) {
+    double off = 0.0, diag = 0.0;
 #pragma unroll
-      for (int c = 0; c < N; ++c) z = __builtin_fma(X[up<N>(a, c)], Y[up<N>(c, b)], z);
-      Z[up<N>(a, b)] = z;
+    for (int a = 0; a < N; ++a) {
+      diag += A[up<N>(a, a)] * A[up<N>(a, a)];
+#pragma unroll
+      for (int b = a + 1; b < N; ++b) off += A[up<N>(a, b)] * A[up<N>(a, b)];
     }
-}
-
-// C = cos A and S = sin A of a packed symmetric A (overwritten), from matrix products only.
-// With B = A^2, cos A = p(B) and sin A = A q(B), p and q of degree 7: the polynomials that
-// interpolate cos(sqrt y) and sin(sqrt y) / sqrt y at the eight Chebyshev nodes of
-// [0, 1.5625] (errors 5e-17 and 3e-18, 1.0e-16 with rounded coefficients), so good for a norm
-// up to 1.25.  Seven products: B, B^2, B^3, B^4, one for the upper half of p and of q
-// each, and A q.  A larger A is halved s times first and the angle doubled s times after,
-// C' = (C - S)(C + S), S' = 2 S C.
-// What bounds the kernel is the instruction stream of one wavefront (an emitter per lane,
-// few wavefronts on the chip), so operations count: for six levels about 1,200 here, where
-// three or four Jacobi sweeps, the sines of the eigenvalues and two products with the
-// eigenvectors took 5,000.
-template <int N>
-__device__ __forceinline__ void cos_sin(double (&A)[N * (N + 1) / 2],
-                                        double (&C)[N * (N + 1) / 2],
-                                        double (&S)[N * (N + 1) / 2]) {
-  constexpr int NS = N * (N + 1) / 2;
-  constexpr double p[8] = {1.0, -0.49999999999999584, 0.04166666666661075,
-                           -0.0013888888886025015, 2.4801586581049492e-05,
-                           -2.755722073848398e-07, 2.0869293481154883e-09,
-                           -1.1175623590078535e-11};
-  constexpr double q[8] = {1.0, -0.1666666666666664, 0.008333333333330037,
-                           -0.00019841269839581692, 2.7557318799284958e-06,
-                           -2.5052050342647083e-08, 1.6054646090937375e-10,
-                           -7.473341292114921e-13};
-  // the largest sum of a row bounds the norm
-  double norm = 0.0;
+    if (!(off > 1e-34 * (diag + 2.0 * off))) break;
 #pragma unroll
-  for (int a = 0; a < N; ++a) {
-    double r = 0.0;
+    for (int round = 1; round <= 2 * N - 3; ++round) {
+      double cs[N - 1], sn[N - 1], tn[N - 1];
 #pragma unroll
-    for (int b = 0; b < N; ++b) r += fabs(A[up<N>(a, b)]);
-    norm = fmax(norm, r);
-  }
-  // 0.8 norm < 2^s (an infinite norm counts as none: the result is no number either way)
-  const int s = max(0, __builtin_amdgcn_frexp_exp(0.8 * norm));
+      for (int i = 0; i < N - 1; ++i) {
+        const int p = i, q = round - i;
+        if (q <= p || q >= N) continue;
+        const double apq = A[up<N>(p, q)];
+        const double d0 = A[up<N>(q, q)] - A[up<N>(p, p)], b0 = 2.0 * apq;
+        const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(d0), fabs(b0)));
+        const double d = __builtin_amdgcn_ldexp(d0, ex), b = __builtin_amdgcn_ldexp(b0, ex);
+        const double rh = rsqrt_refined(__builtin_fma(d, d, b * b));
+        const double rc = rsqrt_refined(__builtin_fma(0.5 * fabs(d), rh, 0.5));
+        const double t = copysign(0.5, d) * b * rh * rc * rc;
+        const double c = 1.0 / sqrt(t * t + 1.0);
+        const bool on = apq != 0.0;
+        cs[i] = on ? c : 1.0;
+        sn[i] = on ? t * c : 0.0;
+        tn[i] = on ? t : 0.0;
+      }
 #pragma unroll
-  for (int k = 0; k < NS; ++k) A[k] = __builtin_amdgcn_ldexp(A[k], -s);
-  {
-    double B[NS], B2[NS], B3[NS], B4[NS], t[NS];
-    sym_mul<N>(A, A, B);
-    sym_mul<N>(B, B, B2);
-    sym_mul<N>(B, B2, B3);
-    sym_mul<N>(B2, B2, B4);
-    auto poly = [&](const double (&c)[8], double (&out)[NS]) {
+      for (int i = 0; i < N - 1; ++i) {
+        const int p = i, q = round - i;
+        if (q <= p || q >= N) continue;
+        const double c = cs[i], s = sn[i], apq = A[up<N>(p, q)];
+        A[up<N>(p, p)] -= tn[i] * apq;
+        A[up<N>(q, q)] += tn[i] * apq;
+        A[up<N>(p, q)] = 0.0;
 #pragma unroll
-      for (int a = 0; a < N; ++a)
-#pragma unroll
-        for (int b = a; b < N; ++b) {
-          const int k = up<N>(a, b);
-          t[k] = __builtin_fma(c[7], B3[k], __builtin_fma(c[6], B2[k], c[5] * B[k])) +
-                 (a == b ? c[4] : 0.0);
+        for (int r = 0; r < N; ++r) {
+          if (r == p || r == q) continue;
+          const double arp = A[up<N>(r, p)], arq = A[up<N>(r, q)];
+          A[up<N>(r, p)] = c * arp - s * arq;
+          A[up<N>(r, q)] = s * arp + c * arq;
         }
-      sym_mul<N>(B4, t, out);
 #pragma unroll
-      for (int a = 0; a < N; ++a)
-#pragma unroll
-        for (int b = a; b < N; ++b) {
-          const int k = up<N>(a, b);
-          out[k] = __builtin_fma(c[1], B[k], __builtin_fma(c[2], B2[k],
-                                                           __builtin_fma(c[3], B3[k], out[k]))) +
-                   (a == b ? c[0] : 0.0);
+        for (int r = 0; r < N; ++r) {
+          const double qrp = Q[r][p], qrq = Q[r][q];
+          Q[r][p] = c * qrp - s * qrq;
+          Q[r][q] = s * qrp + c * qrq;
         }
-    };
-    poly(p, C);
-    double u[NS];
-    poly(q, u);
-    sym_mul<N>(A, u, S);
-  }
-  for (int k = 0; k < s; ++k) {
-    double d[NS], e[NS];
-#pragma unroll
-    for (int n = 0; n < NS; ++n) {
-      d[n] = C[n] - S[n];
-      e[n] = C[n] + S[n];
-    }
-    double c2[NS], s2[NS];
-    sym_mul<N>(d, e, c2);
-    sym_mul<N>(S, C, s2);
-#pragma unroll
-    for (int n = 0; n < NS; ++n) {
-      C[n] = c2[n];
-      S[n] = 2.0 * s2[n];
+      }
     }
   }
 }
@@ -191,26 +164,33 @@ __device__ __forceinline__ double ml_advance(MlState<N>& s, const double et[3], 
                                              bool& finite) {
   constexpr int NS = MlState<N>::NS;
   const double g = et[0] * s.dip[0] + et[1] * s.dip[1] + et[2] * s.dip[2];
-  // U = exp(-i H_eff dt) = C - i S (C, S symmetric, packed upper triangles) up to a phase,
-  // which leaves U rho U^+ as it is: energies count from the middle of their range
+  // U = exp(-i H_eff dt) = C - i S (C, S symmetric, packed upper triangles)
   double C[NS], S[NS];
   {
-    double A[NS], lo = s.en[0] - g * s.M[0], hi = lo;
+    double A[NS], Q[N][N];
+#pragma unroll
+    for (int a = 0; a < N; ++a)
+#pragma unroll
+      for (int b = a; b < N; ++b)
+        A[up<N>(a, b)] = (a == b ? s.en[a] : 0.0) - g * s.M[up<N>(a, b)];
+    jacobi<N>(A, Q);
+    double cl[N], sl[N];
+#pragma unroll
+    for (int q = 0; q < N; ++q) sincos(A[up<N>(q, q)] * dt, &sl[q], &cl[q]);
 #pragma unroll
     for (int a = 0; a < N; ++a)
 #pragma unroll
       for (int b = a; b < N; ++b) {
-        const double h = (a == b ? s.en[a] : 0.0) - g * s.M[up<N>(a, b)];
-        A[up<N>(a, b)] = h * dt;
-        if (a == b) {
-          lo = fmin(lo, h);
-          hi = fmax(hi, h);
-        }
-      }
-    const double mid = 0.5 * (lo + hi) * dt;
+        double c = 0.0, v = 0.0;
 #pragma unroll
-    for (int a = 0; a < N; ++a) A[up<N>(a, a)] -= mid;
-    cos_sin<N>(A, C, S);
+        for (int q = 0; q < N; ++q) {
+          const double qq = Q[a][q] * Q[b][q];
+          c += qq * cl[q];
+          v += qq * sl[q];
+        }
+        C[up<N>(a, b)] = c;
+        S[up<N>(a, b)] = v;
+      }
   }
 #pragma unroll
   for (int a = 0; a < N; ++a)

@@ -8,7 +8,7 @@
 // One step over dt (Strang splitting, second order):
 //   dephase(dt/2): rho_ab *= exp(-gphi dt/2) for a != b   (exact for this dissipator)
 //   unitary:       rho <- U rho U^+, U = exp(-i H_eff dt) = C - i S,
-//                  C = cos(H_eff dt), S = sin(H_eff dt) (see ml_math.h)
+//                  C = Q cos(L dt) Q^T, S = Q sin(L dt) Q^T from H_eff = Q L Q^T
 //   dephase(dt/2)
 // then mu_dot^c = Tr(rho_dot mu^c) (eq. dipole_derivative) at the new state.  For
 // this model the trace has a closed form (with rho = R + i I):
@@ -24,9 +24,8 @@
 // a lone wavefront per SIMD (10,000 emitters are 159 wavefronts for 1024 SIMDs), so
 // the groups of a mixed ensemble run side by side in one launch, the longest first,
 // instead of one launch after another: 10,000 emitters of 2 to 6 levels took
-// 25.6 + 17.5 + 11.6 + 7.2 + 4.9 us in five launches with eigenvectors from Jacobi
-// rotations, 15.7 in one with the rotations' angles free of divisions, 11.8 with the
-// cosine and sine from matrix products (ml_math.h).
+// 25.6 + 17.5 + 11.6 + 7.2 + 4.9 us in five launches, 18.8 in one with the rotations of a
+// round side by side (ml_math.h).
 #include "ml_math.h"
 
 namespace mlk {
