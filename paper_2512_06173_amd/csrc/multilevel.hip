@@ -34,8 +34,8 @@ namespace mlk {
 // wavefront per SIMD (the registers of six levels); separate launches give the small
 // level counts more, which could only tell where a level count fills the chip by
 // itself.  Measured, separate against one launch, a step of 64^3 cells with 1,000,
-// 10,000, 50,000 and 200,000 emitters of 2 to 6 levels: 49.2, 52.9, 79.7, 168.5 against
-// 31.0, 34.8, 61.9, 151.0 us.
+// 10,000, 50,000 and 200,000 emitters of 2 to 6 levels: 66.1, 72.8, 101.6, 191.3 against
+// 37.3, 43.5, 71.1, 164.4 us.
 constexpr int kMlOneLaunchBlocks = 8192;
 
 template <int N>
