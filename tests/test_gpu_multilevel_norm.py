@@ -1,5 +1,5 @@
-"""The multilevel propagator over the sizes of H dt: below the polynomials' range, at its edge and
-over several angle doublings, for every level count."""
+"""The multilevel propagator over the sizes of H dt, from none to many turns a step, for every
+level count."""
 import numpy as np
 import pytest
 
@@ -10,8 +10,8 @@ pytestmark = pytest.mark.gpu
 def test_unitary_step_against_eigenvectors(size):
     """One prescribed step with half the spread of H dt = size, against the exponential from
     numpy's eigenvectors.  Both sides turn phases up to size with relative rounding 2^-53
-    in H, and squaring doubles an error like the angle: 64 (1 + size) 2^-53 on entries
-    of at most one."""
+    in H, and take some tens of operations an entry: 64 (1 + size) 2^-53 on entries of at
+    most one."""
     from paper_2512_06173_amd import mlk
 
     rng = np.random.default_rng(int(1e3 * size))
