@@ -131,7 +131,7 @@ __device__ __forceinline__ void scatter_body(const FieldPtrs<T>& f, const Geom& 
     } else {
       b -= nflux;
       const int q = b / more->sblocks;
-      source_body(f, g, more->src.s[q], more->step, (b - q * more->sblocks) * 256 + threadIdx.x);
+      source_body(f, g, more->src, q, more->step, (b - q * more->sblocks) * 256 + threadIdx.x);
     }
     return;
   }

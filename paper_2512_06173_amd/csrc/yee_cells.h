@@ -79,14 +79,23 @@ __device__ __forceinline__ void update_e_cell(const FieldPtrs<T>& in, const Fiel
   store_field<NT>(&out.E[2][id], n2);
 }
 
+// Whether cell (i,j,k) lies in the support of a source: its plane, or its one cell.
+__device__ __forceinline__ bool source_covers(const Source& s, int i, int j, int k) {
+  if (s.kind == 0) return (s.axis == 0 ? i : (s.axis == 1 ? j : k)) == s.index;
+  return i == s.ijk[0] && j == s.ijk[1] && k == s.ijk[2];
+}
+
 // Soft source currents J at t = (n + 1/2) dt:  E -= (dt/eps_r) J.  One thread per
 // cell of each source's support (a plane, or one cell); metallic-wall cells of
-// the driven component keep E = 0.
+// the driven component keep E = 0.  Supports may share cells (two pulses on one plane, planes
+// that cross, a point on a plane): the first source of a component on a cell adds those
+// behind it there, in their order, so that a cell has one writer.
 template <typename T>
-__device__ __forceinline__ void source_body(const FieldPtrs<T>& f, const Geom& g, const Source& s,
-                                            const int64_t* step, int t) {
+__device__ __forceinline__ void source_body(const FieldPtrs<T>& f, const Geom& g,
+                                            const SourceSet& src, int q, const int64_t* step,
+                                            int t) {
+  const Source& s = src.s[q];
   int i, j, k;
-  double scale;
   if (s.kind == 0) {
     const int u = (s.axis + 1) % 3, v = (s.axis + 2) % 3;
     if (t >= g.n[u] * g.n[v]) return;
@@ -97,20 +106,26 @@ __device__ __forceinline__ void source_body(const FieldPtrs<T>& f, const Geom& g
     i = p[0];
     j = p[1];
     k = p[2];
-    scale = g.inv_dx;
   } else {
     if (t > 0) return;
     i = s.ijk[0];
     j = s.ijk[1];
     k = s.ijk[2];
-    scale = g.inv_dx * g.inv_dx * g.inv_dx;
   }
   if (tangential_wall(g, s.comp, i, j, k)) return;
+  for (int o = 0; o < q; ++o)
+    if (src.s[o].comp == s.comp && source_covers(src.s[o], i, j, k)) return;
   const double tm = ((double)(*step) + 0.5) * g.dt;
   const size_t id = cell_index(g, i, j, k);
-  const double J = pulse_value(s, tm) * scale;
   const double ei = f.epsinv ? (double)f.epsinv[id] : 1.0;  // null: eps_r = 1 everywhere
-  f.E[s.comp][id] -= (T)((double)g.dt * ei * J);
+  T e = f.E[s.comp][id];
+  for (int o = q; o < src.count; ++o) {
+    const Source& so = src.s[o];
+    if (so.comp != s.comp || !source_covers(so, i, j, k)) continue;
+    const double scale = so.kind == 0 ? g.inv_dx : g.inv_dx * g.inv_dx * g.inv_dx;
+    e -= (T)((double)g.dt * ei * (pulse_value(so, tm) * scale));
+  }
+  f.E[s.comp][id] = e;
 }
 
 // Blocks of 256 threads per source of a set (the largest support).

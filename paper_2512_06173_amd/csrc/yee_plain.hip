@@ -54,7 +54,7 @@ template <typename T>
 __global__ void k_sources(FieldPtrs<T> f, Geom g, SourceSet src, const int64_t* step) {
   const int q = blockIdx.y;
   if (q >= src.count) return;
-  source_body(f, g, src.s[q], step, blockIdx.x * blockDim.x + threadIdx.x);
+  source_body(f, g, src, q, step, blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 template <typename T>
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(256) void k_sources_batch(const SourceJob<T>* jobs,
   const int lb = blockIdx.x - start[jb];
   if (lb >= J.nblocks) return;
   const int q = lb / J.bx;
-  source_body(J.f, J.g, J.src.s[q], J.step, (lb - q * J.bx) * blockDim.x + threadIdx.x);
+  source_body(J.f, J.g, J.src, q, J.step, (lb - q * J.bx) * blockDim.x + threadIdx.x);
 }
 
 template <typename T>
