@@ -113,6 +113,10 @@ __device__ __forceinline__ void scatter_body(const FieldPtrs<T>& f, const Geom& 
   typedef int piece_t __attribute__((ext_vector_type(4)));
   using M = Mfma<T>;
   constexpr int P = ScatterCfg<T>::pairs;
+  // FP32 amplitudes are held 2^-9 of what they are: the largest weight of a window is at least
+  // 8^-3, so an amplitude beyond what is left (which counts as the limit: an infinity would
+  // spoil the bin) exceeds FP32 in its window
+  constexpr double kAmpScale = sizeof(T) == 4 ? 0x1p-9 : 1.0, kAmpMax = 3.4028234663852886e38;
   // a pair's weights in LDS: x at 0, y at kY, z at kZ, zeros between and behind
   constexpr int kY = 12, kZ = 24, kStride = 36;
   constexpr int kPer = 16 / (int)sizeof(T2);   // weights per 16-byte piece
@@ -186,9 +190,10 @@ __device__ __forceinline__ void scatter_body(const FieldPtrs<T>& f, const Geom& 
     if (lane < 3 * P) {
       // an amplitude that is no number adds nothing (times the zeros beside its window
       // it would spoil the whole bin), nor does what fills up the last step
-      const double v = amp0 * pg * pm;
-      sAmp[wave][apair][acomp] =
-          apair < cn && fabs(v) <= 1.7976931348623157e308 ? (T)v : T(0);
+      double v = amp0 * pg * pm * kAmpScale;
+      const bool on = apair < cn && fabs(v) <= 1.7976931348623157e308;
+      if constexpr (sizeof(T) == 4) v = fmin(fmax(v, -kAmpMax), kAmpMax);
+      sAmp[wave][apair][acomp] = on ? (T)v : T(0);
       if (acomp == 0) sOff[wave][apair] = aoff;
     }
   };
@@ -261,10 +266,10 @@ __device__ __forceinline__ void scatter_body(const FieldPtrs<T>& f, const Geom& 
   T ev[4][3], ei[4];
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    ei[r] = T(1);
+    ei[r] = T(1 / kAmpScale);
 #pragma unroll
     for (int c = 0; c < 3; ++c) ev[r][c] = r < nr ? f.E[c][cell + r * step] : T(0);
-    if (EPS && f.epsinv && r < nr) ei[r] = f.epsinv[cell + r * step];  // null: eps_r = 1
+    if (EPS && f.epsinv && r < nr) ei[r] *= f.epsinv[cell + r * step];  // null: eps_r = 1
   }
   sums(q1 - c0);
   if constexpr (kExact) {
