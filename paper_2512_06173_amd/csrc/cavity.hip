@@ -146,7 +146,7 @@ struct CavityStep {
   double* out;
   double* partial;
   double dt, w, V, eps;
-  int64_t n;
+  StepNo n;
   int last;
 };
 
@@ -186,6 +186,7 @@ __global__ __launch_bounds__(NT) void k_cavity_tls(TlsPtrs tls, CavityStep c, do
                                                    Series ser) {
   __shared__ double rx[NT / 64], ry[NT / 64];
   const int t = threadIdx.x, stride = gridDim.x * NT;
+  const int64_t n = c.n.get();
   int m = blockIdx.x * NT + t;
   // the first emitter's loads are in flight while the mode is formed
   auto load = [&](int k, int& e, double& w0, double d[3], double st[3]) {
@@ -213,15 +214,15 @@ __global__ __launch_bounds__(NT) void k_cavity_tls(TlsPtrs tls, CavityStep c, do
         Et[3 * (size_t)e + a] = et[a];
         mudot[3 * (size_t)e + a] = md[a];
       }
-    if (ser.pop_every > 0 && c.n % ser.pop_every == 0)
-      ser.pop[(c.n / ser.pop_every) * ser.npop + pop_off[e]] = st[0];
+    if (ser.pop_every > 0 && n % ser.pop_every == 0)
+      ser.pop[(n / ser.pop_every) * ser.npop + pop_off[e]] = st[0];
     const double mu = 2.0 * st[1];
     sx += mu * d[0] + 0.5 * c.dt * md[0];
     sy += mu * d[1] + 0.5 * c.dt * md[1];
     m += stride;
     if (m < tls.count) load(m, e, w0, d, st);
   }
-  if (!finite) flag_nonfinite(ser, c.n);
+  if (!finite) flag_nonfinite(ser, n);
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
     sx += __shfl_xor(sx, off, 64);
@@ -249,6 +250,7 @@ __device__ __forceinline__ void cavity_ml_body(const MlDev& ml, int first, int c
                                                const Series& ser, int t, double& sx, double& sy) {
   if (t >= count) return;
   const int m = first + t, e = ml.gid[m];
+  const int64_t n = c.n.get();
   MlState<N> s;
   ml_load<N>(ml, m, c.dt, s);
   bool finite = true;
@@ -259,12 +261,12 @@ __device__ __forceinline__ void cavity_ml_body(const MlDev& ml, int first, int c
       Et[3 * (size_t)e + a] = et[a];
       mudot[3 * (size_t)e + a] = tr * s.dip[a];
     }
-  if (ser.pop_every > 0 && c.n % ser.pop_every == 0) {
-    double* pop = ser.pop + (c.n / ser.pop_every) * ser.npop + pop_off[e];
+  if (ser.pop_every > 0 && n % ser.pop_every == 0) {
+    double* pop = ser.pop + (n / ser.pop_every) * ser.npop + pop_off[e];
 #pragma unroll
     for (int a = 1; a < N; ++a) pop[a - 1] = s.R[up<N>(a, a)];
   }
-  if (!finite) flag_nonfinite(ser, c.n);
+  if (!finite) flag_nonfinite(ser, n);
   double mu = 0.0;  // sum_ab R_ab M_ab
 #pragma unroll
   for (int a = 0; a < N; ++a)
@@ -304,7 +306,7 @@ __global__ __launch_bounds__(64) void k_cavity_ml(MlDev ml, MlLevels lv, CavityS
 }
 
 // One wavefront: the mode a step on (advance) from the partials, or the new d alone;
-// the step counter, when given.
+// the step counter, when given, moves n steps on.
 __global__ __launch_bounds__(64) void k_cavity_mode(const double* in, const double* partial,
                                                     int nb, double dt, double w, double eps,
                                                     int advance, double* out, int64_t* step,
@@ -319,7 +321,7 @@ __global__ __launch_bounds__(64) void k_cavity_mode(const double* in, const doub
   if (threadIdx.x == 0) {
 #pragma unroll
     for (int k = 0; k < 6; ++k) out[k] = st[k];
-    if (step) *step = n;
+    if (step) *step += n;
   }
 }
 
@@ -349,7 +351,7 @@ int cavity_partials(int ntls, const int* ml_range) {
 }
 
 hipError_t cavity_steps(const CavityDev& cav, const TlsPtrs& tls, const MlDev& ml,
-                        const int* range, double dt, int64_t n0, int64_t nsteps, double* Et,
+                        const int* range, double dt, int64_t nsteps, double* Et,
                         double* mudot, const int64_t* pop_off, const Series& ser, int64_t* step,
                         hipStream_t st) {
   int mlb = 0;
@@ -366,7 +368,7 @@ hipError_t cavity_steps(const CavityDev& cav, const TlsPtrs& tls, const MlDev& m
     // that folds nothing keeps it where the mode launch put it)
     c.out = cav.scratch + 6 * (k & 1);
     c.partial = cav.partial + (k & 1) * 2 * (size_t)cav.npart;
-    c.n = n0 + k;
+    c.n = {step, k};
     c.last = k + 1 == nsteps;
     if (tb > 0 && tls.count <= kWideBlocks)
       hipLaunchKernelGGL(k_cavity_tls<512>, dim3(tb), dim3(512), 0, st, tls, c, Et, mudot, pop_off,
@@ -383,7 +385,7 @@ hipError_t cavity_steps(const CavityDev& cav, const TlsPtrs& tls, const MlDev& m
       c.npend = nb;
     } else {  // (no emitters: the mode alone)
       hipLaunchKernelGGL(k_cavity_mode, dim3(1), dim3(64), 0, st, nb > 0 ? c.out : c.in, c.partial,
-                         nb, dt, cav.w, cav.eps, 1, cav.st, step, c.n + 1);
+                         nb, dt, cav.w, cav.eps, 1, cav.st, c.last ? step : nullptr, nsteps);
       c.in = cav.st;
       c.npend = 0;
     }

@@ -29,8 +29,8 @@ __global__ __launch_bounds__(256) void k_flux_partial(FieldPtrs<T> f, Geom g, Fl
 }
 template <typename T>
 __global__ __launch_bounds__(256) void k_finish(FieldPtrs<T> f, Geom g, FluxPlane fp, Series ser,
-                                                int64_t* step) {
-  finish_body(f, g, fp, ser, *step, step, 256);
+                                                StepNo n) {
+  finish_body(f, g, fp, ser, n.get(), n.counter, 256);
 }
 
 // Batched forms: kind 0 flux save, 1 flux partials, 2 finish (one block per job).
@@ -55,9 +55,9 @@ __global__ __launch_bounds__(256) void k_detect_batch(const FluxJob<T>* jobs, co
 template <typename T>
 __global__ __launch_bounds__(256) void k_energy_partial(FieldPtrs<T> old, FieldPtrs<T> cur,
                                                         size_t ncell, EnergyRec er,
-                                                        const int64_t* step) {
+                                                        StepNo n) {
   __shared__ double red[256];
-  if (*step % er.every != 0) return;  // uniform across the grid
+  if (n.get() % er.every != 0) return;  // uniform across the grid
   double s = 0.0;
   for (size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x; q < ncell;
        q += (size_t)gridDim.x * blockDim.x) {
@@ -77,9 +77,9 @@ __global__ __launch_bounds__(256) void k_energy_partial(FieldPtrs<T> old, FieldP
   if (threadIdx.x == 0) er.partial[blockIdx.x] = red[0];
 }
 
-__global__ __launch_bounds__(256) void k_energy_finish(EnergyRec er, const int64_t* step) {
+__global__ __launch_bounds__(256) void k_energy_finish(EnergyRec er, StepNo step) {
   __shared__ double red[256];
-  const int64_t n = *step;
+  const int64_t n = step.get();
   if (n % er.every != 0) return;
   const int t = threadIdx.x;
   double s = 0.0;
@@ -95,22 +95,22 @@ __global__ __launch_bounds__(256) void k_energy_finish(EnergyRec er, const int64
 
 template <typename T>
 static hipError_t launch_energy(const FieldPtrs<T>& old, const FieldPtrs<T>& cur, size_t ncell,
-                                const EnergyRec& er, const int64_t* step, hipStream_t st) {
+                                const EnergyRec& er, const StepNo& n, hipStream_t st) {
   hipLaunchKernelGGL(k_energy_partial<T>, dim3(er.nblocks), dim3(256), 0, st, old, cur, ncell, er,
-                     step);
+                     n);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_energy_finish, dim3(1), dim3(256), 0, st, er, step);
+  hipLaunchKernelGGL(k_energy_finish, dim3(1), dim3(256), 0, st, er, n);
   return hipGetLastError();
 }
 
 hipError_t energy_f64(const FieldPtrs<double>& old, const FieldPtrs<double>& cur, size_t ncell,
-                      const EnergyRec& er, const int64_t* step, hipStream_t st) {
-  return launch_energy<double>(old, cur, ncell, er, step, st);
+                      const EnergyRec& er, const StepNo& n, hipStream_t st) {
+  return launch_energy<double>(old, cur, ncell, er, n, st);
 }
 hipError_t energy_f32(const FieldPtrs<float>& old, const FieldPtrs<float>& cur, size_t ncell,
-                      const EnergyRec& er, const int64_t* step, hipStream_t st) {
-  return launch_energy<float>(old, cur, ncell, er, step, st);
+                      const EnergyRec& er, const StepNo& n, hipStream_t st) {
+  return launch_energy<float>(old, cur, ncell, er, n, st);
 }
 
 template <typename T>
@@ -131,13 +131,13 @@ static hipError_t launch_partial(const FieldPtrs<T>& f, const Geom& g, const Flu
 
 template <typename T>
 static hipError_t launch_finish(const FieldPtrs<T>& f, const Geom& g, const FluxPlane& fp,
-                                const Series& ser, int64_t* step, bool partials_done,
+                                const Series& ser, const StepNo& n, bool partials_done,
                                 hipStream_t st) {
   if (fp.on && !partials_done) {
     const hipError_t e = launch_partial<T>(f, g, fp, st);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_finish<T>, dim3(1), dim3(256), 0, st, f, g, fp, ser, step);
+  hipLaunchKernelGGL(k_finish<T>, dim3(1), dim3(256), 0, st, f, g, fp, ser, n);
   return hipGetLastError();
 }
 
@@ -158,12 +158,12 @@ hipError_t flux_partial_f32(const FieldPtrs<float>& f, const Geom& g, const Flux
   return launch_partial<float>(f, g, fp, st);
 }
 hipError_t finish_f64(const FieldPtrs<double>& f, const Geom& g, const FluxPlane& fp,
-                      const Series& ser, int64_t* step, bool partials_done, hipStream_t st) {
-  return launch_finish<double>(f, g, fp, ser, step, partials_done, st);
+                      const Series& ser, const StepNo& n, bool partials_done, hipStream_t st) {
+  return launch_finish<double>(f, g, fp, ser, n, partials_done, st);
 }
 hipError_t finish_f32(const FieldPtrs<float>& f, const Geom& g, const FluxPlane& fp,
-                      const Series& ser, int64_t* step, bool partials_done, hipStream_t st) {
-  return launch_finish<float>(f, g, fp, ser, step, partials_done, st);
+                      const Series& ser, const StepNo& n, bool partials_done, hipStream_t st) {
+  return launch_finish<float>(f, g, fp, ser, n, partials_done, st);
 }
 
 template <typename T>

@@ -23,8 +23,8 @@ void bin_shape(bool fp32, int G[3], int S[3]) {
 
 __global__ __launch_bounds__(256) void k_tls_step(TlsPtrs tls, double dt, const double* Et,
                                                   double* mudot, const int64_t* pop_off,
-                                                  Series ser, int64_t n) {
-  tls_body(tls, dt, Et, mudot, pop_off, ser, n, blockIdx.x * blockDim.x + threadIdx.x);
+                                                  Series ser, StepNo n) {
+  tls_body(tls, dt, Et, mudot, pop_off, ser, n.get(), blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 __global__ __launch_bounds__(256) void k_tls_batch(const TlsJob* jobs, const int* start,
@@ -135,7 +135,7 @@ __device__ __forceinline__ void scatter_body(const FieldPtrs<T>& f, const Geom& 
     } else {
       b -= nflux;
       const int q = b / more->sblocks;
-      source_body(f, g, more->src, q, more->step, (b - q * more->sblocks) * 256 + threadIdx.x);
+      source_body(f, g, more->src, q, more->n, (b - q * more->sblocks) * 256 + threadIdx.x);
     }
     return;
   }
@@ -318,7 +318,7 @@ __global__ __launch_bounds__(kThreads, ScatterCfg<T>::waves) void k_scatter_batc
 }
 
 hipError_t tls_step(const TlsPtrs& tls, double dt, const double* Et, double* mudot,
-                    const int64_t* pop_off, const Series& ser, int64_t n, hipStream_t st) {
+                    const int64_t* pop_off, const Series& ser, const StepNo& n, hipStream_t st) {
   if (tls.count == 0) return hipSuccess;
   hipLaunchKernelGGL(k_tls_step, dim3((tls.count + 255) / 256), dim3(256), 0, st, tls, dt, Et,
                      mudot, pop_off, ser, n);

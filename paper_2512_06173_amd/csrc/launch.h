@@ -23,7 +23,7 @@ hipError_t sweep_shell_f32(const FieldPtrs<float>& in, const FieldPtrs<float>& o
                            const Box& inner, bool h_pass, hipStream_t st);
 // Multilevel step of every slot; range[n]..range[n+1] are the slots with n levels.
 hipError_t ml_step(const MlDev& ml, const int* range, double dt, const double* Et, double* mudot,
-                   const int64_t* pop_off, const Series& ser, int64_t n, hipStream_t st);
+                   const int64_t* pop_off, const Series& ser, const StepNo& n, hipStream_t st);
 // nsteps classical-path steps of every emitter under f; the states after every step go
 // to out (nsteps x two-level emitters x 3, null: not recorded), the last step's E~ and
 // mu_dot to last and mudot (emitter-id order).
@@ -31,9 +31,9 @@ hipError_t prescribed_steps(const TlsPtrs& tls, const MlDev& ml, const int* rang
                             PrescribedField f, int64_t nsteps, double* last, double* mudot,
                             double* out, const Series& ser, const int64_t* step, hipStream_t st);
 hipError_t sources_f64(const FieldPtrs<double>& f, const Geom& g, const SourceSet& src,
-                       const int64_t* step, hipStream_t st);
+                       const StepNo& n, hipStream_t st);
 hipError_t sources_f32(const FieldPtrs<float>& f, const Geom& g, const SourceSet& src,
-                       const int64_t* step, hipStream_t st);
+                       const StepNo& n, hipStream_t st);
 // The frame of y and z CPML layers around an interior box (which the fused sweep
 // covers with its lean kernel), by the full fused kernel in one launch.
 hipError_t sweep_frame_f64(const FieldPtrs<double>& a, const FieldPtrs<double>& b, const Geom& g,
@@ -69,9 +69,9 @@ hipError_t flux_save_f32(const FieldPtrs<float>& f, const Geom& g, const FluxPla
 // W^n from the spare (E^n, H^{n-1/2}) and current (H^{n+1/2}) buffers of the fused
 // sweep, into er.series on steps with n % er.every == 0.
 hipError_t energy_f64(const FieldPtrs<double>& old, const FieldPtrs<double>& cur, size_t ncell,
-                      const EnergyRec& er, const int64_t* step, hipStream_t st);
+                      const EnergyRec& er, const StepNo& n, hipStream_t st);
 hipError_t energy_f32(const FieldPtrs<float>& old, const FieldPtrs<float>& cur, size_t ncell,
-                      const EnergyRec& er, const int64_t* step, hipStream_t st);
+                      const EnergyRec& er, const StepNo& n, hipStream_t st);
 // partials_done: the flux partials of this step are formed already (by the scatter
 // launch), so only the finishing block runs
 hipError_t flux_partial_f64(const FieldPtrs<double>& f, const Geom& g, const FluxPlane& fp,
@@ -79,9 +79,9 @@ hipError_t flux_partial_f64(const FieldPtrs<double>& f, const Geom& g, const Flu
 hipError_t flux_partial_f32(const FieldPtrs<float>& f, const Geom& g, const FluxPlane& fp,
                             hipStream_t st);
 hipError_t finish_f64(const FieldPtrs<double>& f, const Geom& g, const FluxPlane& fp,
-                      const Series& ser, int64_t* step, bool partials_done, hipStream_t st);
+                      const Series& ser, const StepNo& n, bool partials_done, hipStream_t st);
 hipError_t finish_f32(const FieldPtrs<float>& f, const Geom& g, const FluxPlane& fp,
-                      const Series& ser, int64_t* step, bool partials_done, hipStream_t st);
+                      const Series& ser, const StepNo& n, bool partials_done, hipStream_t st);
 
 // fp: when given, the same launch saves the flux plane's E^n (needs ngather > 0)
 hipError_t bin_gather_f64(const FieldPtrs<double>& f, const Geom& g, const BinPtrs& b,
@@ -92,7 +92,7 @@ hipError_t bin_gather_f32(const FieldPtrs<float>& f, const Geom& g, const BinPtr
                           hipStream_t st);
 // Two-level step n of every two-level emitter under E~ (emitter-id order).
 hipError_t tls_step(const TlsPtrs& tls, double dt, const double* Et, double* mudot,
-                    const int64_t* pop_off, const Series& ser, int64_t n, hipStream_t st);
+                    const int64_t* pop_off, const Series& ser, const StepNo& n, hipStream_t st);
 // fp: when given, fp->nblocks more workgroups of the same launch form the flux
 // partials of the plane (no window may reach the plane's E cells)
 hipError_t bin_scatter_f64(const FieldPtrs<double>& f, const Geom& g, const BinPtrs& b,
@@ -196,10 +196,9 @@ hipError_t pole_post_f64(const PoleDev& p, const FieldPtrs<double>& f, const Geo
                          const double* epsinv, hipStream_t st);
 hipError_t pole_post_f32(const PoleDev& p, const FieldPtrs<float>& f, const Geom& g,
                          const float* epsinv, hipStream_t st);
-// Single-mode cavity: nsteps steps from step number n0 (E~ and mu_dot of the last one
-// are kept), leaving the mode and the step counter at their end.
+// Single-mode cavity: nsteps steps (E~ and mu_dot of the last one are kept), leaving the mode and the step counter at their end.
 hipError_t cavity_steps(const CavityDev& c, const TlsPtrs& tls, const MlDev& ml, const int* range,
-                        double dt, int64_t n0, int64_t nsteps, double* Et, double* mudot,
+                        double dt, int64_t nsteps, double* Et, double* mudot,
                         const int64_t* pop_off, const Series& ser, int64_t* step, hipStream_t st);
 // Partial sums that a step (or cavity_set_dipole) leaves: the size of each of the two
 // sets of CavityDev::partial.

@@ -215,6 +215,15 @@ struct MlDev {
   double* rho;          // [2 kMaxLevels^2][count]
 };
 
+// Number of the step that a launch belongs to: the device's counter, which moves on when the
+// last step of a call is closed, plus the steps of the call before this one.  Nothing is
+// fixed when the launch is made, so a call that was captured replays as the steps that follow.
+struct StepNo {
+  int64_t* counter;
+  int64_t ahead;
+  __device__ __forceinline__ int64_t get() const { return *counter + ahead; }
+};
+
 struct Series {
   double* probe;       // [nprobe][cap]
   int nprobe;
@@ -475,7 +484,7 @@ struct SourceJob {
   FieldPtrs<T> f;
   Geom g;
   SourceSet src;
-  const int64_t* step;
+  int64_t* step;
   int bx;       // blocks per source
   int nblocks;  // bx * src.count
 };

@@ -64,18 +64,18 @@ __device__ __forceinline__ void ml_body(const MlDev& ml, int first, int count, d
 template <int N>
 __global__ __launch_bounds__(64) void k_ml_step(MlDev ml, int first, int count, double dt,
                                                 const double* Et, double* mudot,
-                                                const int64_t* pop_off, Series ser, int64_t n) {
-  ml_body<N>(ml, first, count, dt, Et, mudot, pop_off, ser, n,
+                                                const int64_t* pop_off, Series ser, StepNo n) {
+  ml_body<N>(ml, first, count, dt, Et, mudot, pop_off, ser, n.get(),
              blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 __global__ __launch_bounds__(64) void k_ml_levels(MlDev ml, MlLevels lv, double dt,
                                                   const double* Et, double* mudot,
                                                   const int64_t* pop_off, Series ser,
-                                                  int64_t n) {
+                                                  StepNo n) {
   const int b = blockIdx.x;
 #define MLK_LEVEL(N)                                                                  \
-  ml_body<N>(ml, lv.first[N], lv.count[N], dt, Et, mudot, pop_off, ser, n,            \
+  ml_body<N>(ml, lv.first[N], lv.count[N], dt, Et, mudot, pop_off, ser, n.get(),      \
              (b - lv.start[N]) * 64 + (int)threadIdx.x)
   if (b < lv.start[5]) MLK_LEVEL(6);
   else if (b < lv.start[4]) MLK_LEVEL(5);
@@ -112,7 +112,7 @@ hipError_t ml_batch(const MlJob* jobs, const int* start, int njobs, int nblocks,
 }
 
 hipError_t ml_step(const MlDev& ml, const int* range, double dt, const double* Et, double* mudot,
-                   const int64_t* pop_off, const Series& ser, int64_t n, hipStream_t st) {
+                   const int64_t* pop_off, const Series& ser, const StepNo& n, hipStream_t st) {
   int total = 0;
   const MlLevels lv = ml_levels(range, &total);
   if (total == 0) return hipSuccess;

@@ -1052,9 +1052,10 @@ FieldPtrs<T> sweep_reads(const mlk_sim* s) {
   return f;
 }
 
-// side: work for extra workgroups of the fused launch; sources: whether to add the sources
+// Step n.  side: work for extra workgroups of the fused launch; sources: whether to add the
+// sources
 template <typename T>
-mlk_status sweep(mlk_sim* s, SideWork side, bool sources) {
+mlk_status sweep(mlk_sim* s, SideWork side, bool sources, const StepNo& n) {
   constexpr bool f32 = sizeof(T) == 4;
   const FieldPtrs<T> f = field_ptrs<T>(s);
   if (s->desc.sweep == MLK_SWEEP_FUSED) {
@@ -1104,8 +1105,8 @@ mlk_status sweep(mlk_sim* s, SideWork side, bool sources) {
   if (sources && s->src.count > 0) {
     const FieldPtrs<T> cur = field_ptrs<T>(s);
     const int t0 = mark_begin(s, MLK_PHASE_SOURCES);
-    if constexpr (f32) HIPCHK(sources_f32(cur, s->g, s->src, s->d_step, s->stream));
-    else HIPCHK(sources_f64(cur, s->g, s->src, s->d_step, s->stream));
+    if constexpr (f32) HIPCHK(sources_f32(cur, s->g, s->src, n, s->stream));
+    else HIPCHK(sources_f64(cur, s->g, s->src, n, s->stream));
     mark_end(s, MLK_PHASE_SOURCES, t0);
   }
   return MLK_OK;
@@ -1151,12 +1152,10 @@ mlk_status enqueue_steps(mlk_sim* s, int64_t nsteps) {
     more.fp = s->fp;
   }
   if (fold_src) more.src = s->src;
-  more.step = s->d_step;
   // The fused sweep's launch also takes the two-level steps (the scatter after it needs
   // them, the sweep does not) and closes the step before; the last step of the call is
-  // closed by a launch of its own.  Kernels take the step number by value, as the
-  // device's counter is one step behind until the sweep.  With the emitter or detector
-  // phase timed, both get launches of their own, which the phase's events enclose.
+  // closed by a launch of its own, which moves the device's step counter on.  With the emitter
+  // or detector phase timed, both get launches of their own, which the phase's events enclose.
   const bool fold = s->desc.sweep == MLK_SWEEP_FUSED &&
                     !(s->timing & (1 << MLK_PHASE_EMITTERS | 1 << MLK_PHASE_DETECTORS));
   SideWork side{};
@@ -1167,11 +1166,11 @@ mlk_status enqueue_steps(mlk_sim* s, int64_t nsteps) {
     side.pop_off = s->d_popoff;
     side.ser = ser;
     side.fp = s->fp;
-    side.step = s->d_step;
   }
   for (int64_t q = 0; q < nsteps; ++q) {
-    const int64_t n = s->host_step + q;
+    const StepNo n{s->d_step, fold ? q : 0};
     side.n = n;
+    more.n = n;
     side.finish = fold && q > 0;
     FieldPtrs<T> f = field_ptrs<T>(s);
     if (s->fp.on && !fold_save) {
@@ -1199,13 +1198,13 @@ mlk_status enqueue_steps(mlk_sim* s, int64_t nsteps) {
       else HIPCHK(pole_pre_f64(s->pole[k], f, s->g, s->stream));
     }
     mark_end(s, MLK_PHASE_POLES, t0);
-    STCHK(sweep<T>(s, side, !fold_src));
+    STCHK(sweep<T>(s, side, !fold_src, n));
     f = field_ptrs<T>(s);
     if (s->er.every > 0) {
       // W^n: E^n and H^{n-1/2} are in the spare buffers now, H^{n+1/2} in the current
       t0 = mark_begin(s, MLK_PHASE_DETECTORS);
-      if constexpr (f32) HIPCHK(energy_f32(spare_ptrs<T>(s), f, s->ncell, s->er, s->d_step, s->stream));
-      else HIPCHK(energy_f64(spare_ptrs<T>(s), f, s->ncell, s->er, s->d_step, s->stream));
+      if constexpr (f32) HIPCHK(energy_f32(spare_ptrs<T>(s), f, s->ncell, s->er, n, s->stream));
+      else HIPCHK(energy_f64(spare_ptrs<T>(s), f, s->ncell, s->er, n, s->stream));
       mark_end(s, MLK_PHASE_DETECTORS, t0);
     }
     t0 = mark_begin(s, MLK_PHASE_SCATTER);
@@ -1238,8 +1237,8 @@ mlk_status enqueue_steps(mlk_sim* s, int64_t nsteps) {
       continue;
     }
     t0 = mark_begin(s, MLK_PHASE_DETECTORS);
-    if constexpr (f32) HIPCHK(finish_f32(f, s->g, s->fp, ser, s->d_step, fold_flux, s->stream));
-    else HIPCHK(finish_f64(f, s->g, s->fp, ser, s->d_step, fold_flux, s->stream));
+    if constexpr (f32) HIPCHK(finish_f32(f, s->g, s->fp, ser, n, fold_flux, s->stream));
+    else HIPCHK(finish_f64(f, s->g, s->fp, ser, n, fold_flux, s->stream));
     mark_end(s, MLK_PHASE_DETECTORS, t0);
   }
   return MLK_OK;
@@ -1251,8 +1250,8 @@ mlk_status enqueue_cavity_steps(mlk_sim* s, int64_t nsteps) {
   const int64_t per = s->timing & (1 << MLK_PHASE_EMITTERS) ? 1 : nsteps;
   for (int64_t q = 0; q < nsteps; q += per) {
     const int t0 = mark_begin(s, MLK_PHASE_EMITTERS);
-    HIPCHK(cavity_steps(s->cav, tls_ptrs(s), ml_dev(s), s->ml_range, s->g.dt, s->host_step + q,
-                        per, s->d_Et, s->d_mudot, s->d_popoff, series_of(s), s->d_step,
+    HIPCHK(cavity_steps(s->cav, tls_ptrs(s), ml_dev(s), s->ml_range, s->g.dt, per, s->d_Et,
+                        s->d_mudot, s->d_popoff, series_of(s), s->d_step,
                         s->stream));
     mark_end(s, MLK_PHASE_EMITTERS, t0);
   }

@@ -33,7 +33,7 @@ __device__ __forceinline__ void tls_body(const TlsPtrs& tls, double dt, const do
 // One workgroup of nt threads (a multiple of 64 up to 1024) closes step n: probe
 // samples, the flux total, then the step counter moves on.  The flux partials are
 // summed over 256 virtual lanes whatever nt is, so the total does not depend on the
-// launch that closes the step.
+// launch that closes the step.  The counter moves when given (by the last step of a call).
 template <typename T>
 __device__ __forceinline__ void finish_body(const FieldPtrs<T>& f, const Geom& g,
                                             const FluxPlane& fp, const Series& ser, int64_t n,
@@ -66,7 +66,7 @@ __device__ __forceinline__ void finish_body(const FieldPtrs<T>& f, const Geom& g
     }
   }
   __syncthreads();  // every thread may have read n from the counter
-  if (t == 0) *step = n + 1;
+  if (t == 0 && step) *step = n + 1;
 }
 
 // Extra workgroups of the fused sweep's launch at step n, behind the sweep's own: they
@@ -84,8 +84,7 @@ struct SideWork {
   const int64_t* pop_off;
   Series ser;
   FluxPlane fp;
-  int64_t n;
-  int64_t* step;
+  StepNo n;
   ShellMap shell;    // H pass over the cells outside the fused box (total 0: none)
 };
 
@@ -93,9 +92,9 @@ template <typename T, int NT, bool STREAM>
 __device__ __forceinline__ void side_body(const SideWork& w, const FieldPtrs<T>& f,
                                           const FieldPtrs<T>& out, const Geom& g, int b) {
   if (b < w.tls_blocks)
-    tls_body(w.tls, g.dt, w.Et, w.mudot, w.pop_off, w.ser, w.n, b * NT + (int)threadIdx.x);
+    tls_body(w.tls, g.dt, w.Et, w.mudot, w.pop_off, w.ser, w.n.get(), b * NT + (int)threadIdx.x);
   else if (b < w.tls_blocks + w.finish)
-    finish_body(f, g, w.fp, w.ser, w.n - 1, w.step, NT);
+    finish_body(f, g, w.fp, w.ser, w.n.get() - 1, nullptr, NT);
   else {
     const unsigned t = (unsigned)(b - w.tls_blocks - w.finish) * NT + threadIdx.x;
     if ((long long)t >= w.shell.total) return;
@@ -118,7 +117,7 @@ struct ScatterMore {
   int flux, sblocks;
   FluxPlane fp;
   SourceSet src;
-  const int64_t* step;
+  StepNo n;
 };
 
 // What rides in a batch's fused launch: its tables of two-level steps and of shells (for

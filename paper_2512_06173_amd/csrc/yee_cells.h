@@ -92,8 +92,7 @@ __device__ __forceinline__ bool source_covers(const Source& s, int i, int j, int
 // behind it there, in their order, so that a cell has one writer.
 template <typename T>
 __device__ __forceinline__ void source_body(const FieldPtrs<T>& f, const Geom& g,
-                                            const SourceSet& src, int q, const int64_t* step,
-                                            int t) {
+                                            const SourceSet& src, int q, const StepNo& n, int t) {
   const Source& s = src.s[q];
   int i, j, k;
   if (s.kind == 0) {
@@ -115,7 +114,7 @@ __device__ __forceinline__ void source_body(const FieldPtrs<T>& f, const Geom& g
   if (tangential_wall(g, s.comp, i, j, k)) return;
   for (int o = 0; o < q; ++o)
     if (src.s[o].comp == s.comp && source_covers(src.s[o], i, j, k)) return;
-  const double tm = ((double)(*step) + 0.5) * g.dt;
+  const double tm = ((double)n.get() + 0.5) * g.dt;
   const size_t id = cell_index(g, i, j, k);
   const double ei = f.epsinv ? (double)f.epsinv[id] : 1.0;  // null: eps_r = 1 everywhere
   T e = f.E[s.comp][id];

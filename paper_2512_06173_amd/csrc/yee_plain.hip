@@ -51,10 +51,10 @@ __global__ __launch_bounds__(256) void k_update_shell_batch(const ShellJob<T>* j
 }
 
 template <typename T>
-__global__ void k_sources(FieldPtrs<T> f, Geom g, SourceSet src, const int64_t* step) {
+__global__ void k_sources(FieldPtrs<T> f, Geom g, SourceSet src, StepNo n) {
   const int q = blockIdx.y;
   if (q >= src.count) return;
-  source_body(f, g, src, q, step, blockIdx.x * blockDim.x + threadIdx.x);
+  source_body(f, g, src, q, n, blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 template <typename T>
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(256) void k_sources_batch(const SourceJob<T>* jobs,
   const int lb = blockIdx.x - start[jb];
   if (lb >= J.nblocks) return;
   const int q = lb / J.bx;
-  source_body(J.f, J.g, J.src, q, J.step, (lb - q * J.bx) * blockDim.x + threadIdx.x);
+  source_body(J.f, J.g, J.src, q, StepNo{J.step, 0}, (lb - q * J.bx) * blockDim.x + threadIdx.x);
 }
 
 template <typename T>
@@ -128,10 +128,10 @@ static hipError_t launch_shell(const FieldPtrs<T>& in, const FieldPtrs<T>& out, 
 
 template <typename T>
 static hipError_t launch_sources(const FieldPtrs<T>& f, const Geom& g, const SourceSet& src,
-                                 const int64_t* step, hipStream_t st) {
+                                 const StepNo& n, hipStream_t st) {
   if (src.count == 0) return hipSuccess;
   hipLaunchKernelGGL(k_sources<T>, dim3(source_blocks(g, src), src.count), dim3(256), 0, st, f, g,
-                     src, step);
+                     src, n);
   return hipGetLastError();
 }
 
@@ -187,12 +187,12 @@ hipError_t sources_batch_f32(const SourceJob<float>* jobs, const int* start, int
   return launch_sources_batch<float>(jobs, start, njobs, nblocks, st);
 }
 hipError_t sources_f64(const FieldPtrs<double>& f, const Geom& g, const SourceSet& src,
-                       const int64_t* step, hipStream_t st) {
-  return launch_sources<double>(f, g, src, step, st);
+                       const StepNo& n, hipStream_t st) {
+  return launch_sources<double>(f, g, src, n, st);
 }
 hipError_t sources_f32(const FieldPtrs<float>& f, const Geom& g, const SourceSet& src,
-                       const int64_t* step, hipStream_t st) {
-  return launch_sources<float>(f, g, src, step, st);
+                       const StepNo& n, hipStream_t st) {
+  return launch_sources<float>(f, g, src, n, st);
 }
 
 }  // namespace mlk

@@ -1,0 +1,72 @@
+"""mlk_step captured by the caller into a graph on the sim's stream: every replay is the steps
+that follow (the source's time, the series rows and the step counter move on), checked
+against a sim that steps eagerly, with eager steps and read-backs between the replays."""
+import numpy as np
+import pytest
+
+from paper_2512_06173_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def mlk():
+    from paper_2512_06173_amd import mlk as m
+    return m
+
+
+def build(what, precision, stream=None):
+    rng = np.random.default_rng(3)
+    s = mlk().Simulation((40, 28, 32), precision=precision, bc=("cpml",) * 6, cpml=(5,) * 6,
+                         sweep="plain" if what == "plain" else "fused", stream=stream)
+    t = W.tls_ensemble(rng, 40, 9.0, 19.0, "superposition")
+    s.add_tls(t.pos, t.sigma, t.gamma, t.omega0, t.dipole, t.rho0)
+    if what != "tls":
+        m = W.random_multilevel(rng, 9, rng.uniform(9.0, 19.0, (9, 3)))
+        s.add_multilevel(m.nlev, m.energies, m.mop, m.dipole, m.gphi, m.rho0, m.pos, m.sigma,
+                         m.gamma)
+    s.record_populations(1)
+    if what == "cavity":
+        s.set_cavity(0.25, 50.0, (0.4, 0.1), (0.0, 0.2))
+        return s
+    s.add_plane_source(2, 24 if what == "tls" else 12, 1, 1.0, 0.3, 6.0, 2.0)
+    s.add_probe(1, (20, 14, 16))
+    s.add_flux_plane(2, 25)
+    return s
+
+
+def state(s, what):
+    out = [s.tls_state(0, 40)]
+    return out + ([s.cavity()] if what == "cavity" else s.fields())
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("what", ["tls", "mixed", "plain", "cavity"])
+def test_replays_are_the_steps_that_follow(what, precision):
+    import torch
+    st = torch.cuda.Stream()
+    sim, ref = build(what, precision, st.cuda_stream), build(what, precision)
+    sim.step(2)
+    sim.sync()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=st):
+        sim.step(4)
+    ref.step(2)
+    for q in range(4):
+        print(f"[capture] {what} {precision} replay {q}", flush=True)
+        with torch.cuda.stream(st):
+            g.replay()
+        ref.step(4)
+        assert all(np.array_equal(a, b) for a, b in zip(state(sim, what), state(ref, what)))
+        if q == 1:
+            sim.step(2)
+            ref.step(2)
+            assert all(np.array_equal(a, b) for a, b in zip(state(sim, what), state(ref, what)))
+    # the rows that the sim's own count of steps (2 + 4 + 2) covers
+    n = sim.step_count
+    assert n == 8 and np.array_equal(sim.populations(), ref.populations()[:n])
+    if what != "cavity":
+        assert np.array_equal(sim.probe(0), ref.probe(0)[:n])
+        assert np.array_equal(sim.flux_series(), ref.flux_series()[:n])
+        assert sim.flux_total() == ref.flux_total()
+    sim.close()
+    ref.close()
