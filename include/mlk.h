@@ -38,7 +38,11 @@
  *
  * Streams: all work is enqueued on the stream given in the grid description
  * (a hipStream_t, NULL = a stream the library creates).  mlk_step is
- * asynchronous; getters synchronise that stream.
+ * asynchronous; getters synchronise that stream.  A caller may capture it into a
+ * graph there (with the fused sweep, whose two field buffers alternate, an even number
+ * of steps): every replay is the steps that follow.  The sim's own count of steps,
+ * which mlk_step_count and the series' lengths use, sees the captured call alone, and
+ * series keep what earlier calls have made room for.
  */
 #ifndef MLK_H
 #define MLK_H

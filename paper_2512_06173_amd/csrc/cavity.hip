@@ -186,7 +186,6 @@ __global__ __launch_bounds__(NT) void k_cavity_tls(TlsPtrs tls, CavityStep c, do
                                                    Series ser) {
   __shared__ double rx[NT / 64], ry[NT / 64];
   const int t = threadIdx.x, stride = gridDim.x * NT;
-  const int64_t n = c.n.get();
   int m = blockIdx.x * NT + t;
   // the first emitter's loads are in flight while the mode is formed
   auto load = [&](int k, int& e, double& w0, double d[3], double st[3]) {
@@ -214,15 +213,14 @@ __global__ __launch_bounds__(NT) void k_cavity_tls(TlsPtrs tls, CavityStep c, do
         Et[3 * (size_t)e + a] = et[a];
         mudot[3 * (size_t)e + a] = md[a];
       }
-    if (ser.pop_every > 0 && n % ser.pop_every == 0)
-      ser.pop[(n / ser.pop_every) * ser.npop + pop_off[e]] = st[0];
+    if (double* pop = pop_record(ser, c.n)) pop[pop_off[e]] = st[0];
     const double mu = 2.0 * st[1];
     sx += mu * d[0] + 0.5 * c.dt * md[0];
     sy += mu * d[1] + 0.5 * c.dt * md[1];
     m += stride;
     if (m < tls.count) load(m, e, w0, d, st);
   }
-  if (!finite) flag_nonfinite(ser, n);
+  if (!finite) flag_nonfinite(ser, c.n.get());
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
     sx += __shfl_xor(sx, off, 64);
@@ -250,7 +248,6 @@ __device__ __forceinline__ void cavity_ml_body(const MlDev& ml, int first, int c
                                                const Series& ser, int t, double& sx, double& sy) {
   if (t >= count) return;
   const int m = first + t, e = ml.gid[m];
-  const int64_t n = c.n.get();
   MlState<N> s;
   ml_load<N>(ml, m, c.dt, s);
   bool finite = true;
@@ -261,12 +258,12 @@ __device__ __forceinline__ void cavity_ml_body(const MlDev& ml, int first, int c
       Et[3 * (size_t)e + a] = et[a];
       mudot[3 * (size_t)e + a] = tr * s.dip[a];
     }
-  if (ser.pop_every > 0 && n % ser.pop_every == 0) {
-    double* pop = ser.pop + (n / ser.pop_every) * ser.npop + pop_off[e];
+  if (double* pop = pop_record(ser, c.n)) {
+    pop += pop_off[e];
 #pragma unroll
     for (int a = 1; a < N; ++a) pop[a - 1] = s.R[up<N>(a, a)];
   }
-  if (!finite) flag_nonfinite(ser, n);
+  if (!finite) flag_nonfinite(ser, c.n.get());
   double mu = 0.0;  // sum_ab R_ab M_ab
 #pragma unroll
   for (int a = 0; a < N; ++a)

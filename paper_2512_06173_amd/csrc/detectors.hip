@@ -90,7 +90,7 @@ __global__ __launch_bounds__(256) void k_energy_finish(EnergyRec er, StepNo step
     if (t < w) red[t] += red[t + w];
     __syncthreads();
   }
-  if (t == 0) er.series[n / er.every] = red[0] * er.dv;
+  if (t == 0 && n / er.every < er.cap) er.series[n / er.every] = red[0] * er.dv;
 }
 
 template <typename T>

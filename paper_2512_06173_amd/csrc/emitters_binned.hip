@@ -24,7 +24,7 @@ void bin_shape(bool fp32, int G[3], int S[3]) {
 __global__ __launch_bounds__(256) void k_tls_step(TlsPtrs tls, double dt, const double* Et,
                                                   double* mudot, const int64_t* pop_off,
                                                   Series ser, StepNo n) {
-  tls_body(tls, dt, Et, mudot, pop_off, ser, n.get(), blockIdx.x * blockDim.x + threadIdx.x);
+  tls_body(tls, dt, Et, mudot, pop_off, ser, n, blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 __global__ __launch_bounds__(256) void k_tls_batch(const TlsJob* jobs, const int* start,
@@ -33,7 +33,7 @@ __global__ __launch_bounds__(256) void k_tls_batch(const TlsJob* jobs, const int
   const TlsJob J = load_job(jobs, j);
   const int lb = blockIdx.x - start[j];
   if (lb >= J.nblocks) return;
-  tls_body(J.tls, J.dt, J.Et, J.mudot, J.pop_off, J.ser, *J.step,
+  tls_body(J.tls, J.dt, J.Et, J.mudot, J.pop_off, J.ser, StepNo{J.step, 0},
            lb * blockDim.x + threadIdx.x);
 }
 

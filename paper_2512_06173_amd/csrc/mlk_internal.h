@@ -221,7 +221,15 @@ struct MlDev {
 struct StepNo {
   int64_t* counter;
   int64_t ahead;
-  __device__ __forceinline__ int64_t get() const { return *counter + ahead; }
+  // (a scalar load: no launch that uses the number moves the counter before every wavefront
+  // has read it, and as a scalar it costs emitter kernels neither registers nor VALU divisions)
+  __device__ __forceinline__ int64_t get() const {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return *(const __attribute__((address_space(4))) int64_t*)counter + ahead;
+#else
+    return *counter + ahead;
+#endif
+  }
 };
 
 struct Series {
@@ -238,6 +246,16 @@ struct Series {
   // step at which an emitter state, dipole rate, probe sample or flux value was not
   unsigned long long* numeric;
 };
+
+// The record of the population series that a step fills; null where it records none, and past
+// the room that the host has made (only replays of a captured call get there).
+__device__ __forceinline__ double* pop_record(const Series& ser, const StepNo& step) {
+  if (ser.pop_every <= 0) return nullptr;
+  const int64_t n = step.get();
+  if (n % ser.pop_every != 0) return nullptr;
+  const int64_t r = n / ser.pop_every;
+  return r < ser.pop_cap ? ser.pop + r * ser.npop : nullptr;
+}
 
 // Record step n as the first non-finite one.  Steps n - 1 and n can be checked by the
 // same launch, so the earliest of the competing records is kept.
@@ -286,7 +304,8 @@ struct EnergyRec {
   int every;
   double* partial;  // per-block partial sums (FP64)
   int nblocks;
-  double* series;   // [records]
+  double* series;   // [cap]
+  int64_t cap;      // records that the series has room for
   double dv;        // cell volume dx^3
 };
 
@@ -506,7 +525,7 @@ struct TlsJob {
   double* mudot;
   const int64_t* pop_off;
   Series ser;
-  const int64_t* step;
+  int64_t* step;
   int nblocks;
 };
 
@@ -518,7 +537,7 @@ struct MlJob {
   double* mudot;
   const int64_t* pop_off;
   Series ser;
-  const int64_t* step;
+  int64_t* step;
   int nblocks;
 };
 

@@ -41,7 +41,7 @@ constexpr int kMlOneLaunchBlocks = 8192;
 template <int N>
 __device__ __forceinline__ void ml_body(const MlDev& ml, int first, int count, double dt,
                                         const double* Et, double* mudot, const int64_t* pop_off,
-                                        const Series& ser, int64_t n, int t) {
+                                        const Series& ser, const StepNo& n, int t) {
   const int m = first + t;
   if (t >= count) return;
   const int e = ml.gid[m];
@@ -51,12 +51,12 @@ __device__ __forceinline__ void ml_body(const MlDev& ml, int first, int count, d
   bool finite = true;
   const double tr = ml_advance<N>(s, et, dt, finite);
   ml_store<N>(ml, m, s);
-  if (ser.pop_every > 0 && n % ser.pop_every == 0) {
-    double* pop = ser.pop + (n / ser.pop_every) * ser.npop + pop_off[e];
+  if (double* pop = pop_record(ser, n)) {
+    pop += pop_off[e];
 #pragma unroll
     for (int a = 1; a < N; ++a) pop[a - 1] = s.R[up<N>(a, a)];
   }
-  if (!finite) flag_nonfinite(ser, n);
+  if (!finite) flag_nonfinite(ser, n.get());
 #pragma unroll
   for (int c = 0; c < 3; ++c) mudot[3 * e + c] = tr * s.dip[c];
 }
@@ -65,7 +65,7 @@ template <int N>
 __global__ __launch_bounds__(64) void k_ml_step(MlDev ml, int first, int count, double dt,
                                                 const double* Et, double* mudot,
                                                 const int64_t* pop_off, Series ser, StepNo n) {
-  ml_body<N>(ml, first, count, dt, Et, mudot, pop_off, ser, n.get(),
+  ml_body<N>(ml, first, count, dt, Et, mudot, pop_off, ser, n,
              blockIdx.x * blockDim.x + threadIdx.x);
 }
 
@@ -75,7 +75,7 @@ __global__ __launch_bounds__(64) void k_ml_levels(MlDev ml, MlLevels lv, double 
                                                   StepNo n) {
   const int b = blockIdx.x;
 #define MLK_LEVEL(N)                                                                  \
-  ml_body<N>(ml, lv.first[N], lv.count[N], dt, Et, mudot, pop_off, ser, n.get(),      \
+  ml_body<N>(ml, lv.first[N], lv.count[N], dt, Et, mudot, pop_off, ser, n,            \
              (b - lv.start[N]) * 64 + (int)threadIdx.x)
   if (b < lv.start[5]) MLK_LEVEL(6);
   else if (b < lv.start[4]) MLK_LEVEL(5);
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(64) void k_ml_batch(const MlJob* jobs, const int* s
   const MlJob J = load_job(jobs, j);
   const int lb = blockIdx.x - start[j];
   if (lb >= J.nblocks) return;
-  ml_body<N>(J.ml, J.first, J.count, J.dt, J.Et, J.mudot, J.pop_off, J.ser, *J.step,
+  ml_body<N>(J.ml, J.first, J.count, J.dt, J.Et, J.mudot, J.pop_off, J.ser, StepNo{J.step, 0},
              lb * blockDim.x + threadIdx.x);
 }
 

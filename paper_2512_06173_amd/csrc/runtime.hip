@@ -239,7 +239,6 @@ struct mlk_sim {
   int64_t pop_cap = 0;
 
   EnergyRec er{};          // discrete field energy detector (off: er.every == 0)
-  int64_t energy_cap = 0;  // records
 
   int64_t* d_step = nullptr;
   int64_t host_step = 0;
@@ -826,9 +825,9 @@ mlk_status reserve_series(mlk_sim* s, int64_t nsteps) {
   }
   if (s->er.every > 0) {
     const int64_t rec = (need + s->er.every - 1) / s->er.every;
-    if (rec > s->energy_cap) {
+    if (rec > s->er.cap) {
       STCHK(sync_sim(s));
-      int64_t cap = s->energy_cap ? 2 * s->energy_cap : 64;
+      int64_t cap = s->er.cap ? 2 * s->er.cap : 64;
       while (cap < rec) cap *= 2;
       double* ne = nullptr;
       HIPCHK(dalloc(&ne, (size_t)cap * sizeof(double)));
@@ -838,7 +837,7 @@ mlk_status reserve_series(mlk_sim* s, int64_t nsteps) {
                          hipMemcpyDeviceToDevice));
       dfree(s->er.series);
       s->er.series = ne;
-      s->energy_cap = cap;
+      s->er.cap = cap;
     }
   }
   if (s->pop_every > 0 && s->npop > 0) {
@@ -1869,7 +1868,7 @@ mlk_status mlk_record_energy(mlk_sim* s, int32_t every) {
   HIPCHK(hipSetDevice(s->desc.device));
   dfree(s->er.series);
   dfree(s->er.partial);
-  s->energy_cap = 0;
+  s->er.cap = 0;
   s->er.every = every;
   if (every == 0) return MLK_OK;
   s->er.nblocks = (int)std::max<size_t>(1, std::min<size_t>((s->ncell + 255) / 256, 1024));

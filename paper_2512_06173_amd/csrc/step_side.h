@@ -11,7 +11,7 @@ namespace mlk {
 // Exact two-level step of emitter slot m at step n.
 __device__ __forceinline__ void tls_body(const TlsPtrs& tls, double dt, const double* Et,
                                          double* mudot, const int64_t* pop_off, const Series& ser,
-                                         int64_t n, int m) {
+                                         const StepNo& n, int m) {
   if (m >= tls.count) return;
   const int e = tls.gid[m];
   const double et[3] = {Et[3 * e], Et[3 * e + 1], Et[3 * e + 2]};
@@ -19,15 +19,14 @@ __device__ __forceinline__ void tls_body(const TlsPtrs& tls, double dt, const do
   double st[3] = {tls.rho[3 * m], tls.rho[3 * m + 1], tls.rho[3 * m + 2]};
   double md[3];
   tls_advance(tls.omega0[m], d, et, dt, st, md);
-  if (!isfinite(st[0] + st[1] + st[2] + md[0] + md[1] + md[2])) flag_nonfinite(ser, n);
+  if (!isfinite(st[0] + st[1] + st[2] + md[0] + md[1] + md[2])) flag_nonfinite(ser, n.get());
   tls.rho[3 * m] = st[0];
   tls.rho[3 * m + 1] = st[1];
   tls.rho[3 * m + 2] = st[2];
   mudot[3 * e] = md[0];
   mudot[3 * e + 1] = md[1];
   mudot[3 * e + 2] = md[2];
-  if (ser.pop_every > 0 && n % ser.pop_every == 0)
-    ser.pop[(n / ser.pop_every) * ser.npop + pop_off[e]] = st[0];
+  if (double* pop = pop_record(ser, n)) pop[pop_off[e]] = st[0];
 }
 
 // One workgroup of nt threads (a multiple of 64 up to 1024) closes step n: probe
@@ -44,7 +43,7 @@ __device__ __forceinline__ void finish_body(const FieldPtrs<T>& f, const Geom& g
     const int comp = ser.probe_comp[t];
     const T* a = comp < 3 ? f.E[comp] : f.H[comp - 3];
     const double v = (double)a[ser.probe_idx[t]];
-    ser.probe[(size_t)t * ser.cap + n] = v;
+    if (n < ser.cap) ser.probe[(size_t)t * ser.cap + n] = v;
     if (!isfinite(v)) flag_nonfinite(ser, n);
   }
   if (fp.on) {
@@ -60,7 +59,7 @@ __device__ __forceinline__ void finish_body(const FieldPtrs<T>& f, const Geom& g
     }
     if (t == 0) {
       const double F = red[0] * g.dx * g.dx;
-      fp.series[n] = F;
+      if (n < ser.cap) fp.series[n] = F;
       *fp.total += g.dt * F;
       if (!isfinite(F)) flag_nonfinite(ser, n);
     }
@@ -92,7 +91,7 @@ template <typename T, int NT, bool STREAM>
 __device__ __forceinline__ void side_body(const SideWork& w, const FieldPtrs<T>& f,
                                           const FieldPtrs<T>& out, const Geom& g, int b) {
   if (b < w.tls_blocks)
-    tls_body(w.tls, g.dt, w.Et, w.mudot, w.pop_off, w.ser, w.n.get(), b * NT + (int)threadIdx.x);
+    tls_body(w.tls, g.dt, w.Et, w.mudot, w.pop_off, w.ser, w.n, b * NT + (int)threadIdx.x);
   else if (b < w.tls_blocks + w.finish)
     finish_body(f, g, w.fp, w.ser, w.n.get() - 1, nullptr, NT);
   else {

@@ -611,7 +611,7 @@ __device__ __forceinline__ void batch_side_body(const BatchSide<T>& w, int b) {
     const TlsJob J = load_job(w.tls, j);
     u -= w.tls_start[j];
     if (u < J.nblocks)
-      tls_body(J.tls, J.dt, J.Et, J.mudot, J.pop_off, J.ser, *J.step, u * 256 + l);
+      tls_body(J.tls, J.dt, J.Et, J.mudot, J.pop_off, J.ser, StepNo{J.step, 0}, u * 256 + l);
     return;
   }
   u -= w.ntls;

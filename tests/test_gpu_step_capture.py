@@ -70,3 +70,33 @@ def test_replays_are_the_steps_that_follow(what, precision):
         assert sim.flux_total() == ref.flux_total()
     sim.close()
     ref.close()
+
+
+def test_replays_past_the_room_of_the_series():
+    """Populations have room for 64 records and probes and fluxes for 1024 at first: what the
+    replays record beyond is dropped (a probe's row would run on into the next probe's)."""
+    import torch
+    st = torch.cuda.Stream()
+    sim, ref = build("tls", "fp64", st.cuda_stream), build("tls", "fp64")
+    for s in (sim, ref):
+        s.add_probe(0, (14, 14, 14))
+        s.record_energy(1)
+        s.step(40)
+        s.sync()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=st):
+        sim.step(4)
+    ref.step(4)
+    before = [ref.populations(), ref.probe(0), ref.probe(1), ref.flux_series(),
+              ref.energy_series()]
+    print("[capture] 1040 steps, room for 1024 (64)", flush=True)
+    with torch.cuda.stream(st):
+        for _ in range(250):
+            g.replay()
+    ref.step(996)
+    assert all(np.array_equal(a, b) for a, b in zip(state(sim, "tls"), state(ref, "tls")))
+    after = [sim.populations(), sim.probe(0), sim.probe(1), sim.flux_series(),
+             sim.energy_series()]
+    assert all(np.array_equal(a, b) for a, b in zip(before, after))
+    sim.close()
+    ref.close()
