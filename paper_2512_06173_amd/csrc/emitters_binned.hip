@@ -21,6 +21,14 @@ void bin_shape(bool fp32, int G[3], int S[3]) {
   S[0] = kScX; S[1] = kScY; S[2] = kScZ;
 }
 
+// A wavefront takes 0.7 us for a chunk of pairs, whatever else the chip does, so a bin of many
+// pairs that a wavefront had to itself kept the launch waiting; sharing costs a bin of few pairs
+// the exchange.  Limits of 64, 128, 256 and 512 pairs, us: FP32 128^3 with 100,000 emitters
+// 45.7, 36.1, 35.9, 36.6; 10,000 in 12 planes of 64 x 64 12.3, 13.4, 18.7, 26.4; 300 within four
+// cells 9.8, 10.7, 10.9, 20.3; FP64 86.7, 69.6, 70.3, 71.5; 17.5, 19.4, 30.2, 44.3; 13.1, 13.8,
+// 13.8, 33.5.
+int scatter_shared() { return 128; }
+
 __global__ __launch_bounds__(256) void k_tls_step(TlsPtrs tls, double dt, const double* Et,
                                                   double* mudot, const int64_t* pop_off,
                                                   Series ser, StepNo n) {
@@ -80,7 +88,10 @@ struct Mfma<double> {
 // its pairs m, per component c:
 //   J_c[(y, z), x] = sum_m (wy_m(y) wz_m(z)) (amp_m^c wx_m(x)).
 // A wavefront owns a bin of 16 x by 4 y and 4 z (16 rows) and takes its pairs four at a
-// time, three 16 x 16 x 4 products of the field's own precision each.
+// time, three 16 x 16 x 4 products of the field's own precision each.  A bin of many pairs (see
+// scatter_shared) is shared by the four wavefronts of a workgroup, a quarter of the pairs each,
+// whose sums are added in FP64 and in order: 10,000 emitters within four cells 442 -> 117 us
+// (FP64 847 -> 220), 10,000 in 12 planes of 64 x 64 26.6 -> 13.6 (43 -> 19).
 //
 // A pair (emitter, bin) comes with its offset per axis, set up on the host (see
 // PairDesc): bin-local cell x reads weight x + o.  The weights are staged in LDS with
@@ -90,7 +101,7 @@ struct Mfma<double> {
 // of cells is zero: a run begins at weight 0 or at cell 0, and ends with the weights, with
 // the bin or with the axis, whose cells are the only ones written.
 //
-// The wavefronts of a workgroup share nothing and never wait for each other; registers allow
+// Otherwise the wavefronts of a workgroup share nothing and never wait for each other; registers allow
 // five a SIMD (FP64: three), which hide the trips to memory of each other (ids, then records, then
 // E).  With 50,000 to 100,000 emitters no unit is busy more than a third of the time (cube:
 // VALU 32%, matrix cores 18%, LDS 27%) and the reads and writes of E run at 1 to 4 TB/s: what
@@ -98,8 +109,7 @@ struct Mfma<double> {
 // (8 with FP64) cells with LDS atomics, two or three per cell and emitter.  Kernel times,
 // us a step, before and now: cube 256^3 with 100,000 emitters 59.6 -> 50, 187 x 149 x 163
 // FP64 with 20,000 76 -> 53, 384^3 with 100,000 113 -> 89, 160^3 with 10,000 28 -> 16.7,
-// 10,000 in 12 planes of 64 x 64 42 -> 23 (few bins then, so the launch lasts as long as a
-// bin), 1,000 in 128^3 10.4 -> 6.1.  Measured and not taken: bins of four wavefronts with
+// 1,000 in 128^3 10.4 -> 6.1.  Measured and not taken: bins of four wavefronts with
 // their pairs staged together (cube 51, 64 x 64 planes 36); E read at the start (54).
 //
 // Blocks from bins.nscatter on (when more is given) form the flux partials of the plane, in
@@ -116,14 +126,17 @@ __device__ __forceinline__ void scatter_body(const FieldPtrs<T>& f, const Geom& 
   // FP32 amplitudes are held 2^-9 of what they are: the largest weight of a window is at least
   // 8^-3, so an amplitude beyond what is left (which counts as the limit: an infinity would
   // spoil the bin) exceeds FP32 in its window
-  constexpr double kAmpScale = sizeof(T) == 4 ? 0x1p-9 : 1.0, kAmpMax = 3.4028234663852886e38;
+  constexpr double kAmpScale = sizeof(T) == 4 ? 0x1p-9 : 1.0;
+  constexpr float kAmpMax = 3.4028234663852886e38f;
   // a pair's weights in LDS: x at 0, y at kY, z at kZ, zeros between and behind
   constexpr int kY = 12, kZ = 24, kStride = 36;
   constexpr int kPer = 16 / (int)sizeof(T2);   // weights per 16-byte piece
   constexpr int R4 = 3 * kMaxWin / kPer;       // pieces of a record
   constexpr int NP = P * R4 / 64;              // pieces per lane and chunk
   static_assert(P * R4 % 64 == 0 && 3 * P <= 64 && P % 4 == 0 && kMaxWin == 8, "chunk");
-  __shared__ alignas(16) T2 sWin[kScWaves][P * kStride];
+  // (or, of a bin that the workgroup shares, the wavefronts' sums: 12 a lane)
+  constexpr int kWin = P * kStride > 12 * 64 / 2 ? P * kStride : 12 * 64 / 2;
+  __shared__ alignas(16) T2 sWin[kScWaves][kWin];
   __shared__ alignas(16) T sAmp[kScWaves][P][4];
   __shared__ int sOff[kScWaves][P];
   if (more && bid >= bins.nscatter) {  // uniform across the block
@@ -142,8 +155,14 @@ __device__ __forceinline__ void scatter_body(const FieldPtrs<T>& f, const Geom& 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int4 bin = bins.sbin[bid * kScWaves + wave];
-  const int q0 = bin.y, q1 = bin.z;
-  if (q0 >= q1) return;  // fills up the last workgroup
+  if (bin.y >= bin.z) return;  // fills up the last workgroup
+  const bool shared = bin.w != 0;  // uniform across the workgroup
+  int q0 = bin.y, q1 = bin.z;
+  if (shared) {
+    const int part = (q1 - q0 + kScWaves * P - 1) / (kScWaves * P) * P;
+    q0 = min(q0 + wave * part, q1);
+    q1 = min(q0 + part, q1);
+  }
 
   // A chunk's weights and amplitudes pass through registers: its loads are issued a
   // chunk ahead, those of the emitters, on which they depend, two chunks ahead.
@@ -190,10 +209,10 @@ __device__ __forceinline__ void scatter_body(const FieldPtrs<T>& f, const Geom& 
     if (lane < 3 * P) {
       // an amplitude that is no number adds nothing (times the zeros beside its window
       // it would spoil the whole bin), nor does what fills up the last step
-      double v = amp0 * pg * pm * kAmpScale;
-      const bool on = apair < cn && fabs(v) <= 1.7976931348623157e308;
-      if constexpr (sizeof(T) == 4) v = fmin(fmax(v, -kAmpMax), kAmpMax);
-      sAmp[wave][apair][acomp] = on ? (T)v : T(0);
+      const double v = amp0 * pg * pm * kAmpScale;
+      T a = (T)v;
+      if constexpr (sizeof(T) == 4) a = __builtin_amdgcn_fmed3f(a, -kAmpMax, kAmpMax);
+      sAmp[wave][apair][acomp] = apair < cn && fabs(v) <= 1.7976931348623157e308 ? a : T(0);
       if (acomp == 0) sOff[wave][apair] = aoff;
     }
   };
@@ -251,7 +270,7 @@ __device__ __forceinline__ void scatter_body(const FieldPtrs<T>& f, const Geom& 
     sums(P);
     fold();
   }
-  stage(q1 - c0);
+  if (c0 < q1) stage(q1 - c0);
   // Lane l holds x = l % 16 and four of the rows (y, z), neighbours along y (FP32) or z
   // (FP64), nr of them in the grid.  Their E is read ahead of the last chunk's sums.
   const int bx = bin.x % bins.nbx, by = (bin.x / bins.nbx) % bins.nby,
@@ -270,6 +289,36 @@ __device__ __forceinline__ void scatter_body(const FieldPtrs<T>& f, const Geom& 
 #pragma unroll
     for (int c = 0; c < 3; ++c) ev[r][c] = r < nr ? f.E[c][cell + r * step] : T(0);
     if (EPS && f.epsinv && r < nr) ei[r] *= f.epsinv[cell + r * step];  // null: eps_r = 1
+  }
+  if (shared) {
+    // the wavefronts' sums, in their order and in FP64; wavefront r writes row r
+    if (c0 < q1) sums(q1 - c0);
+    const bool in = wave < nr;
+    const size_t own = cell + wave * step;
+    T e[3], ei = T(1 / kAmpScale);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) e[c] = in ? f.E[c][own] : T(0);
+    if (EPS && f.epsinv && in) ei *= f.epsinv[own];
+    __syncthreads();
+    T* s = reinterpret_cast<T*>(&sWin[0][0]);
+    if constexpr (kExact) fold();
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        T v = acc[c][r];
+        if constexpr (kExact) v = hi[c][r] + lo[c][r];
+        s[((wave * 3 + c) * 4 + r) * 64 + lane] = v;
+      }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      double v = 0.0;
+#pragma unroll
+      for (int w = 0; w < kScWaves; ++w) v += (double)s[((w * 3 + c) * 4 + wave) * 64 + lane];
+      if (in && v != 0.0) f.E[c][own] = e[c] - ei * (T)v;
+    }
+    return;
   }
   sums(q1 - c0);
   if constexpr (kExact) {

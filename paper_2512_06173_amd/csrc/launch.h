@@ -104,6 +104,8 @@ hipError_t bin_scatter_f32(const FieldPtrs<float>& f, const Geom& g, const BinPt
 // bin edge lengths (cells) of the gather (G) and scatter (S) bins for a field precision
 void bin_shape(bool fp32, int G[3], int S[3]);
 void gather_bin_shape(bool fp32, int G[3]);
+// A scatter bin of more pairs than this is shared by a workgroup's wavefronts.
+int scatter_shared();
 // Gather bins of at most this many emitters are light (no tile); the workgroups that
 // nlight of their emitters take.
 int gather_light_max();

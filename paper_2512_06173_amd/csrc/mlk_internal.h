@@ -399,7 +399,8 @@ struct BinPtrs {
   const int* gbin_start;    // [ngather+1] CSR into gbin_em
   const int* gbin_em;       // emitter ids; the record of gbin_em[q] is rec[q]
   int nscatter;             // workgroups of the scatter, kScWaves bins each
-  const int4* sbin;         // [kScWaves*nscatter] bin, first and end pair (equal: no bin)
+  const int4* sbin;         // [kScWaves*nscatter] bin, first and end pair (equal: no bin),
+                            // 1 if the four wavefronts of the workgroup share the bin
   const int4* sbin_pair;    // one PairDesc per (emitter, bin) pair
 };
 

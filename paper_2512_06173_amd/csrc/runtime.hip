@@ -645,43 +645,65 @@ mlk_status build_bins(mlk_sim* s) {
       pd = bp.second;
       pd.rec = (unsigned)q * rec16 + w16;
     }
-  // The launch's order of bins, kScWaves to a workgroup.  Workgroups go to the eight XCDs
-  // in turn, and neighbouring bins share records and lines of E, so each XCD takes an
-  // eighth of the bins, neighbours in space; within it the heaviest first (in steps of 32
-  // pairs, so that neighbours stay together), as the light ones then fill in behind them.
-  // Work of a bin: its pairs and, in the same unit, what every bin costs.  Where the eighths
-  // differ by more than a quarter in work, the heaviest of all go first instead.
+  // The launch's order of bins, kScWaves to a workgroup, or a workgroup to a bin of more than
+  // scatter_shared() pairs.  Workgroups go to the eight XCDs in turn, and neighbouring bins
+  // share records and lines of E, so each XCD takes an eighth of the bins of both kinds,
+  // neighbours in space; within it the heaviest first (in steps of 32 pairs, so that
+  // neighbours stay together), as the light ones then fill in behind them.  Work of a bin: its
+  // pairs and, in the same unit, what every bin costs.  Where the eighths differ by more
+  // than a quarter in work, the heaviest of all go first instead.
   std::vector<int4> sbin;
   s->swork.clear();
   {
-    const int nsl = (int)sid.size(), nblk = (nsl + kScWaves - 1) / kScWaves;
+    std::vector<int> kind[2];  // bins that wavefronts take, and that workgroups take
+    const int limit = scatter_shared();
+    for (int sl = 0; sl < (int)sid.size(); ++sl)
+      kind[sstart[sl + 1] - sstart[sl] > limit].push_back(sl);
+    const int nsh = (int)kind[1].size(), nlt = (int)kind[0].size();
+    const int nblk = nsh + (nlt + kScWaves - 1) / kScWaves;
     auto work = [&](int sl) { return sl < 0 ? 0 : 16 + sstart[sl + 1] - sstart[sl]; };
-    std::vector<int> seg[8];
+    auto heavier = [&](int x, int y) { return work(x) / 32 > work(y) / 32; };
+    std::vector<int> sh[8], lt[8];
     double most = 0.0, total = 0.0;
-    for (int x = 0, q = 0; x < 8; ++x) {
+    for (int x = 0, qs = 0, ql = 0; x < 8; ++x) {
+      const int blocks = nblk / 8 + (x < nblk % 8), mine = nsh / 8 + (x < nsh % 8);
       double w = 0.0;
-      for (const int end = q + kScWaves * (nblk / 8 + (x < nblk % 8)); q < end; ++q) {
-        seg[x].push_back(q < nsl ? q : -1);
-        w += work(seg[x].back());
-      }
+      for (const int end = qs + mine; qs < end; ++qs) sh[x].push_back(kind[1][qs]);
+      for (const int end = ql + kScWaves * (blocks - mine); ql < end; ++ql)
+        lt[x].push_back(ql < nlt ? kind[0][ql] : -1);
+      for (int sl : sh[x]) w += work(sl);
+      for (int sl : lt[x]) w += work(sl);
       most = std::max(most, w);
       total += w;
     }
-    auto heavier = [&](int x, int y) { return work(x) / 32 > work(y) / 32; };
-    std::vector<int> all;
-    if (most <= 1.25 * total / 8) {
-      for (auto& v : seg) std::stable_sort(v.begin(), v.end(), heavier);
+    if (most > 1.25 * total / 8) {
+      // one order over all, dealt to the eight in turn
+      std::stable_sort(kind[1].begin(), kind[1].end(), heavier);
+      std::stable_sort(kind[0].begin(), kind[0].end(), heavier);
+      kind[0].resize((size_t)kScWaves * (nblk - nsh), -1);
+      for (int x = 0; x < 8; ++x) {
+        sh[x].clear();
+        lt[x].clear();
+      }
+      for (int b = 0; b < nblk; ++b)
+        if (b < nsh) sh[b % 8].push_back(kind[1][b]);
+        else
+          for (int k = 0; k < kScWaves; ++k)
+            lt[b % 8].push_back(kind[0][(size_t)kScWaves * (b - nsh) + k]);
     } else {
-      for (auto& v : seg) all.insert(all.end(), v.begin(), v.end());
-      std::stable_sort(all.begin(), all.end(), heavier);
+      for (int x = 0; x < 8; ++x) {
+        std::stable_sort(sh[x].begin(), sh[x].end(), heavier);
+        std::stable_sort(lt[x].begin(), lt[x].end(), heavier);
+      }
     }
     for (int b = 0; b < nblk; ++b) {
-      const int* sl = all.empty() ? &seg[b % 8][kScWaves * (b / 8)] : &all[kScWaves * b];
+      const int x = b % 8, q = b / 8, ns = (int)sh[x].size();
       float w = 0.f;
       for (int k = 0; k < kScWaves; ++k) {
-        sbin.push_back(sl[k] < 0 ? make_int4(0, 0, 0, 0)
-                                 : make_int4(sid[sl[k]], sstart[sl[k]], sstart[sl[k] + 1], 0));
-        w = std::max(w, (float)(work(sl[k]) / 32));
+        const int sl = q < ns ? sh[x][q] : lt[x][(size_t)kScWaves * (q - ns) + k];
+        sbin.push_back(sl < 0 ? make_int4(0, 0, 0, 0)
+                              : make_int4(sid[sl], sstart[sl], sstart[sl + 1], q < ns));
+        w = std::max(w, (float)(work(sl) / 32));
       }
       s->swork.push_back(w);
     }
