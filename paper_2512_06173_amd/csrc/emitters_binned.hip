@@ -285,20 +285,20 @@ __device__ __forceinline__ void scatter_body(const FieldPtrs<T>& f, const Geom& 
   T ev[4][3], ei[4];
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    ei[r] = T(1 / kAmpScale);
+    ei[r] = T(1);
 #pragma unroll
     for (int c = 0; c < 3; ++c) ev[r][c] = r < nr ? f.E[c][cell + r * step] : T(0);
-    if (EPS && f.epsinv && r < nr) ei[r] *= f.epsinv[cell + r * step];  // null: eps_r = 1
+    if (EPS && f.epsinv && r < nr) ei[r] = f.epsinv[cell + r * step];  // null: eps_r = 1
   }
   if (shared) {
     // the wavefronts' sums, in their order and in FP64; wavefront r writes row r
     if (c0 < q1) sums(q1 - c0);
     const bool in = wave < nr;
     const size_t own = cell + wave * step;
-    T e[3], ei = T(1 / kAmpScale);
+    T e[3], ei = T(1);
 #pragma unroll
     for (int c = 0; c < 3; ++c) e[c] = in ? f.E[c][own] : T(0);
-    if (EPS && f.epsinv && in) ei *= f.epsinv[own];
+    if (EPS && f.epsinv && in) ei = f.epsinv[own];
     __syncthreads();
     T* s = reinterpret_cast<T*>(&sWin[0][0]);
     if constexpr (kExact) fold();
@@ -316,7 +316,7 @@ __device__ __forceinline__ void scatter_body(const FieldPtrs<T>& f, const Geom& 
       double v = 0.0;
 #pragma unroll
       for (int w = 0; w < kScWaves; ++w) v += (double)s[((w * 3 + c) * 4 + wave) * 64 + lane];
-      if (in && v != 0.0) f.E[c][own] = e[c] - ei * (T)v;
+      if (in && v != 0.0) f.E[c][own] = e[c] - ei * (T)(v / kAmpScale);
     }
     return;
   }
@@ -331,7 +331,8 @@ __device__ __forceinline__ void scatter_body(const FieldPtrs<T>& f, const Geom& 
   for (int r = 0; r < 4; ++r)
 #pragma unroll
     for (int c = 0; c < 3; ++c)
-      if (r < nr && acc[c][r] != T(0)) f.E[c][cell + r * step] = ev[r][c] - ei[r] * acc[c][r];
+      if (r < nr && acc[c][r] != T(0))
+        f.E[c][cell + r * step] = ev[r][c] - ei[r] * (acc[c][r] * T(1 / kAmpScale));
 }
 
 template <typename T>
