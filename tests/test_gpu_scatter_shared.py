@@ -76,3 +76,21 @@ def test_shared_and_other_bins_alone_and_in_a_batch(precision):
     assert np.any(out[0][0])
     for o in out[1:]:
         assert all(np.array_equal(x, y) for x, y in zip(out[0], o))
+
+
+@pytest.mark.parametrize("n", [128, 1024, 1025, 2500, 12000])
+def test_fp32_error_does_not_grow_with_the_emitters_around_a_cell(n):
+    """A wavefront sums at most 256 pairs in FP32 before they are added up in FP64, four in one
+    product: 64 roundings, each spread evenly over half a unit of the sum's last place (at most
+    2^-24 of it), one of E and, far less over many terms, those of the terms.  The root mean
+    square over the cells is then at most sqrt(66) 2^-24 / sqrt(3) = 2.8e-7 of the largest |E|,
+    whatever n is.  (A sum of all pairs in FP32 passes that from some 4,000 on.)"""
+    shape = (37, 23, 21)
+    sim = run(lambda: mlk().Simulation(shape, precision="fp32"), shape, n)
+    ora = run(lambda: Oracle(shape), shape, n)
+    got, want = sim.fields()[:3], ora.fields()[:3]
+    scale = max(np.max(np.abs(w)) for w in want)
+    e = np.concatenate([(a - b)[np.abs(b) > 0.05 * scale] for a, b in zip(got, want)]) / scale
+    rms = float(np.sqrt(np.mean(e ** 2)))
+    print(f"[shared] fp32 {n}: rms {rms:.2e} over {e.size} cells", flush=True)
+    assert rms <= np.sqrt(66 / 3) * 2.0 ** -24
