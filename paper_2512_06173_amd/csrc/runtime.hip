@@ -65,63 +65,35 @@ void dfree(P*& p) {
   p = nullptr;
 }
 
-// Device blocks that a sim keeps from one adjoint call for the next, at most a GiB of them:
-// a call takes two dozen, and allocating and freeing them took 3.0 of its 11.8 ms on
-// 112 x 104 x 120 cells (48 steps).  Above that a call's own work hides it, and the memory
-// is worth more to others.  A block is reused for the same size only; a call of another shape
-// frees what it finds first.  The owner's stream has been synchronised when a block is
-// handed out (mlk_adjoint does that first), and it belongs to one sim, like every call on it.
-struct Scratch {
-  static constexpr size_t kKeep = (size_t)1 << 30;
-  std::vector<std::pair<void*, size_t>> blocks;
-  size_t bytes = 0;
-  void clear() {
-    for (auto& b : blocks) (void)hipFree(b.first);
-    blocks.clear();
-    bytes = 0;
-  }
-  hipError_t get(void** p, size_t n) {
-    for (size_t q = 0; q < blocks.size(); ++q)
-      if (blocks[q].second == n) {
-        *p = blocks[q].first;
-        bytes -= n;
-        blocks.erase(blocks.begin() + q);
-        return hipSuccess;
-      }
-    clear();
-    return dalloc(p, n);
-  }
-  void put(void* p, size_t n) {
-    if (bytes + n > kKeep) {
-      (void)hipFree(p);
-      return;
-    }
-    blocks.push_back({p, n});
-    bytes += n;
-  }
-};
-
-// Device buffer owned by a scope, taken from and given back to a Scratch if there is one.
+// Device buffer owned by a scope.
 template <typename T>
 struct DevBuf {
   T* p = nullptr;
-  size_t n = 0;
-  Scratch* pool = nullptr;
-  DevBuf() = default;
-  explicit DevBuf(Scratch* s) : pool(s) {}
-  DevBuf(const DevBuf&) = delete;
-  DevBuf& operator=(const DevBuf&) = delete;
-  ~DevBuf() { release(); }
-  void release() {
-    if (p && pool) pool->put(p, n * sizeof(T));
-    else dfree(p);
-    p = nullptr;
-  }
-  hipError_t alloc(size_t count) {
-    release();
-    n = count;
+  ~DevBuf() { dfree(p); }
+  hipError_t alloc(size_t n) {
+    dfree(p);
     if (n == 0) return hipSuccess;
-    return pool ? pool->get((void**)&p, n * sizeof(T)) : dalloc(&p, n * sizeof(T));
+    return dalloc(&p, n * sizeof(T));
+  }
+};
+
+// The arrays of an adjoint call in one device block, which the call allocates and frees: on
+// 112 x 104 x 120 cells (40 steps) 11.8 ms a call; 14.7 with two dozen blocks, 11.6 with blocks
+// kept for the next call, which no other user of the memory could get back.  Every array
+// is asked for twice, first with no block, to size it.
+struct Arena {
+  char* base = nullptr;
+  size_t used = 0;
+  ~Arena() { dfree(base); }
+  hipError_t alloc() {
+    const size_t n = used;
+    used = 0;
+    return dalloc(&base, n);
+  }
+  template <typename T>
+  void take(T*& p, size_t n) {
+    p = base && n ? reinterpret_cast<T*>(base + used) : nullptr;
+    used += (n * sizeof(T) + 255) / 256 * 256;
   }
 };
 
@@ -136,7 +108,6 @@ struct mlk_sim {
   mlk_grid_desc desc{};
   // phase timing: event pool, pending (phase, start event, end event) marks
   int timing = 0;  // bit p set: phase p is timed
-  Scratch scratch;
   std::vector<hipEvent_t> events;
   size_t next_event = 0;
   std::vector<std::array<int, 3>> marks;
@@ -1280,7 +1251,6 @@ mlk_status enqueue_cavity_steps(mlk_sim* s, int64_t nsteps) {
 }
 
 void release(mlk_sim* s) {
-  s->scratch.clear();
   for (hipEvent_t e : s->events) (void)hipEventDestroy(e);
   s->events.clear();
   // caller-owned buffers are dropped, not freed
@@ -2407,9 +2377,33 @@ mlk_status adjoint_run(mlk_sim* s, int kind, const double* weights, int64_t T_st
   STCHK(reserve_series(s, T_steps));
   const int64_t step0 = s->host_step;
 
-  Scratch* const sp = &s->scratch;
-  DevBuf<char> ckpt{sp};
-  HIPCHK(ckpt.alloc(ck * (size_t)nseg));
+  // checkpoints; adjoint state: a fused-sweep sim takes the transposed sweep out of place
+  // (fused box plus shell), with two sets of adjoint fields used in turn; tape of one segment
+  const bool oop = s->desc.sweep == MLK_SWEEP_FUSED;
+  const size_t npsi = psi_total(s->g);
+  char* ckpt;
+  T *Eb[2][3] = {}, *Hb[2][3] = {}, *psib[2], *tbox;
+  double *sb, *gd, *mub, *etb, *geps, *ts, *tg, *tf;
+  Arena arena;
+  for (int pass = 0; pass < 2; ++pass) {
+    if (pass == 1) HIPCHK(arena.alloc());
+    arena.take(ckpt, ck * (size_t)nseg);
+    for (int q = 0; q < (oop ? 2 : 1); ++q)
+      for (int c = 0; c < 3; ++c) {
+        arena.take(Eb[q][c], nc);
+        arena.take(Hb[q][c], nc);
+      }
+    for (auto& p : psib) arena.take(p, npsi);
+    arena.take(sb, (size_t)3 * nt);
+    arena.take(gd, (size_t)3 * nt);
+    arena.take(mub, (size_t)3 * M);
+    arena.take(etb, (size_t)3 * M);
+    arena.take(geps, nb);
+    arena.take(tbox, nb * 3 * (size_t)(K + 1));
+    arena.take(ts, (size_t)3 * nt * K);
+    arena.take(tg, (size_t)3 * M * K);
+    arena.take(tf, (size_t)8 * np * K);
+  }
   hipEvent_t ev[3];
   for (auto& e : ev) HIPCHK(hipEventCreate(&e));
   struct EvGuard {
@@ -2423,7 +2417,7 @@ mlk_status adjoint_run(mlk_sim* s, int kind, const double* weights, int64_t T_st
   if (s->fp.on) HIPCHK(hipMemcpy(&ftot0, s->fp.total, sizeof(double), hipMemcpyDeviceToHost));
   // forward pass with the checkpoints
   for (int seg = 0; seg < nseg; ++seg) {
-    STCHK(mlk_checkpoint_save(s, ckpt.p + ck * (size_t)seg, MLK_MEM_DEVICE));
+    STCHK(mlk_checkpoint_save(s, ckpt + ck * (size_t)seg, MLK_MEM_DEVICE));
     const int64_t ns = std::min<int64_t>(K, T_steps - (int64_t)seg * K);
     STCHK(enqueue_steps<T>(s, ns));
     s->host_step += ns;
@@ -2443,47 +2437,22 @@ mlk_status adjoint_run(mlk_sim* s, int kind, const double* weights, int64_t T_st
   }
   *value = J;
 
-  // adjoint state; a fused-sweep sim takes the transposed sweep out of place
-  // (fused box plus shell), with two sets of adjoint fields used in turn
-  const bool oop = s->desc.sweep == MLK_SWEEP_FUSED;
-  using Buf = DevBuf<T>;
-  Buf Eb[2][3] = {{Buf{sp}, Buf{sp}, Buf{sp}}, {Buf{sp}, Buf{sp}, Buf{sp}}};
-  Buf Hb[2][3] = {{Buf{sp}, Buf{sp}, Buf{sp}}, {Buf{sp}, Buf{sp}, Buf{sp}}};
-  Buf psib[2] = {Buf{sp}, Buf{sp}};
   for (int q = 0; q < (oop ? 2 : 1); ++q)
     for (int c = 0; c < 3; ++c) {
-      HIPCHK(Eb[q][c].alloc(nc));
-      HIPCHK(Hb[q][c].alloc(nc));
-      HIPCHK(hipMemsetAsync(Eb[q][c].p, 0, nc * sizeof(T), st));
-      HIPCHK(hipMemsetAsync(Hb[q][c].p, 0, nc * sizeof(T), st));
+      HIPCHK(hipMemsetAsync(Eb[q][c], 0, nc * sizeof(T), st));
+      HIPCHK(hipMemsetAsync(Hb[q][c], 0, nc * sizeof(T), st));
     }
-  const size_t npsi = psi_total(s->g);
-  for (int q = 0; q < 2; ++q) {
-    HIPCHK(psib[q].alloc(npsi));
-    if (npsi) HIPCHK(hipMemsetAsync(psib[q].p, 0, npsi * sizeof(T), st));
-  }
-  DevBuf<double> sb{sp}, gd{sp}, mub{sp}, etb{sp}, geps{sp};
-  HIPCHK(sb.alloc((size_t)3 * nt));
-  HIPCHK(gd.alloc((size_t)3 * nt));
-  HIPCHK(mub.alloc((size_t)3 * M));
-  HIPCHK(etb.alloc((size_t)3 * M));
-  HIPCHK(geps.alloc(nb));
-  if (nt) HIPCHK(hipMemsetAsync(gd.p, 0, (size_t)3 * nt * sizeof(double), st));
-  if (M) HIPCHK(hipMemsetAsync(etb.p, 0, (size_t)3 * M * sizeof(double), st));
-  if (nb) HIPCHK(hipMemsetAsync(geps.p, 0, nb * sizeof(double), st));
+  for (T* p : psib)
+    if (npsi) HIPCHK(hipMemsetAsync(p, 0, npsi * sizeof(T), st));
+  if (nt) HIPCHK(hipMemsetAsync(gd, 0, (size_t)3 * nt * sizeof(double), st));
+  if (M) HIPCHK(hipMemsetAsync(etb, 0, (size_t)3 * M * sizeof(double), st));
+  if (nb) HIPCHK(hipMemsetAsync(geps, 0, nb * sizeof(double), st));
   if (nt) {
     std::vector<double> s0((size_t)3 * nt, 0.0);
     if (kind == MLK_OBJ_POPULATION)
       for (int m = 0; m < nt; ++m) s0[3 * m] = weights[s->tls_gid[m]];
-    HIPCHK(hipMemcpy(sb.p, s0.data(), s0.size() * sizeof(double), hipMemcpyHostToDevice));
+    HIPCHK(hipMemcpy(sb, s0.data(), s0.size() * sizeof(double), hipMemcpyHostToDevice));
   }
-  // tape of one segment
-  Buf tbox{sp};
-  DevBuf<double> ts{sp}, tg{sp}, tf{sp};
-  HIPCHK(tbox.alloc(nb * 3 * (size_t)(K + 1)));
-  HIPCHK(ts.alloc((size_t)3 * nt * K));
-  HIPCHK(tg.alloc((size_t)3 * M * K));
-  HIPCHK(tf.alloc((size_t)8 * np * K));
 
   const WindowPtrs<T> win = window_ptrs<T>(s);
   const BinPtrs bins = bin_ptrs(s);
@@ -2493,18 +2462,18 @@ mlk_status adjoint_run(mlk_sim* s, int kind, const double* weights, int64_t T_st
   int cur = 0;        // the set holding the current adjoint fields
   auto bind = [&]() {
     for (int c = 0; c < 3; ++c) {
-      adj.E[c] = Eb[cur][c].p;
-      adj.H[c] = Hb[cur][c].p;
-      adj.Eo[c] = oop ? Eb[cur ^ 1][c].p : nullptr;
-      adj.Ho[c] = oop ? Hb[cur ^ 1][c].p : nullptr;
-      fb.E[c] = Eb[cur][c].p;
+      adj.E[c] = Eb[cur][c];
+      adj.H[c] = Hb[cur][c];
+      adj.Eo[c] = oop ? Eb[cur ^ 1][c] : nullptr;
+      adj.Ho[c] = oop ? Hb[cur ^ 1][c] : nullptr;
+      fb.E[c] = Eb[cur][c];
     }
   };
   bind();
   adj.epsinv = (const T*)s->epsinv;
   adj.tab = (const T*)s->tab;
-  adj.psi[0] = psib[0].p;
-  adj.psi[1] = psib[1].p;
+  adj.psi[0] = psib[0];
+  adj.psi[1] = psib[1];
   adj.kz = 16;
   adj.vacuum = s->vacuum;
   // in vacuum the adjoint gather reads no 1/eps_r (the scatter never does)
@@ -2513,41 +2482,41 @@ mlk_status adjoint_run(mlk_sim* s, int kind, const double* weights, int64_t T_st
   const FluxPlane* fpp = s->fp.on ? &s->fp : nullptr;
 
   for (int seg = nseg - 1; seg >= 0; --seg) {
-    STCHK(load_state(s, ckpt.p + ck * (size_t)seg, MLK_MEM_DEVICE));
+    STCHK(load_state(s, ckpt + ck * (size_t)seg, MLK_MEM_DEVICE));
     const int64_t ns = std::min<int64_t>(K, T_steps - (int64_t)seg * K);
     // recompute the segment, recording the tape
     if (nb) {
-      if constexpr (f32) HIPCHK(pack_tape_f32(field_ptrs<T>(s), s->g, box, tbox.p, nullptr, nullptr, st));
-      else HIPCHK(pack_tape_f64(field_ptrs<T>(s), s->g, box, tbox.p, nullptr, nullptr, st));
+      if constexpr (f32) HIPCHK(pack_tape_f32(field_ptrs<T>(s), s->g, box, tbox, nullptr, nullptr, st));
+      else HIPCHK(pack_tape_f64(field_ptrs<T>(s), s->g, box, tbox, nullptr, nullptr, st));
     }
     for (int64_t q = 0; q < ns; ++q) {
-      if (nt) HIPCHK(hipMemcpyAsync(ts.p + (size_t)3 * nt * q, s->d_tls_rho,
+      if (nt) HIPCHK(hipMemcpyAsync(ts + (size_t)3 * nt * q, s->d_tls_rho,
                                     (size_t)3 * nt * sizeof(double), hipMemcpyDeviceToDevice, st));
       STCHK(enqueue_steps<T>(s, 1));
       s->host_step += 1;
-      if (M) HIPCHK(hipMemcpyAsync(tg.p + (size_t)3 * M * q, s->d_Et, (size_t)3 * M * sizeof(double),
+      if (M) HIPCHK(hipMemcpyAsync(tg + (size_t)3 * M * q, s->d_Et, (size_t)3 * M * sizeof(double),
                                    hipMemcpyDeviceToDevice, st));
-      T* bo = nb ? tbox.p + nb * 3 * (size_t)(q + 1) : nullptr;
-      double* fo = kind == MLK_OBJ_FLUX ? tf.p + (size_t)8 * np * q : nullptr;
+      T* bo = nb ? tbox + nb * 3 * (size_t)(q + 1) : nullptr;
+      double* fo = kind == MLK_OBJ_FLUX ? tf + (size_t)8 * np * q : nullptr;
       if constexpr (f32) HIPCHK(pack_tape_f32(field_ptrs<T>(s), s->g, box, bo, fpp, fo, st));
       else HIPCHK(pack_tape_f64(field_ptrs<T>(s), s->g, box, bo, fpp, fo, st));
     }
     // reverse steps
     for (int64_t q = ns - 1; q >= 0; --q) {
-      const double* tfq = tf.p + (size_t)8 * np * q;
+      const double* tfq = tf + (size_t)8 * np * q;
       if (kind == MLK_OBJ_FLUX) {
         if constexpr (f32) HIPCHK(adj_flux_f32(adj, s->g, s->fp.axis, s->fp.index, tfq, 0, st));
         else HIPCHK(adj_flux_f64(adj, s->g, s->fp.axis, s->fp.index, tfq, 0, st));
       }
       if (nb) {
-        const T* e0 = tbox.p + nb * 3 * (size_t)q;
-        const T* e1 = tbox.p + nb * 3 * (size_t)(q + 1);
-        if constexpr (f32) HIPCHK(adj_eps_f32(adj, s->g, box, e0, e1, geps.p, st));
-        else HIPCHK(adj_eps_f64(adj, s->g, box, e0, e1, geps.p, st));
+        const T* e0 = tbox + nb * 3 * (size_t)q;
+        const T* e1 = tbox + nb * 3 * (size_t)(q + 1);
+        if constexpr (f32) HIPCHK(adj_eps_f32(adj, s->g, box, e0, e1, geps, st));
+        else HIPCHK(adj_eps_f64(adj, s->g, box, e0, e1, geps, st));
       }
       if (M) {
-        if constexpr (f32) HIPCHK(gather_epsw_f32(fb, s->g, bins, win, mub.p, st));
-        else HIPCHK(gather_epsw_f64(fb, s->g, bins, win, mub.p, st));
+        if constexpr (f32) HIPCHK(gather_epsw_f32(fb, s->g, bins, win, mub, st));
+        else HIPCHK(gather_epsw_f64(fb, s->g, bins, win, mub, st));
       }
       if constexpr (f32) HIPCHK(adj_sweep_f32(adj, s->g, st));
       else HIPCHK(adj_sweep_f64(adj, s->g, st));
@@ -2557,10 +2526,10 @@ mlk_status adjoint_run(mlk_sim* s, int kind, const double* weights, int64_t T_st
         bind();
       }
       if (nt) {
-        HIPCHK(adj_tls(tls, s->g.dt, mub_scale, ts.p + (size_t)3 * nt * q,
-                       tg.p + (size_t)3 * M * q, mub.p, sb.p, gd.p, etb.p, st));
-        if constexpr (f32) HIPCHK(scatter_plain_f32(fb, s->g, bins, win, etb.p, -1.0, st));
-        else HIPCHK(scatter_plain_f64(fb, s->g, bins, win, etb.p, -1.0, st));
+        HIPCHK(adj_tls(tls, s->g.dt, mub_scale, ts + (size_t)3 * nt * q,
+                       tg + (size_t)3 * M * q, mub, sb, gd, etb, st));
+        if constexpr (f32) HIPCHK(scatter_plain_f32(fb, s->g, bins, win, etb, -1.0, st));
+        else HIPCHK(scatter_plain_f64(fb, s->g, bins, win, etb, -1.0, st));
       }
       if (kind == MLK_OBJ_FLUX) {
         if constexpr (f32) HIPCHK(adj_flux_f32(adj, s->g, s->fp.axis, s->fp.index, tfq, 1, st));
@@ -2576,13 +2545,13 @@ mlk_status adjoint_run(mlk_sim* s, int kind, const double* weights, int64_t T_st
   s->adj_forward_ms = f_ms;
   s->adj_reverse_ms = r_ms;
   // back to the state before the call
-  STCHK(load_state(s, ckpt.p, MLK_MEM_DEVICE));
+  STCHK(load_state(s, ckpt, MLK_MEM_DEVICE));
   s->host_step = step0;
   STCHK(sync_sim(s));
-  if (nb && grad_eps) HIPCHK(hipMemcpy(grad_eps, geps.p, nb * sizeof(double), hipMemcpyDeviceToHost));
+  if (nb && grad_eps) HIPCHK(hipMemcpy(grad_eps, geps, nb * sizeof(double), hipMemcpyDeviceToHost));
   if (grad_dip) {
     std::vector<double> g((size_t)3 * nt);
-    if (nt) HIPCHK(hipMemcpy(g.data(), gd.p, g.size() * sizeof(double), hipMemcpyDeviceToHost));
+    if (nt) HIPCHK(hipMemcpy(g.data(), gd, g.size() * sizeof(double), hipMemcpyDeviceToHost));
     for (int e = 0; e < 3 * M; ++e) grad_dip[e] = 0.0;
     for (int m = 0; m < nt; ++m)
       for (int c = 0; c < 3; ++c) grad_dip[3 * s->tls_gid[m] + c] = g[3 * m + c];
