@@ -71,20 +71,21 @@ __global__ void k_windows(int count, const double* pos, const double* sigma, dou
   len[slot] = L;
 }
 
-// One thread per (emitter, axis, variant): the union-window record of the
-// binned kernels (see WinRec).
+// One thread per (record, axis, variant): the union-window records of the binned kernels (see
+// WinRec), record q that of emitter em[q].
 template <typename T>
-__global__ void k_records(int count, const int* lo, const int* len, const T* w, WinRec<T>* rec) {
+__global__ void k_records(int count, const int* em, const int* lo, const int* len, const T* w,
+                          WinRec<T>* rec) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= count * 6) return;
-  const int m = t / 6, a = (t / 2) % 3, v = t % 2;
+  const int q = t / 6, m = em[q], a = (t / 2) % 3, v = t % 2;
   const int lo0 = lo[win_slot(m, a, 0)], n0 = len[win_slot(m, a, 0)];
   const int lo1 = lo[win_slot(m, a, 1)], n1 = len[win_slot(m, a, 1)];
   const int org = min(lo0, lo1);
   const int end = max(lo0 + n0, lo1 + n1);
   const int l = v ? lo1 : lo0, n = v ? n1 : n0;
   const T* wv = w + (size_t)win_slot(m, a, v) * kMaxWin;
-  WinRec<T>& r = rec[m];
+  WinRec<T>& r = rec[q];
   for (int d = 0; d < kMaxWin; ++d) {
     const int k = org + d - l;
     r.wr[a][d][v] = (k >= 0 && k < n) ? wv[k] : T(0);
@@ -145,20 +146,20 @@ hipError_t windows_f64(int count, const double* pos, const double* sigma, double
 }
 
 template <typename T>
-static hipError_t launch_records(int count, const int* lo, const int* len, const T* w,
+static hipError_t launch_records(int count, const int* em, const int* lo, const int* len, const T* w,
                                  WinRec<T>* rec, hipStream_t st) {
   if (count <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_records<T>, dim3((count * 6 + 255) / 256), dim3(256), 0, st, count, lo, len,
-                     w, rec);
+  hipLaunchKernelGGL(k_records<T>, dim3((count * 6 + 255) / 256), dim3(256), 0, st, count, em, lo,
+                     len, w, rec);
   return hipGetLastError();
 }
-hipError_t records_f64(int count, const int* lo, const int* len, const double* w,
+hipError_t records_f64(int count, const int* em, const int* lo, const int* len, const double* w,
                        WinRec<double>* rec, hipStream_t st) {
-  return launch_records<double>(count, lo, len, w, rec, st);
+  return launch_records<double>(count, em, lo, len, w, rec, st);
 }
-hipError_t records_f32(int count, const int* lo, const int* len, const float* w,
+hipError_t records_f32(int count, const int* em, const int* lo, const int* len, const float* w,
                        WinRec<float>* rec, hipStream_t st) {
-  return launch_records<float>(count, lo, len, w, rec, st);
+  return launch_records<float>(count, em, lo, len, w, rec, st);
 }
 hipError_t windows_f32(int count, const double* pos, const double* sigma, double R, const Geom& g,
                        int* lo, int* len, float* w, hipStream_t st) {

@@ -51,9 +51,9 @@ hipError_t windows_f64(int count, const double* pos, const double* sigma, double
                        int* lo, int* len, double* w, hipStream_t st);
 hipError_t windows_f32(int count, const double* pos, const double* sigma, double R, const Geom& g,
                        int* lo, int* len, float* w, hipStream_t st);
-hipError_t records_f64(int count, const int* lo, const int* len, const double* w,
+hipError_t records_f64(int count, const int* em, const int* lo, const int* len, const double* w,
                        WinRec<double>* rec, hipStream_t st);
-hipError_t records_f32(int count, const int* lo, const int* len, const float* w,
+hipError_t records_f32(int count, const int* em, const int* lo, const int* len, const float* w,
                        WinRec<float>* rec, hipStream_t st);
 hipError_t scatter_atomic_f64(const FieldPtrs<double>& f, const Geom& g,
                               const WindowPtrs<double>& win, int count, const double* mudot,

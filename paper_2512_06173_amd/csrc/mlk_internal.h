@@ -420,17 +420,6 @@ __device__ __forceinline__ J load_job(const J* jobs, int j) {
 #endif
 }
 
-// A scatter pair: emitter e, where its record's weights lie (in 16-byte units from the first
-// record), and per axis the offset of its union window in the bin, o = (window offset) -
-// (bin-local cell), as a signed byte at bit 8 a of off.
-struct PairDesc {
-  int e;
-  int off;
-  unsigned rec;
-  int pad;
-};
-static_assert(sizeof(PairDesc) == 16, "a pair is loaded as one int4");
-
 // scatter bins, one per wavefront
 constexpr int kScX = 16, kScY = 4, kScZ = 4, kScWaves = 4;
 

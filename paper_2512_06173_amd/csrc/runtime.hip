@@ -19,6 +19,7 @@
 #include <vector>
 #include <mutex>
 
+#include "emitter_bins.h"
 #include "launch.h"
 #include "mlk.h"
 
@@ -190,7 +191,7 @@ struct mlk_sim {
   int* d_gbin_org = nullptr;
   int* d_gbin_start = nullptr;
   int* d_gbin_em = nullptr;
-  int4* d_sbin = nullptr;
+  BinSlot* d_sbin = nullptr;
   PairDesc* d_sbin_pair = nullptr;
   int* d_tls_slot = nullptr;
 
@@ -383,309 +384,58 @@ BinPtrs bin_ptrs(const mlk_sim* s) {
   b.gbin_start = s->d_gbin_start;
   b.gbin_em = s->d_gbin_em;
   b.nscatter = s->nscatter;
-  b.sbin = s->d_sbin;
+  b.sbin = reinterpret_cast<const int4*>(s->d_sbin);
   b.sbin_pair = reinterpret_cast<const int4*>(s->d_sbin_pair);
   return b;
 }
 
-// Union windows of the emitters as the binned kernels see them: origin and
-// length per axis, read back from the records.
-template <typename T>
-mlk_status read_unions(const mlk_sim* s, std::vector<int>& org, std::vector<int>& n) {
-  std::vector<WinRec<T>> rec(s->nem);
-  if (s->nem > 0)
-    HIPCHK(hipMemcpy(rec.data(), s->d_rec, rec.size() * sizeof(WinRec<T>),
-                     hipMemcpyDeviceToHost));
-  for (int e = 0; e < s->nem; ++e)
-    for (int a = 0; a < 3; ++a) {
-      org[3 * e + a] = rec[e].org[a];
-      n[3 * e + a] = rec[e].n[a];
-    }
-  return MLK_OK;
-}
-
-// The records in the order em: those of a gather bin, and nearly those of a scatter bin,
-// lie side by side.
-template <typename T>
-mlk_status order_records(mlk_sim* s, const std::vector<int>& em) {
-  if (em.empty()) return MLK_OK;
-  std::vector<WinRec<T>> rec(em.size()), out(em.size());
-  HIPCHK(hipMemcpy(rec.data(), s->d_rec, rec.size() * sizeof(WinRec<T>), hipMemcpyDeviceToHost));
-  for (size_t q = 0; q < em.size(); ++q) out[q] = rec[em[q]];
-  HIPCHK(hipMemcpy(s->d_rec, out.data(), out.size() * sizeof(WinRec<T>), hipMemcpyHostToDevice));
-  return MLK_OK;
-}
-
-// Emitter bins (index bookkeeping only).  Gather bins group emitters by the
-// bin of their centre cell; scatter bins list, for every bin, the emitters
-// whose windows (as computed on the device) touch it.
+// The bins of the gather and the scatter (emitter_bins.h) from the windows that the device
+// has formed.
 mlk_status build_bins(mlk_sim* s) {
-  const Geom& g = s->g;
-  int G[3], B[3];
-  bin_shape(s->fp32, G, B);
-  int nb[3];
-  for (int a = 0; a < 3; ++a) nb[a] = (g.n[a] + B[a] - 1) / B[a];
-  s->nbx = nb[0];
-  s->nby = nb[1];
-  s->nbz = nb[2];
   const int M = s->nem;
-
-  // gather: key = bin of the (unwrapped) centre cell
-  struct Key {
-    int b[3];
-    int e;
-  };
-  std::vector<Key> keys(M);
-  for (int e = 0; e < M; ++e) {
-    keys[e].e = e;
-    for (int a = 0; a < 3; ++a) {
-      const int c = (int)std::floor(s->pos[3 * e + a]);
-      keys[e].b[a] = (c >= 0 ? c : c - G[a] + 1) / G[a];
-    }
+  std::vector<int> lo((size_t)6 * M), len((size_t)6 * M), org((size_t)3 * M), n((size_t)3 * M);
+  HIPCHK(hipMemcpy(lo.data(), s->d_wlo, lo.size() * sizeof(int), hipMemcpyDeviceToHost));
+  HIPCHK(hipMemcpy(len.data(), s->d_wlen, len.size() * sizeof(int), hipMemcpyDeviceToHost));
+  for (size_t q = 0; q < org.size(); ++q) {  // the union of an axis's two windows
+    const int l0 = lo[2 * q], l1 = lo[2 * q + 1];
+    org[q] = std::min(l0, l1);
+    n[q] = std::min(std::max(l0 + len[2 * q], l1 + len[2 * q + 1]) - org[q], kMaxWin);
   }
-  std::stable_sort(keys.begin(), keys.end(), [](const Key& x, const Key& y) {
-    if (x.b[2] != y.b[2]) return x.b[2] < y.b[2];
-    if (x.b[1] != y.b[1]) return x.b[1] < y.b[1];
-    return x.b[0] < y.b[0];
-  });
-  std::vector<int> gorg, gstart, gem;
-  for (int q = 0; q < M; ++q) {
-    if (q == 0 || keys[q].b[0] != keys[q - 1].b[0] || keys[q].b[1] != keys[q - 1].b[1] ||
-        keys[q].b[2] != keys[q - 1].b[2]) {
-      gstart.push_back(q);
-      for (int a = 0; a < 3; ++a) gorg.push_back(keys[q].b[a] * G[a]);
-    }
-    gem.push_back(keys[q].e);
-  }
-  gstart.push_back(M);
-  {
-    // light bins (at most gather_light_max() emitters) after the others, keeping the
-    // order within each kind: the heavier bins are dispatched first
-    const int light_max = gather_light_max();
-    const int nbin = (int)gstart.size() - 1;
-    std::vector<int> org2, start2, em2;
-    for (int pass = 0; pass < 2; ++pass) {
-      for (int b = 0; b < nbin; ++b) {
-        const bool light = gstart[b + 1] - gstart[b] <= light_max;
-        if (light != (pass == 1)) continue;
-        start2.push_back((int)em2.size());
-        for (int a = 0; a < 3; ++a) org2.push_back(gorg[3 * b + a]);
-        for (int q = gstart[b]; q < gstart[b + 1]; ++q) em2.push_back(gem[q]);
-      }
-      if (pass == 0) s->gdense = (int)start2.size();
-    }
-    start2.push_back((int)em2.size());
-    gorg.swap(org2);
-    gstart.swap(start2);
-    gem.swap(em2);
-    s->ngather = nbin;
-    // the light bins' emitters, one run of gem (the forward gather serves them
-    // without a tile)
-    s->glight0 = gstart[s->gdense];
-    s->nlight = M - s->glight0;
-    // work of launch block q of the staged bins (taken through the kernel's XCD
-    // order): its emitter count
-    const int nd = s->gdense, q8 = nd / 8;
-    s->gwork.assign(nd, 0.f);
-    for (int q = 0; q < nd; ++q) {
-      const int bin = q < 8 * q8 ? (q % 8) * q8 + q / 8 : q;
-      s->gwork[q] = (float)(gstart[bin + 1] - gstart[bin]);
-    }
-  }
-
-  // scatter: the union window of each emitter (org, n per axis, as in its
-  // record) split, per axis, into runs inside one bin: consecutive window
-  // offsets on consecutive cells.  A pair is one run per axis; a window wraps
-  // inside a bin only on a periodic axis no longer than the bin, where it gives
-  // two runs.
-  std::vector<int> worg((size_t)M * 3), wn((size_t)M * 3);
-  if (s->fp32)
-    STCHK(read_unions<float>(s, worg, wn));
-  else
-    STCHK(read_unions<double>(s, worg, wn));
+  BinSpec sp{};
   for (int a = 0; a < 3; ++a) {
-    const int n = g.n[a];
-    s->wplane[a].assign(n, 0);
-    for (int e = 0; e < M; ++e)
-      for (int d = 0; d < wn[3 * e + a]; ++d) {
-        int q = worg[3 * e + a] + d;
-        if (g.periodic[a]) q = ((q % n) + n) % n;
-        if (q >= 0 && q < n) s->wplane[a][q] = 1;
-      }
+    sp.n[a] = s->g.n[a];
+    sp.periodic[a] = s->g.periodic[a];
   }
-  // how far a window reaches beyond its emitter's centre cell
-  s->reach = 0;
-  for (int e = 0; e < M; ++e)
-    for (int a = 0; a < 3; ++a) {
-      const int c = (int)std::floor(s->pos[3 * e + a]), o = worg[3 * e + a];
-      s->reach = std::max(s->reach, std::max(c - o, o + wn[3 * e + a] - 1 - c));
-    }
-  if (s->reach > kHalo) return fail(MLK_EUNSUPPORTED, "a kernel window reaches %d cells", s->reach);
+  bin_shape(s->fp32, sp.G, sp.S);
+  sp.halo = kHalo;
+  sp.light_max = gather_light_max();
+  sp.waves = kScWaves;
+  sp.limit = scatter_shared();
+  sp.deal = s->fp32;
+  sp.rec16 = (s->fp32 ? sizeof(WinRec<float>) : sizeof(WinRec<double>)) / 16;
+  sp.w16 = (s->fp32 ? offsetof(WinRec<float>, wr) : offsetof(WinRec<double>, wr)) / 16;
+  EmitterBins b;
+  if (const char* e = build_emitter_bins(sp, M, s->pos.data(), org.data(), n.data(), b))
+    return fail(MLK_EUNSUPPORTED, "%s", e);
+  s->nbx = b.nb[0];
+  s->nby = b.nb[1];
+  s->nbz = b.nb[2];
+  s->ngather = (int)b.gstart.size() - 1;
+  s->gdense = b.gdense;
+  s->glight0 = b.glight0;
+  s->nlight = M - b.glight0;
+  s->reach = b.reach;
+  s->nscatter = (int)b.swork.size();
   // a batch's launch order: the light bins' workgroups come last
-  s->gwork.resize(s->gdense + gather_light_blocks(s->fp32, s->reach, s->nlight), 0.f);
-  // FP32 gather: the eight emitters of a wavefront read their window rows from the
-  // staged tile at the same row and plane offsets, so lane i of emitter m reads word
-  // s_m + i + (a common offset), and emitters whose windows start in the same LDS
-  // banks conflict.  The bank of s_m is its tile index mod 64.  Within a staged bin, the
-  // emitters are sorted by that bank and dealt to the wavefronts with a stride, so
-  // those of one wavefront (and of each half) start in banks spread around the 64.
-  // Only the assignment of emitters to lanes changes, not any result.
-  if (s->fp32) {
-    const int TXg = G[0] + 2 * kHalo, R = s->reach <= 3 ? 3 : 4, PSg = TXg * (G[1] + 2 * R);
-    std::vector<std::pair<int, int>> v;
-    for (int b = 0; b < s->gdense; ++b) {
-      const int q0 = gstart[b], q1 = gstart[b + 1], n = q1 - q0;
-      const int x0 = gorg[3 * b] - kHalo, y0 = gorg[3 * b + 1] - R, z0 = gorg[3 * b + 2] - R;
-      v.clear();
-      for (int q = q0; q < q1; ++q) {
-        const int e = gem[q];
-        v.push_back({((worg[3 * e] - x0) + TXg * (worg[3 * e + 1] - y0) +
-                      PSg * (worg[3 * e + 2] - z0)) & 63, e});
-      }
-      std::stable_sort(v.begin(), v.end(), [](const std::pair<int, int>& x,
-                                              const std::pair<int, int>& y) {
-        return x.first < y.first;
-      });
-      const int nw = (n + 7) / 8;
-      int q = q0;
-      for (int w = 0; w < nw; ++w)
-        for (int k = 0; k < 8; ++k)
-          if (w + k * nw < n) gem[q++] = v[w + k * nw].second;
-    }
-  }
-  struct Run {
-    int bin, l0, d0, c;
-  };
-  auto runs_of = [&](int e, int a, std::vector<Run>& out) {
-    out.clear();
-    for (int d = 0; d < wn[3 * e + a]; ++d) {
-      int w = (worg[3 * e + a] + d) % g.n[a];
-      if (w < 0) w += g.n[a];
-      const int bq = w / B[a], l = w - bq * B[a];
-      if (!out.empty()) {
-        Run& r = out.back();
-        if (r.bin == bq && r.d0 + r.c == d && r.l0 + r.c == l) {
-          ++r.c;
-          continue;
-        }
-      }
-      out.push_back({bq, l, d, 1});
-    }
-  };
-  const size_t nball = (size_t)nb[0] * nb[1] * nb[2];
-  std::vector<std::vector<std::pair<int, PairDesc>>> per_em(M);  // (bin, pair)
-  std::vector<Run> rx, ry, rz;
-  for (int e = 0; e < M; ++e) {
-    runs_of(e, 0, rx);
-    runs_of(e, 1, ry);
-    runs_of(e, 2, rz);
-    for (const Run& z : rz)
-      for (const Run& y : ry)
-        for (const Run& x : rx) {
-          PairDesc pd{};
-          pd.e = e;
-          pd.off = ((x.d0 - x.l0) & 255) | ((y.d0 - y.l0) & 255) << 8 |
-                   ((z.d0 - z.l0) & 255) << 16;
-          per_em[e].push_back({x.bin + nb[0] * (y.bin + nb[1] * z.bin), pd});
-        }
-  }
-  std::vector<int> count(nball, 0);
-  size_t npairs = 0;
-  for (int e = 0; e < M; ++e)
-    for (const auto& bp : per_em[e]) {
-      ++count[bp.first];
-      ++npairs;
-    }
-  if (npairs > (size_t)INT32_MAX) return fail(MLK_EUNSUPPORTED, "too many emitter-bin pairs");
-  std::vector<int> sid, sstart(1, 0), slot_of(nball, -1);
-  for (size_t b = 0; b < nball; ++b)
-    if (count[b]) {
-      slot_of[b] = (int)sid.size();
-      sid.push_back((int)b);
-      sstart.push_back(sstart.back() + count[b]);
-    }
-  std::vector<int> fill(sstart.begin(), sstart.end() - 1);
-  std::vector<PairDesc> spair(npairs);
-  // emitters in gather order, so neighbouring pairs touch neighbouring windows
-  const unsigned rec16 = (s->fp32 ? sizeof(WinRec<float>) : sizeof(WinRec<double>)) / 16;
-  const unsigned w16 = (s->fp32 ? offsetof(WinRec<float>, wr) : offsetof(WinRec<double>, wr)) / 16;
-  if ((size_t)M * rec16 > UINT32_MAX) return fail(MLK_EUNSUPPORTED, "too many emitters");
-  for (int q = 0; q < M; ++q)
-    for (const auto& bp : per_em[gem[q]]) {
-      PairDesc& pd = spair[fill[slot_of[bp.first]]++];
-      pd = bp.second;
-      pd.rec = (unsigned)q * rec16 + w16;
-    }
-  // The launch's order of bins, kScWaves to a workgroup, or a workgroup to a bin of more than
-  // scatter_shared() pairs.  Workgroups go to the eight XCDs in turn, and neighbouring bins
-  // share records and lines of E, so each XCD takes an eighth of the bins of both kinds,
-  // neighbours in space; within it the heaviest first (in steps of 32 pairs, so that
-  // neighbours stay together), as the light ones then fill in behind them.  Work of a bin: its
-  // pairs and, in the same unit, what every bin costs.  Where the eighths differ by more
-  // than a quarter in work, the heaviest of all go first instead.
-  std::vector<int4> sbin;
-  s->swork.clear();
-  {
-    std::vector<int> kind[2];  // bins that wavefronts take, and that workgroups take
-    const int limit = scatter_shared();
-    for (int sl = 0; sl < (int)sid.size(); ++sl)
-      kind[sstart[sl + 1] - sstart[sl] > limit].push_back(sl);
-    const int nsh = (int)kind[1].size(), nlt = (int)kind[0].size();
-    const int nblk = nsh + (nlt + kScWaves - 1) / kScWaves;
-    auto work = [&](int sl) { return sl < 0 ? 0 : 16 + sstart[sl + 1] - sstart[sl]; };
-    auto heavier = [&](int x, int y) { return work(x) / 32 > work(y) / 32; };
-    std::vector<int> sh[8], lt[8];
-    double most = 0.0, total = 0.0;
-    for (int x = 0, qs = 0, ql = 0; x < 8; ++x) {
-      const int blocks = nblk / 8 + (x < nblk % 8), mine = nsh / 8 + (x < nsh % 8);
-      double w = 0.0;
-      for (const int end = qs + mine; qs < end; ++qs) sh[x].push_back(kind[1][qs]);
-      for (const int end = ql + kScWaves * (blocks - mine); ql < end; ++ql)
-        lt[x].push_back(ql < nlt ? kind[0][ql] : -1);
-      for (int sl : sh[x]) w += work(sl);
-      for (int sl : lt[x]) w += work(sl);
-      most = std::max(most, w);
-      total += w;
-    }
-    if (most > 1.25 * total / 8) {
-      // one order over all, dealt to the eight in turn
-      std::stable_sort(kind[1].begin(), kind[1].end(), heavier);
-      std::stable_sort(kind[0].begin(), kind[0].end(), heavier);
-      kind[0].resize((size_t)kScWaves * (nblk - nsh), -1);
-      for (int x = 0; x < 8; ++x) {
-        sh[x].clear();
-        lt[x].clear();
-      }
-      for (int b = 0; b < nblk; ++b)
-        if (b < nsh) sh[b % 8].push_back(kind[1][b]);
-        else
-          for (int k = 0; k < kScWaves; ++k)
-            lt[b % 8].push_back(kind[0][(size_t)kScWaves * (b - nsh) + k]);
-    } else {
-      for (int x = 0; x < 8; ++x) {
-        std::stable_sort(sh[x].begin(), sh[x].end(), heavier);
-        std::stable_sort(lt[x].begin(), lt[x].end(), heavier);
-      }
-    }
-    for (int b = 0; b < nblk; ++b) {
-      const int x = b % 8, q = b / 8, ns = (int)sh[x].size();
-      float w = 0.f;
-      for (int k = 0; k < kScWaves; ++k) {
-        const int sl = q < ns ? sh[x][q] : lt[x][(size_t)kScWaves * (q - ns) + k];
-        sbin.push_back(sl < 0 ? make_int4(0, 0, 0, 0)
-                              : make_int4(sid[sl], sstart[sl], sstart[sl + 1], q < ns));
-        w = std::max(w, (float)(work(sl) / 32));
-      }
-      s->swork.push_back(w);
-    }
-    s->nscatter = nblk;
-  }
-  STCHK(s->fp32 ? order_records<float>(s, gem) : order_records<double>(s, gem));
-  STCHK(upload(&s->d_gbin_org, gorg));
-  STCHK(upload(&s->d_gbin_start, gstart));
-  STCHK(upload(&s->d_gbin_em, gem));
-  STCHK(upload(&s->d_sbin, sbin));
-  STCHK(upload(&s->d_sbin_pair, spair));
+  b.gwork.resize(s->gdense + gather_light_blocks(s->fp32, s->reach, s->nlight), 0.f);
+  s->gwork = std::move(b.gwork);
+  s->swork = std::move(b.swork);
+  for (int a = 0; a < 3; ++a) s->wplane[a] = std::move(b.wplane[a]);
+  STCHK(upload(&s->d_gbin_org, b.gorg));
+  STCHK(upload(&s->d_gbin_start, b.gstart));
+  STCHK(upload(&s->d_gbin_em, b.gem));
+  STCHK(upload(&s->d_sbin, b.sbin));
+  STCHK(upload(&s->d_sbin_pair, b.spair));
   STCHK(upload(&s->d_tls_slot, s->tls_slot));
   return MLK_OK;
 }
@@ -774,18 +524,21 @@ mlk_status rebuild_emitters(mlk_sim* s) {
   else
     HIPCHK(windows_f64(M, s->d_pos, s->d_sigma, s->desc.window_r, s->g, s->d_wlo, s->d_wlen,
                        (double*)s->d_w, s->stream));
+  STCHK(sync_sim(s));
+  STCHK(build_bins(s));
+  // the records in the gather's order of the emitters: those of a gather bin, and nearly
+  // those of a scatter bin, lie side by side
   dfree(s->d_rec);
   if (s->fp32) {
     HIPCHK(dalloc(&s->d_rec, (size_t)M * sizeof(WinRec<float>)));
-    HIPCHK(records_f32(M, s->d_wlo, s->d_wlen, (const float*)s->d_w, (WinRec<float>*)s->d_rec,
-                       s->stream));
+    HIPCHK(records_f32(M, s->d_gbin_em, s->d_wlo, s->d_wlen, (const float*)s->d_w,
+                       (WinRec<float>*)s->d_rec, s->stream));
   } else {
     HIPCHK(dalloc(&s->d_rec, (size_t)M * sizeof(WinRec<double>)));
-    HIPCHK(records_f64(M, s->d_wlo, s->d_wlen, (const double*)s->d_w, (WinRec<double>*)s->d_rec,
-                       s->stream));
+    HIPCHK(records_f64(M, s->d_gbin_em, s->d_wlo, s->d_wlen, (const double*)s->d_w,
+                       (WinRec<double>*)s->d_rec, s->stream));
   }
-  STCHK(sync_sim(s));
-  return build_bins(s);
+  return sync_sim(s);
 }
 
 // Grow the on-device series buffers so that nsteps more steps fit.
