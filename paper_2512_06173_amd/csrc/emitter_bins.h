@@ -13,7 +13,8 @@
 
 namespace mlk {
 
-// A scatter pair: emitter e, where its record's weights lie (in 16-byte units from the first
+// A scatter pair: emitter e (its place in the gather's order where the amplitudes are put in
+// that order, see scatter_amps), where its record's weights lie (in 16-byte units from the first
 // record), and per axis the offset of its union window in the bin, o = (window offset) -
 // (bin-local cell), as a signed byte at bit 8 a of off.
 struct PairDesc {
@@ -38,6 +39,7 @@ struct BinSpec {
   int light_max;          // gather bins of at most this many emitters are light
   int waves, limit;       // wavefronts of a scatter workgroup; pairs beyond which they share a bin
   bool deal;              // deal the emitters of a gather bin to wavefronts by LDS bank (FP32)
+  bool places;            // pairs name an emitter by its place
   unsigned rec16, w16;    // 16-byte units of a record, and those before its weights
 };
 
@@ -218,7 +220,7 @@ inline const char* build_emitter_bins(const BinSpec& sp, int M, const double* po
   for (int q = 0; q < M; ++q) {
     const int e = out.gem[q];
     each_pair(e, [&](size_t b, int off) {
-      out.spair[at[b]++] = {e, off, (unsigned)q * sp.rec16 + sp.w16, 0};
+      out.spair[at[b]++] = {sp.places ? q : e, off, (unsigned)q * sp.rec16 + sp.w16, 0};
     });
   }
 

@@ -29,6 +29,30 @@ void bin_shape(bool fp32, int G[3], int S[3]) {
 // 13.8, 33.5.
 int scatter_shared() { return 128; }
 
+// Every pair of an emitter fetches its gamma and mu_dot, 8.6 times in all, and in the emitters'
+// own order each time from some other line; beyond what an L2 holds these trips weigh more than
+// the rest.  Larger ensembles put the amplitudes in the gather's order first, where those of
+// a bin's pairs lie together.  In 128^3 cells, us without and with: FP32 100,000 emitters 39.0,
+// 40.9; 200,000 75.5, 75.9; 300,000 112.9, 98.8; 1,000,000 504, 351; FP64 200,000 143, 147;
+// 300,000 185, 193; 1,000,000 687, 545.
+int scatter_amps_min(bool fp32) { return fp32 ? 262144 : 524288; }
+
+__global__ __launch_bounds__(256) void k_scatter_amps(BinPtrs bins, const double* gamma,
+                                                      const double* a, double amp0) {
+  const unsigned t = blockIdx.x * 256u + threadIdx.x, q = t / 3u;
+  if (q >= (unsigned)bins.nem) return;
+  const int e = bins.gbin_em[q];
+  bins.amp[t] = amp0 * gamma[e] * a[3 * (size_t)e + (t - 3u * q)];
+}
+
+hipError_t scatter_amps(const BinPtrs& b, const double* gamma, const double* a, double amp0,
+                        hipStream_t st) {
+  if (!b.amp || b.nem <= 0) return hipSuccess;
+  const unsigned blocks = (unsigned)(((size_t)3 * b.nem + 255) / 256);
+  hipLaunchKernelGGL(k_scatter_amps, dim3(blocks), dim3(256), 0, st, b, gamma, a, amp0);
+  return hipGetLastError();
+}
+
 __global__ __launch_bounds__(256) void k_tls_step(TlsPtrs tls, double dt, const double* Et,
                                                   double* mudot, const int64_t* pop_off,
                                                   Series ser, StepNo n) {
@@ -114,7 +138,8 @@ struct Mfma<double> {
 //
 // Blocks from bins.nscatter on (when more is given) form the flux partials of the plane, in
 // the LDS of the weights, and then the soft sources.
-template <typename T, bool EPS = true>
+// AMPS: amplitudes in the gather's order where the bins have them (see scatter_amps).
+template <typename T, bool AMPS, bool EPS = true>
 __device__ __forceinline__ void scatter_body(const FieldPtrs<T>& f, const Geom& g,
                                              const BinPtrs& bins, const WindowPtrs<T>& win,
                                              const double* mudot, double amp0, int bid,
@@ -182,8 +207,11 @@ __device__ __forceinline__ void scatter_body(const FieldPtrs<T>& f, const Geom& 
   int2 apd = make_int2(0, 0);
   int aoff = 0;
   piece_t piece[NP];
-  double pg = 0.0, pm = 0.0;
+  double pg = 1.0, pm = 0.0;
   const int apair = lane / 3, acomp = lane % 3;  // lanes below 3 P: a pair's amplitudes
+  const bool ordered = AMPS && bins.amp;
+  const double* const amps = ordered ? bins.amp : mudot;
+  const double scale = (ordered ? 1.0 : amp0) * kAmpScale;
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
     slot[p] = (lane + p * 64) / R4;
@@ -199,8 +227,8 @@ __device__ __forceinline__ void scatter_body(const FieldPtrs<T>& f, const Geom& 
     for (int p = 0; p < NP; ++p)
       piece[p] = reinterpret_cast<const piece_t*>(win.rec)[(unsigned)(rec[p] + part[p])];
     aoff = apd.y;
-    pg = win.gamma[apd.x];
-    pm = mudot[3 * apd.x + acomp];
+    if (!ordered) pg = win.gamma[apd.x];
+    pm = amps[3 * apd.x + acomp];
   };
   auto begin = [&] {
     load_pairs(q0);
@@ -225,7 +253,7 @@ __device__ __forceinline__ void scatter_body(const FieldPtrs<T>& f, const Geom& 
     if (lane < 3 * P) {
       // an amplitude that is no number adds nothing (times the zeros beside its window
       // it would spoil the whole bin), nor does what fills up the last step
-      const double v = amp0 * pg * pm * kAmpScale;
+      const double v = scale * pg * pm;
       T a = (T)v;
       if constexpr (sizeof(T) == 4) a = __builtin_amdgcn_fmed3f(a, -kAmpMax, kAmpMax);
       sAmp[wave][apair][acomp] = apair < cn && fabs(v) <= 1.7976931348623157e308 ? a : T(0);
@@ -384,21 +412,22 @@ __device__ __forceinline__ void scatter_body(const FieldPtrs<T>& f, const Geom& 
         f.E[c][cell + r * step] = ev[r][c] - ei[r] * (acc[c][r] * T(1 / kAmpScale));
 }
 
-template <typename T>
+template <typename T, bool AMPS>
 __global__ __launch_bounds__(kThreads, ScatterCfg<T>::waves) void k_scatter_bins(
     FieldPtrs<T> f, Geom g, BinPtrs bins, WindowPtrs<T> win, const double* mudot) {
-  scatter_body(f, g, bins, win, mudot, g.dt * g.inv_dx * g.inv_dx * g.inv_dx, blockIdx.x);
+  scatter_body<T, AMPS>(f, g, bins, win, mudot, g.dt * g.inv_dx * g.inv_dx * g.inv_dx, blockIdx.x);
 }
 
 // The scatter with the flux partials and the soft sources in more workgroups.
-template <typename T>
+template <typename T, bool AMPS>
 __global__ __launch_bounds__(kThreads, ScatterCfg<T>::waves) void k_scatter_more(
     FieldPtrs<T> f, Geom g, BinPtrs bins, WindowPtrs<T> win, const double* mudot,
     ScatterMore more) {
-  scatter_body(f, g, bins, win, mudot, g.dt * g.inv_dx * g.inv_dx * g.inv_dx, blockIdx.x, &more);
+  scatter_body<T, AMPS>(f, g, bins, win, mudot, g.dt * g.inv_dx * g.inv_dx * g.inv_dx, blockIdx.x,
+                        &more);
 }
 
-template <typename T>
+template <typename T, bool AMPS>
 __global__ __launch_bounds__(kThreads, ScatterCfg<T>::waves) void k_scatter_batch(
     const ScatterJob<T>* jobs, const int* start, int njobs, const int2* order) {
   int j, bid;
@@ -412,8 +441,8 @@ __global__ __launch_bounds__(kThreads, ScatterCfg<T>::waves) void k_scatter_batc
     if (bid >= jobs[j].nblocks) return;
   }
   const ScatterJob<T> J = load_job(jobs, j);
-  scatter_body(J.f, J.g, J.bins, J.win, J.mudot, J.g.dt * J.g.inv_dx * J.g.inv_dx * J.g.inv_dx,
-               bid);
+  scatter_body<T, AMPS>(J.f, J.g, J.bins, J.win, J.mudot,
+                        J.g.dt * J.g.inv_dx * J.g.inv_dx * J.g.inv_dx, bid);
 }
 
 hipError_t tls_step(const TlsPtrs& tls, double dt, const double* Et, double* mudot,
@@ -429,15 +458,21 @@ static hipError_t launch_scatter(const FieldPtrs<T>& f, const Geom& g, const Bin
                                  const WindowPtrs<T>& win, const double* mudot,
                                  ScatterMore more, hipStream_t st) {
   if (b.nscatter <= 0) return hipSuccess;
+  const hipError_t e =
+      scatter_amps(b, win.gamma, mudot, g.dt * g.inv_dx * g.inv_dx * g.inv_dx, st);
+  if (e != hipSuccess) return e;
   more.flux = more.flux && more.fp.on && more.fp.nblocks > 0;
   more.sblocks = source_blocks(g, more.src);
   const int nmore = (more.flux ? more.fp.nblocks : 0) + more.src.count * more.sblocks;
-  if (nmore > 0)
-    hipLaunchKernelGGL(k_scatter_more<T>, dim3(b.nscatter + nmore), dim3(kThreads), 0, st, f, g, b,
-                       win, mudot, more);
+  const dim3 grid(b.nscatter + nmore), block(kThreads);
+  if (nmore > 0 && b.amp)
+    hipLaunchKernelGGL((k_scatter_more<T, true>), grid, block, 0, st, f, g, b, win, mudot, more);
+  else if (nmore > 0)
+    hipLaunchKernelGGL((k_scatter_more<T, false>), grid, block, 0, st, f, g, b, win, mudot, more);
+  else if (b.amp)
+    hipLaunchKernelGGL((k_scatter_bins<T, true>), grid, block, 0, st, f, g, b, win, mudot);
   else
-    hipLaunchKernelGGL(k_scatter_bins<T>, dim3(b.nscatter), dim3(kThreads), 0, st, f, g, b, win,
-                       mudot);
+    hipLaunchKernelGGL((k_scatter_bins<T, false>), grid, block, 0, st, f, g, b, win, mudot);
   return hipGetLastError();
 }
 
@@ -454,20 +489,24 @@ hipError_t bin_scatter_f32(const FieldPtrs<float>& f, const Geom& g, const BinPt
 
 template <typename T>
 static hipError_t launch_scatter_batch(const ScatterJob<T>* jobs, const int* start, int njobs,
-                                       const int2* order, int nblocks, hipStream_t st) {
+                                       const int2* order, int nblocks, bool amps, hipStream_t st) {
   if (nblocks <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_scatter_batch<T>, dim3(nblocks), dim3(kThreads), 0, st, jobs, start, njobs,
-                     order);
+  if (amps)
+    hipLaunchKernelGGL((k_scatter_batch<T, true>), dim3(nblocks), dim3(kThreads), 0, st, jobs, start,
+                       njobs, order);
+  else
+    hipLaunchKernelGGL((k_scatter_batch<T, false>), dim3(nblocks), dim3(kThreads), 0, st, jobs, start,
+                       njobs, order);
   return hipGetLastError();
 }
 
 hipError_t scatter_batch_f64(const ScatterJob<double>* jobs, const int* start, int njobs,
-                             const int2* order, int nblocks, hipStream_t st) {
-  return launch_scatter_batch<double>(jobs, start, njobs, order, nblocks, st);
+                             const int2* order, int nblocks, bool amps, hipStream_t st) {
+  return launch_scatter_batch<double>(jobs, start, njobs, order, nblocks, amps, st);
 }
 hipError_t scatter_batch_f32(const ScatterJob<float>* jobs, const int* start, int njobs,
-                             const int2* order, int nblocks, hipStream_t st) {
-  return launch_scatter_batch<float>(jobs, start, njobs, order, nblocks, st);
+                             const int2* order, int nblocks, bool amps, hipStream_t st) {
+  return launch_scatter_batch<float>(jobs, start, njobs, order, nblocks, amps, st);
 }
 hipError_t tls_batch(const TlsJob* jobs, const int* start, int njobs, int nblocks,
                      hipStream_t st) {
@@ -477,18 +516,24 @@ hipError_t tls_batch(const TlsJob* jobs, const int* start, int njobs, int nblock
 }
 
 // ---- adjoint-step variants
-template <typename T>
+template <typename T, bool AMPS>
 __global__ __launch_bounds__(kThreads, ScatterCfg<T>::waves) void k_scatter_plain(
     FieldPtrs<T> f, Geom g, BinPtrs bins, WindowPtrs<T> win, const double* amp, double amp0) {
-  scatter_body<T, false>(f, g, bins, win, amp, amp0, blockIdx.x);
+  scatter_body<T, AMPS, false>(f, g, bins, win, amp, amp0, blockIdx.x);
 }
 template <typename T>
 static hipError_t launch_scatter_plain(const FieldPtrs<T>& f, const Geom& g, const BinPtrs& b,
                                        const WindowPtrs<T>& win, const double* amp, double amp0,
                                        hipStream_t st) {
   if (b.nscatter <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_scatter_plain<T>, dim3(b.nscatter), dim3(kThreads), 0, st, f, g, b, win,
-                     amp, amp0);
+  const hipError_t e = scatter_amps(b, win.gamma, amp, amp0, st);
+  if (e != hipSuccess) return e;
+  if (b.amp)
+    hipLaunchKernelGGL((k_scatter_plain<T, true>), dim3(b.nscatter), dim3(kThreads), 0, st, f, g, b,
+                       win, amp, amp0);
+  else
+    hipLaunchKernelGGL((k_scatter_plain<T, false>), dim3(b.nscatter), dim3(kThreads), 0, st, f, g, b,
+                       win, amp, amp0);
   return hipGetLastError();
 }
 hipError_t scatter_plain_f64(const FieldPtrs<double>& f, const Geom& g, const BinPtrs& b,

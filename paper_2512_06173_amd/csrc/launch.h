@@ -106,6 +106,8 @@ void bin_shape(bool fp32, int G[3], int S[3]);
 void gather_bin_shape(bool fp32, int G[3]);
 // A scatter bin of more pairs than this is shared by a workgroup's wavefronts.
 int scatter_shared();
+// From more emitters than this on, the scatter's amplitudes are put in order first.
+int scatter_amps_min(bool fp32);
 // Gather bins of at most this many emitters are light (no tile); the workgroups that
 // nlight of their emitters take.
 int gather_light_max();
@@ -146,10 +148,15 @@ hipError_t tls_batch(const TlsJob* jobs, const int* start, int njobs, int nblock
                      hipStream_t st);
 hipError_t ml_batch(const MlJob* jobs, const int* start, int njobs, int nblocks, int nl,
                     hipStream_t st);
+// The amplitudes amp0 gamma a of a scatter in the gather's order, into b.amp (if any).  The
+// launches of one sim do this themselves, a batched one needs it done.
+hipError_t scatter_amps(const BinPtrs& b, const double* gamma, const double* a, double amp0,
+                        hipStream_t st);
+// amps: whether any member's amplitudes are put in order
 hipError_t scatter_batch_f64(const ScatterJob<double>* jobs, const int* start, int njobs,
-                             const int2* order, int nblocks, hipStream_t st);
+                             const int2* order, int nblocks, bool amps, hipStream_t st);
 hipError_t scatter_batch_f32(const ScatterJob<float>* jobs, const int* start, int njobs,
-                             const int2* order, int nblocks, hipStream_t st);
+                             const int2* order, int nblocks, bool amps, hipStream_t st);
 hipError_t detect_batch_f64(const FluxJob<double>* jobs, const int* start, int njobs, int nblocks,
                             int kind, hipStream_t st);
 hipError_t detect_batch_f32(const FluxJob<float>* jobs, const int* start, int njobs, int nblocks,

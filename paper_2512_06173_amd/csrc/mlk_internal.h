@@ -402,6 +402,8 @@ struct BinPtrs {
   const int4* sbin;         // [kScWaves*nscatter] bin, first and end pair (equal: no bin),
                             // 1 if the four wavefronts of the workgroup share the bin
   const int4* sbin_pair;    // one PairDesc per (emitter, bin) pair
+  int nem;                  // emitters
+  double* amp;              // [3 nem] amplitudes in the order of gbin_em, or null (see scatter_amps)
 };
 
 // A batch kernel's job, read from its table through the constant address space.

@@ -175,6 +175,7 @@ struct mlk_sim {
   double* d_gamma = nullptr;
   double* d_Et = nullptr;
   double* d_mudot = nullptr;
+  double* d_amp = nullptr;  // the scatter's amplitudes in order, of large ensembles
   int64_t* d_popoff = nullptr;
   int* d_tls_gid = nullptr;
   double* d_tls_w0 = nullptr;
@@ -386,6 +387,8 @@ BinPtrs bin_ptrs(const mlk_sim* s) {
   b.nscatter = s->nscatter;
   b.sbin = reinterpret_cast<const int4*>(s->d_sbin);
   b.sbin_pair = reinterpret_cast<const int4*>(s->d_sbin_pair);
+  b.nem = s->nem;
+  b.amp = s->d_amp;
   return b;
 }
 
@@ -412,6 +415,7 @@ mlk_status build_bins(mlk_sim* s) {
   sp.waves = kScWaves;
   sp.limit = scatter_shared();
   sp.deal = s->fp32;
+  sp.places = M > scatter_amps_min(s->fp32);
   sp.rec16 = (s->fp32 ? sizeof(WinRec<float>) : sizeof(WinRec<double>)) / 16;
   sp.w16 = (s->fp32 ? offsetof(WinRec<float>, wr) : offsetof(WinRec<double>, wr)) / 16;
   EmitterBins b;
@@ -437,6 +441,8 @@ mlk_status build_bins(mlk_sim* s) {
   STCHK(upload(&s->d_sbin, b.sbin));
   STCHK(upload(&s->d_sbin_pair, b.spair));
   STCHK(upload(&s->d_tls_slot, s->tls_slot));
+  dfree(s->d_amp);
+  if (sp.places) HIPCHK(dalloc(&s->d_amp, (size_t)3 * M * sizeof(double)));
   return MLK_OK;
 }
 
@@ -1046,6 +1052,7 @@ void release(mlk_sim* s) {
   dfree(s->d_gamma);
   dfree(s->d_Et);
   dfree(s->d_mudot);
+  dfree(s->d_amp);
   dfree(s->d_popoff);
   dfree(s->d_tls_gid);
   dfree(s->d_tls_w0);
@@ -2771,14 +2778,21 @@ mlk_status enqueue_batch_step(mlk_batch* b, const BatchTables<T>& t) {
   for (int n = 2; n <= kMaxLevels; ++n)
     HIPCHK(ml_batch(b->ml[n].jobs, b->ml[n].start, b->ml[n].njobs, b->ml[n].nblocks, n, st));
   HIPCHK(batch_sweeps(b, t, true));
+  bool amps = false;
+  for (const mlk_sim* s : b->sims)
+    if (s->d_amp) {
+      amps = true;
+      HIPCHK(scatter_amps(bin_ptrs(s), s->d_gamma, s->d_mudot,
+                          s->g.dt * s->g.inv_dx * s->g.inv_dx * s->g.inv_dx, st));
+    }
   if constexpr (f32) HIPCHK(sources_batch_f32(t.sources.jobs, t.sources.start, t.sources.njobs,
                                               t.sources.nblocks, st));
   else HIPCHK(sources_batch_f64(t.sources.jobs, t.sources.start, t.sources.njobs,
                                 t.sources.nblocks, st));
   if constexpr (f32) HIPCHK(scatter_batch_f32(t.scatter.jobs, t.scatter.start, t.scatter.njobs,
-                                              t.scatter.order, t.scatter.norder, st));
+                                              t.scatter.order, t.scatter.norder, amps, st));
   else HIPCHK(scatter_batch_f64(t.scatter.jobs, t.scatter.start, t.scatter.njobs,
-                                t.scatter.order, t.scatter.norder, st));
+                                t.scatter.order, t.scatter.norder, amps, st));
   HIPCHK(detect(t.fpart, 1));
   HIPCHK(detect(t.finish, 2));
   return MLK_OK;
