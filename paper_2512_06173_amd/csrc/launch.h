@@ -72,12 +72,12 @@ hipError_t energy_f64(const FieldPtrs<double>& old, const FieldPtrs<double>& cur
                       const EnergyRec& er, const StepNo& n, hipStream_t st);
 hipError_t energy_f32(const FieldPtrs<float>& old, const FieldPtrs<float>& cur, size_t ncell,
                       const EnergyRec& er, const StepNo& n, hipStream_t st);
-// partials_done: the flux partials of this step are formed already (by the scatter
-// launch), so only the finishing block runs
 hipError_t flux_partial_f64(const FieldPtrs<double>& f, const Geom& g, const FluxPlane& fp,
                             hipStream_t st);
 hipError_t flux_partial_f32(const FieldPtrs<float>& f, const Geom& g, const FluxPlane& fp,
                             hipStream_t st);
+// Closes step n and moves the step counter past it.  partials_done: the flux partials of the
+// step are formed already (by the scatter launch), so only the finishing block runs
 hipError_t finish_f64(const FieldPtrs<double>& f, const Geom& g, const FluxPlane& fp,
                       const Series& ser, const StepNo& n, bool partials_done, hipStream_t st);
 hipError_t finish_f32(const FieldPtrs<float>& f, const Geom& g, const FluxPlane& fp,
@@ -93,8 +93,7 @@ hipError_t bin_gather_f32(const FieldPtrs<float>& f, const Geom& g, const BinPtr
 // Two-level step n of every two-level emitter under E~ (emitter-id order).
 hipError_t tls_step(const TlsPtrs& tls, double dt, const double* Et, double* mudot,
                     const int64_t* pop_off, const Series& ser, const StepNo& n, hipStream_t st);
-// fp: when given, fp->nblocks more workgroups of the same launch form the flux
-// partials of the plane (no window may reach the plane's E cells)
+// more: what else its launch takes (see ScatterMore)
 hipError_t bin_scatter_f64(const FieldPtrs<double>& f, const Geom& g, const BinPtrs& b,
                            const WindowPtrs<double>& win, const double* mudot,
                            const ScatterMore& more, hipStream_t st);
