@@ -143,12 +143,15 @@ def traffic_from_profile(launch_cells, tile):
     txt = open(TRAFFIC_SUMMARY).read()
     want = hashlib.sha256(open(FUSED_SRC, "rb").read()).hexdigest()
     m = re.search(r"kernel_source_sha256:\s*([0-9a-f]{64})", txt)
-    c = re.search(r"cells_per_launch:\s*(\d+)", txt)
-    if not (m and c) or m.group(1) != want or int(c.group(1)) != launch_cells:
+    if not m or m.group(1) != want:
         return None
-    for k in re.finditer(r"tile_traffic:\s*(\d+)\s+(\d+)\s+(\d+)\s+(\d+)\s+([0-9.eE+]+)", txt):
-        if tuple(int(v) for v in k.groups()[:4]) == tuple(tile):
-            return float(k.group(5))
+    cells = None  # of the launches whose tiles follow
+    for k in re.finditer(r"cells_per_launch:\s*(\d+)|"
+                         r"tile_traffic:\s*(\d+)\s+(\d+)\s+(\d+)\s+(\d+)\s+([0-9.eE+]+)", txt):
+        if k.group(1):
+            cells = int(k.group(1))
+        elif cells == launch_cells and tuple(int(v) for v in k.groups()[1:5]) == tuple(tile):
+            return float(k.group(6))
     return None
 
 

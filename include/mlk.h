@@ -403,8 +403,9 @@ mlk_status mlk_get_interior_box(mlk_sim* s, int32_t box[6]);
  * The forward run keeps the whole state every ckpt_every steps in device
  * memory; the reverse pass recomputes one segment at a time from its
  * checkpoint and undoes it, so memory is one state per segment plus one
- * segment of tape, in one block that the call allocates and frees.  The result does not depend on ckpt_every.  Outputs (host
- * memory, written): grad_eps (design-box cells, x fastest; may be NULL),
+ * segment of tape, in one block that the call allocates and frees.  The result
+ * does not depend on ckpt_every.  Outputs (host memory, written): grad_eps
+ * (design-box cells, x fastest; may be NULL),
  * grad_dipole (3 per emitter id; may be NULL), value (the objective).  The sim
  * is left in the state it had before the call.  Multilevel emitters: the call
  * returns MLK_EUNSUPPORTED.  MLK_ENUMERIC when a run inside the call met a
@@ -444,10 +445,10 @@ mlk_status mlk_set_tls_dipoles(mlk_sim* s, int32_t first, int32_t count, const d
  * mlk_batch_replay launches it nreplays times (re-capturing by itself when a
  * recorded series had to grow).  The sims keep their state and can be stepped
  * on their own after mlk_batch_destroy.  Which sweep is the faster one depends on the
- * members (mlk_grid_desc.sweep): 64 domains of 32^3 to 96^3 cells with 8 layers on
- * every face step in 0.50 ms with the plain sweep and 0.51 with the fused one (FP32);
- * where the layers are a smaller part of the domains the fused sweep, which moves
- * fewer bytes, is ahead. */
+ * members (mlk_grid_desc.sweep): with 8 layers on every face and FP32 fields, 64
+ * domains of mixed sizes from 32^3 to 96^3 cells step in 0.50 ms with the plain sweep
+ * and in 0.52 with the fused one, tuned; domains of one size are level at 48^3 and
+ * otherwise up to 19% faster with the fused one (32 of 64^3: 0.25 and 0.20 ms). */
 typedef struct mlk_batch mlk_batch;
 mlk_status mlk_batch_create(mlk_sim* const* sims, int32_t n, mlk_batch** out);
 mlk_status mlk_batch_step(mlk_batch* b, int64_t nsteps);
